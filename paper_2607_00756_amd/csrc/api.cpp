@@ -966,7 +966,7 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
   };
   int max_n1_all = 0;
   for (int a : atoms) max_n1_all = std::max<int>(max_n1_all, (int)n1_of(p->W[a]));
-  const int64_t n_partial_tiles = gram ? GEMM_MAX_ZSPLIT * (max_n1_all / 128) : Dpad / 128;
+  const int64_t n_partial_tiles = gram ? GEMM_MAX_ZSPLIT * (max_n1_all / 128) : Dpad / ABS2_MAP_ROWS;
   // residue cells of the aperture beams (h_y mod S_y, h_x mod S_x), beams ascending in each
   std::vector<int32_t>& cells = p->h_cells;
   cells.assign((size_t)P + 1 + p->B, 0);
@@ -1019,7 +1019,36 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
       b = e;
     }
   }
-  const size_t need = (size_t)(fixed + max_chunk + 16 * 256);
+  size_t need = (size_t)(fixed + max_chunk + 16 * 256);
+  // Partial products of contractions split over K segments (Gram) or job
+  // groups (per-beam): as much as the launches want, within kSplitBytes, and
+  // with a caller-given workspace within what the rest of the call leaves.
+  int64_t split_cap = kSplitBytes;
+  if (ext_work) split_cap = std::min<int64_t>(split_cap, (int64_t)ext_bytes - (int64_t)need);
+  const int det_epi = map_direct ? EPI_ABS2_MAP : EPI_ABS2_BEAMS;
+  int det_m, det_n, quad_m, quad_n;
+  gemm_tile(precision, det_epi, det_m, det_n);
+  gemm_tile(precision, EPI_QUAD, quad_m, quad_n);
+  const int64_t slice_bytes = map_direct ? Dpad / det_m * Ppad * 4 : (int64_t)P * p->ndet * 4;
+  auto det_groups = [&](int njobs) {  // job groups of a per-beam launch of njobs jobs
+    return abs2_groups((Dpad / det_m) * (Ppad / det_n), njobs, p->n_cu, std::max<int64_t>(0, split_cap) / slice_bytes);
+  };
+  std::vector<int64_t> gram_n(chunks.size(), 0);  // Gram tiles and K segments of each chunk
+  std::vector<int> gram_k(chunks.size(), 1);
+  int64_t split_bytes = 0;
+  for (size_t c = 0; c < chunks.size(); ++c) {
+    if (gram) {
+      for (int i = chunks[c].first; i < chunks[c].second; ++i)
+        gram_n[c] += gemm_gram_tiles(p->W[atoms[i]] * p->W[atoms[i]], gram_prec, fixed_order(p));
+      if (!fixed_order(p)) gram_k[c] = gemm_gram_ksplit(gram_prec, gram_n[c], (int)Dk, p->n_cu, split_cap);
+      if (gram_n[c] * gram_k[c] > INT32_MAX / 2) return err(BIP_EUNSUPPORTED, "Gram launch beyond the grid limit");
+      if (gram_k[c] > 1) split_bytes = std::max(split_bytes, gram_n[c] * gram_k[c] * gemm_gram_part_bytes(gram_prec));
+    } else {
+      const int z = det_groups((chunks[c].second - chunks[c].first) * n_ch);
+      if (z > 1) split_bytes = std::max(split_bytes, z * slice_bytes);
+    }
+  }
+  if (!ext_work || split_bytes > 0) need += (size_t)roundup(split_bytes, 256);
   char* work_base = nullptr;
   size_t work_cap = 0;
   if (ext_work) {
@@ -1169,16 +1198,9 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
   }
   GemmJob* d_jdet = d_jobs;
   GemmJob* d_jquad = d_jdet + jdet.size();
-  // Gram launches: one per chunk over its atoms' jobs (their slot rows set here)
-  std::vector<int64_t> gram_gx(chunks.size(), 0);
-  if (gram)
-    for (size_t c = 0; c < chunks.size(); ++c) {
-      int tiles = 0;
-      for (int i = chunks[c].first; i < chunks[c].second; ++i)
-        tiles = std::max(tiles, (int)(n1_of(p->W[atoms[i]]) / 128));
-      gram_gx[c] = gemm_gram_plan(&jdet[det_first[chunks[c].first]], chunks[c].second - chunks[c].first, tiles);
-      if (gram_gx[c] > 0x7fffffff) return err(BIP_EUNSUPPORTED, "Gram launch beyond the grid limit");
-    }
+  if (gram)  // Gram launches: one per chunk over its atoms' jobs (their tile offsets set here)
+    for (size_t c = 0; c < chunks.size(); ++c)
+      gemm_gram_plan(&jdet[det_first[chunks[c].first]], chunks[c].second - chunks[c].first, gram_prec, fixed_order(p));
   HIPCHK(hipMemcpyAsync(d_probe, jprobe.data(), jprobe.size() * sizeof(ProbeJob), hipMemcpyHostToDevice, st), "jobs");
   if (p->focal && !jfocal.empty())
     HIPCHK(hipMemcpyAsync(d_fjobs, jfocal.data(), jfocal.size() * sizeof(FocalProbeJob), hipMemcpyHostToDevice, st),
@@ -1221,8 +1243,9 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
     char* X2 = (char*)ws.take(pl2 * csz);   // Q (Gram) or U (direct)
     char* PsiT = (char*)ws.take(std::max<int64_t>(pl3, 1) * csz);
     float* PsiC = p->focal ? (float*)ws.take(std::max<int64_t>(pl4, 1) * 8) : nullptr;
+    void* split_buf = split_bytes > 0 ? ws.take(split_bytes) : nullptr;
     if (ws.used > work_cap) return err(BIP_ENOMEM, "internal: chunk exceeds the workspace");
-    int max_n1 = 0, max_kd = 0, max_m = 0;
+    int max_n1 = 0, max_kd = 0, max_kd_w = 0, max_m = 0;
     const int c0 = chunks[c].first, c1 = chunks[c].second, nat = c1 - c0;
     for (int i = c0; i < c1; ++i) {
       const int a = atoms[i];
@@ -1231,6 +1254,7 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
       sizes(a, s);
       max_n1 = std::max<int>(max_n1, (int)n1_of(W));
       max_kd = std::max<int>(max_kd, (int)kd_of(W1));
+      max_kd_w = std::max<int>(max_kd_w, (int)kd_of(W));
       max_m = std::max(max_m, W1);
       if (off[0][i] + s[0] > pl0 || off[1][i] + s[1] > pl1 || off[2][i] + s[2] > pl2 ||
           off[3][i] + s[3] > pl3 || off[4][i] + s[4] > pl4)
@@ -1318,11 +1342,13 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
       q.njobs = nat;
       q.out = X2;
       q.out_plane = pl2;
-      q.tiles = max_n1 / 128;
+      q.ksplit = gram_k[c];
+      q.whole_diag = fixed_order(p);
+      q.gpart = (float4*)split_buf;
       q.gscale = (float)(p->f * p->f) / (gram_scale * gram_scale);
       q.qtri = 1;
       HIPCHK(timed(p, ST_GRAM, st, [&] {
-               return launch_zgemm_gram(gram_prec, precision, q, (int)gram_gx[c], st);
+               return launch_zgemm_gram(gram_prec, precision, q, (int)gram_n[c], st);
              }),
              "Gram contraction");
       GemmArgs u = g;
@@ -1334,15 +1360,17 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
       u.njobs = nat;
       u.partial = partial;
       u.qtri = 1;
-      // job groups that fill the chip evenly; partial rows reduced in a fixed order
-      const int qt = (int)(Ppad / 128) * (max_n1 / 128);
-      u.zsplit = quad_groups(qt, nat, p->n_cu);
-      HIPCHK(timed(p, ST_DET, st, [&] {
-               return launch_zgemm(precision, EPI_QUAD, u, (int)(Ppad / 128), max_n1 / 128, u.zsplit, st);
-             }),
+      // job groups and K segments that fill the chip evenly; partial rows reduced in a fixed order
+      const int mt = (int)(Ppad / quad_m), nt = max_n1 / quad_n;
+      int zj = 1;
+      u.ksplit = 1;
+      if (fixed_order(p)) zj = quad_groups(Ppad / 128 * nt, nat, p->n_cu);
+      else quad_split((int64_t)mt * nt, nat, max_kd_w / gemm_bk(precision), p->n_cu, zj, u.ksplit);
+      u.zsplit = zj * u.ksplit;
+      HIPCHK(timed(p, ST_DET, st, [&] { return launch_zgemm(precision, EPI_QUAD, u, mt, nt, u.zsplit, st); }),
              "quadratic form");
       HIPCHK(timed(p, ST_REDUCE, st, [&] {
-               return launch_reduce_map(partial, u.zsplit * (max_n1 / 128), (int)Ppad, P, out, 1, st);
+               return launch_reduce_map(partial, u.zsplit * nt, (int)Ppad, P, out, 1, st);
              }),
              "reduce");
     } else {
@@ -1356,14 +1384,19 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
       d.partial = partial;
       d.out_beams = beams_out;
       d.Npad = (int)Ppad;
+      const int mt = (int)(Dpad / det_m), nt = (int)(Ppad / det_n);
+      d.zsplit = det_groups(d.njobs);
+      if (d.zsplit > 1) {  // a slice per job group
+        if (map_direct) d.partial = (float*)split_buf;
+        else d.slices = (float*)split_buf;
+      }
       HIPCHK(timed(p, ST_DET, st, [&] {
-               return launch_zgemm(precision, map_direct ? EPI_ABS2_MAP : EPI_ABS2_BEAMS, d,
-                                   (int)(Dpad / 128), (int)(Ppad / 128), 1, st);
+               return launch_zgemm(precision, det_epi, d, mt, nt, d.zsplit, st);
              }),
              "detector contraction");
       if (map_direct)
         HIPCHK(timed(p, ST_REDUCE, st, [&] {
-                 return launch_reduce_map(partial, (int)(Dpad / 128), (int)Ppad, P, out, 1, st);
+                 return launch_reduce_map(d.partial, d.zsplit * mt, (int)Ppad, P, out, 1, st);
                }),
                "reduce");
     }

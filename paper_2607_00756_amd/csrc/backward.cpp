@@ -179,6 +179,16 @@ int bip_eels_backward(bip_plan* p, int32_t n_ch, const float* H, const int64_t* 
   const int64_t budget = (int64_t)(budget_gb * (1 << 30));
   const int nat_max =
       (int)std::max<int64_t>(1, std::min<int64_t>(p->n_atoms, (budget - (int64_t)fixed) / per_atom));
+  // Gram tiles of each chunk of nat_max atoms (the Gram runs unsplit: fixed_order)
+  std::vector<int64_t> gram_n;
+  for (int c0 = 0; c0 < p->n_atoms; c0 += nat_max) {
+    int64_t n = 0;
+    for (int a = c0; a < std::min(p->n_atoms, c0 + nat_max); ++a) n += gemm_gram_tiles(p->W[a] * p->W[a], gprec, 1);
+    if (n > INT32_MAX / 2) return err(BIP_EUNSUPPORTED, "Gram launch beyond the grid limit");
+    gram_n.push_back(n);
+  }
+  int gt, gtn;
+  gemm_tile(prec, EPI_STORE, gt, gtn);
   int rc = ensure_work(p, fixed + (size_t)nat_max * per_atom + 4096, st);
   if (rc) return rc;
   Workspace ws{(char*)p->d_work, 0};
@@ -298,15 +308,7 @@ int bip_eels_backward(bip_plan* p, int32_t n_ch, const float* H, const int64_t* 
     sj.W2 = W2;
     sj.ldo = (int32_t)kd;
   }
-  // Gram launches: one per chunk of nat_max atoms (their slot rows set here)
-  std::vector<int64_t> gram_gx;
-  for (int c0 = 0; c0 < na; c0 += nat_max) {
-    const int nat = std::min(nat_max, na - c0);
-    int tiles = 0;
-    for (int a = c0; a < c0 + nat; ++a) tiles = std::max(tiles, (int)(roundup((int64_t)p->W[a] * p->W[a], 128) / 128));
-    gram_gx.push_back(gemm_gram_plan(&hj[c0], nat, tiles));
-    if (gram_gx.back() > 0x7fffffff) return err(BIP_EUNSUPPORTED, "Gram launch beyond the grid limit");
-  }
+  for (int c0 = 0; c0 < na; c0 += nat_max) gemm_gram_plan(&hj[c0], std::min(nat_max, na - c0), gprec, 1);
   HIPCHK(hipMemcpyAsync(d_jobs, hj.data(), hj.size() * sizeof(GemmJob), hipMemcpyHostToDevice, st), "jobs");
   for (int c0 = 0; c0 < na; c0 += nat_max) {
     const int nat = std::min(nat_max, na - c0);
@@ -349,9 +351,10 @@ int bip_eels_backward(bip_plan* p, int32_t n_ch, const float* H, const int64_t* 
     ga.out = Qp;
     ga.out_plane = NA * bQ;
     ga.out2 = Gm;
-    ga.tiles = max_n1 / 128;
+    ga.ksplit = 1;
+    ga.whole_diag = 1;
     ga.gscale = 1.f / (gsc * gsc);
-    HIPCHK(launch_zgemm_gram(gprec, prec, ga, (int)gram_gx[c0 / nat_max], st), "Gram");
+    HIPCHK(launch_zgemm_gram(gprec, prec, ga, (int)gram_n[c0 / nat_max], st), "Gram");
     // R = conj(psi) diag(Ibar) psi^T over the raster
     GemmArgs gr{};
     gr.A = A1;
@@ -361,7 +364,7 @@ int bip_eels_backward(bip_plan* p, int32_t n_ch, const float* H, const int64_t* 
     gr.njobs = nat;
     gr.out = R;
     gr.m_store = max_n1;
-    HIPCHK(launch_zgemm(prec, EPI_STORE + EPI_CONJ_A, gr, max_n1 / 128, max_n1 / 128, nat, st), "R");
+    HIPCHK(launch_zgemm(prec, EPI_STORE + EPI_CONJ_A, gr, max_n1 / gt, max_n1 / gtn, nat, st), "R");
     for (int a = c0; a < c0 + nat; ++a) {
       const int64_t i = a - c0;
       const int W2 = p->W[a] * p->W[a];
@@ -380,7 +383,7 @@ int bip_eels_backward(bip_plan* p, int32_t n_ch, const float* H, const int64_t* 
     gp.out = gpsi;
     gp.rowscale = ibar;
     gp.m_store = (int)Ppad;
-    HIPCHK(launch_zgemm(prec, EPI_STORE, gp, (int)(Ppad / 128), max_n1 / 128, nat, st), "g_psi");
+    HIPCHK(launch_zgemm(prec, EPI_STORE, gp, (int)(Ppad / gt), max_n1 / gtn, nat, st), "g_psi");
     GemmArgs gs{};
     gs.A = S2d;
     gs.a_plane = NA * bS2d;
@@ -390,7 +393,7 @@ int bip_eels_backward(bip_plan* p, int32_t n_ch, const float* H, const int64_t* 
     gs.njobs = nat;
     gs.out = gS2;
     gs.m_store = (int)Dpad;
-    HIPCHK(launch_zgemm(prec, EPI_STORE, gs, (int)(Dpad / 128), max_n1 / 128, nat, st), "g_S2");
+    HIPCHK(launch_zgemm(prec, EPI_STORE, gs, (int)(Dpad / gt), max_n1 / gtn, nat, st), "g_S2");
     for (int a = c0; a < c0 + nat; ++a) {
       const int64_t i = a - c0;
       const int W2 = p->W[a] * p->W[a];

@@ -50,7 +50,7 @@ struct GemmJob {
                          // B (0: contiguous; K-blocked operands: row count x chunk width)
   int32_t cu0, cnu;      // crop mask of the atom (GemmArgs::crop): raster rows u with
   int32_t cv0, cnv;      // (u - cu0) mod S_y < cnu and columns v with (v - cv0) mod S_x < cnv
-  int32_t s0;            // EPI_GRAMQ: first slot row of the job's tiles (set by gemm_gram_plan)
+  int32_t s0;            // EPI_GRAMQ: workgroup tiles of the jobs before it (set by gemm_gram_plan)
   int32_t pad;
 };
 
@@ -78,8 +78,13 @@ struct GemmArgs {
   float* partial;            // map partial sums
   float* out_beams;          // [P][ndet] (EPI_ABS2_BEAMS)
   int ndet, P;
-  int tiles;                 // EPI_GRAMQ: 128-row tiles per side (upper triangle launched)
-  int zsplit;                // EPI_QUAD: job groups along grid z, one partial row each
+  int zsplit;                // EPI_ABS2_*: job groups along grid z; EPI_QUAD: job groups x K segments,
+                             // one partial row each
+  int ksplit;                // EPI_GRAMQ, EPI_QUAD: K segments of every job (1: whole)
+  int whole_diag;            // EPI_GRAMQ: every tile of a 128 x 128 block on the diagonal computed
+  int nunits;                // EPI_GRAMQ: tiles x ksplit (set by launch_zgemm_gram)
+  float4* gpart;             // EPI_GRAMQ: partial products of ksplit > 1 (gemm_gram_part_bytes a unit)
+  float* slices;             // EPI_ABS2_BEAMS: [zsplit][P][ndet] of zsplit > 1
   float2* out2;              // EPI_GRAMQ: also store G itself (complex64 [r][r'], pitch ldo)
   const float* rowscale;     // EPI_STORE: optional real factor per output row
   int m_store;               // EPI_STORE: rows >= m_store are not written
@@ -414,18 +419,26 @@ hipError_t launch_atom_grad_sum(const double* out, const int64_t* first, int n_a
                                 double* dxyz, hipStream_t s);
 
 // contraction (k_gemm.hip)
-// grid: (m_tiles, n_tiles, z) for EPI_ABS2_* and EPI_QUAD (z = g.zsplit), (m_tiles,
-// n_tiles, njobs) for EPI_STORE; for EPI_GRAMQ a 1-D grid of the gemm_gram_plan count
-// for the launch's jobs.  epi EPI_STORE + EPI_CONJ_A conjugates the A operand.
+// Rows and columns of a workgroup's output tile.
+void gemm_tile(int prec, int epi, int& m, int& n);
+// grid, in tiles: (m_tiles, n_tiles, z) for EPI_ABS2_* and EPI_QUAD (z = g.zsplit),
+// (m_tiles, n_tiles, njobs) for EPI_STORE.  epi EPI_STORE + EPI_CONJ_A conjugates the A operand.
 constexpr int EPI_CONJ_A = 16;
-// EPI_GRAMQ: operands in in_prec, Q stored in out_prec (equal, or FP16 -> SPLIT_BF16)
-hipError_t launch_zgemm_gram(int in_prec, int out_prec, const GemmArgs& g, int gx, hipStream_t s);
+constexpr int ABS2_MAP_ROWS = 128;  // detector rows of an EPI_ABS2_MAP workgroup
+// EPI_GRAMQ: operands in in_prec, Q stored in out_prec (equal, or FP16 -> SPLIT_BF16); tiles: the
+// sum of gemm_gram_tiles over the launch's jobs
+hipError_t launch_zgemm_gram(int in_prec, int out_prec, const GemmArgs& g, int tiles, hipStream_t s);
 hipError_t launch_zgemm(int prec, int epi, const GemmArgs& g, int gx, int gy, int gz,
                         hipStream_t s);
-// Workgroups of an EPI_GRAMQ launch over the host copies jobs[0 .. njobs) (tiles:
-// the largest job's tiles per side, g.tiles); sets each job's s0.  Call before the
-// jobs are uploaded.
-int64_t gemm_gram_plan(GemmJob* jobs, int njobs, int tiles);
+// Workgroup tiles of an EPI_GRAMQ job of n_lim rows.
+int64_t gemm_gram_tiles(int n_lim, int prec, int whole_diag);
+// Sets s0 of the jobs of one EPI_GRAMQ launch.  Call before they are uploaded.
+void gemm_gram_plan(GemmJob* jobs, int njobs, int prec, int whole_diag);
+// K segments of an EPI_GRAMQ launch of `tiles` tiles of contraction length K: the count with the
+// least modelled time whose partial tiles (gemm_gram_part_bytes each) fit in part_bytes.
+int gemm_gram_ksplit(int prec, int64_t tiles, int K, int n_cu, int64_t part_bytes);
+int64_t gemm_gram_part_bytes(int prec);
+// Most partial rows of the quadratic form per 128 columns, and most job groups.
 constexpr int GEMM_MAX_ZSPLIT = 16;
 int gemm_bk(int prec);
 hipError_t launch_reduce_map(const float* partial, int ntiles, int Ppad, int P, float* out,

@@ -162,18 +162,66 @@ inline int balanced_batch(int n, int cap) {
   return (int)((n + nb - 1) / nb);
 }
 
-// Job groups of the quadratic form.  Its workgroups hold a CU each (LDS), so
-// qt tiles x z groups run in ceil(qt z / n_cu) rounds of ceil(nat / z) jobs
-// per workgroup: take the z with the fewest job-rounds, the smallest on ties
+// Most a launch may add to the workspace for partial products of split
+// contractions.
+constexpr int64_t kSplitBytes = (int64_t)512 << 20;
+
+// Plans that keep checkpoints differentiate the map: their contractions run
+// whole (no K segments, every tile of a diagonal block), in the job groups of
+// quad_groups, so that a gradient does not move with the splits chosen below.
+inline bool fixed_order(const bip_plan* p) { return p->o.ckpt_stride > 0; }
+
+// Job groups of the quadratic form without K segments: qt tiles of 128 x 128 x
+// z groups run in ceil(qt z / n_cu) rounds of ceil(nat / z) jobs per
+// workgroup: take the z with the fewest job-rounds, the smallest on ties
 // (fewer partial rows to reduce).
-inline int quad_groups(int qt, int nat, int n_cu) {
+inline int quad_groups(int64_t qt, int nat, int n_cu) {
   int best = 1;
   int64_t cost = INT64_MAX;
   for (int z = 1; z <= std::min(GEMM_MAX_ZSPLIT, nat); ++z) {
-    const int64_t c = ((int64_t)qt * z + n_cu - 1) / n_cu * ((nat + z - 1) / z);
+    const int64_t c = (qt * z + n_cu - 1) / n_cu * ((nat + z - 1) / z);
     if (c < cost) {
       cost = c;
       best = z;
+    }
+  }
+  return best;
+}
+
+// Job groups (z) and K segments (k) of the quadratic form: qt tiles x z x k
+// workgroups give a CU ceil(qt z k / n_cu) of them, of ceil(nat / z) jobs of
+// ceil(chunks / k) K chunks, each job with about kQuadFill chunk times of
+// filling and epilogue (psi staging).  Take the pair with the least modelled
+// time, at most GEMM_MAX_ZSPLIT partial rows; the smaller on ties (fewer rows
+// to reduce).
+constexpr double kQuadFill = 6.0;
+inline void quad_split(int64_t qt, int nat, int chunks, int64_t n_cu, int& z_out, int& k_out) {
+  z_out = k_out = 1;
+  double cost = 1e300;
+  for (int z = 1; z <= std::min(GEMM_MAX_ZSPLIT, nat); ++z)
+    for (int k = 1; z * k <= GEMM_MAX_ZSPLIT && k <= std::max(1, chunks / 2); ++k) {
+      const double c = (double)((qt * z * k + n_cu - 1) / n_cu) * (double)((nat + z - 1) / z) *
+                       ((double)((chunks + k - 1) / k) + kQuadFill);
+      if (c < 0.999 * cost) {
+        z_out = z;
+        k_out = k;
+        cost = c;
+      }
+    }
+}
+
+// Job groups of the per-beam products: tiles x z workgroups, ceil(tiles z /
+// n_cu) of them per CU, of ceil(njobs / z) jobs each.  More than one group costs a slice of
+// the output each, written and summed: only for a gain above a tenth, and only
+// while the slices fit in max_z.
+inline int abs2_groups(int64_t tiles, int njobs, int64_t n_cu, int64_t max_z) {
+  int best = 1;
+  double cost = 1e300;
+  for (int z = 1; z <= std::min<int64_t>({GEMM_MAX_ZSPLIT, njobs, std::max<int64_t>(1, max_z)}); ++z) {
+    const double c = (double)((tiles * z + n_cu - 1) / n_cu) * (double)((njobs + z - 1) / z);
+    if (c < 0.9 * cost) {
+      best = z;
+      cost = c;
     }
   }
   return best;
