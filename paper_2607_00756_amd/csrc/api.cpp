@@ -629,7 +629,8 @@ int bip_plan_create(const bip_grid* grid, const bip_optics* optics, int32_t n_at
   if (p->focal) {
     for (int a = 0; a < n_atoms; ++a)
       fatoms.push_back(FocalAtom{p->off1[a], p->W1[a], p->W[a], p->oy1[a], p->ox1[a], p->plane[a], a});
-    if ((rc = upload(p, &p->d_fatoms, fatoms, st)) || (rc = dalloc(p, &p->d_fdist, (size_t)n_atoms, st)))
+    if ((rc = upload(p, &p->d_fatoms, fatoms, st)) || (rc = dalloc(p, &p->d_fdist, (size_t)n_atoms, st)) ||
+        (rc = dalloc(p, &p->d_fker, (size_t)n_atoms * focal_kernel_elems(), st)))
       return fail(rc);
   }
   if (o.ckpt_stride >= 1) {
@@ -694,6 +695,8 @@ int bip_build_smatrix(bip_plan* p, const float* V, void* stream) {
   // ---- focal back-propagation of the S1 windows to each atom's centroid plane
   if (p->focal) {
     HIPCHK(launch_focal_dist(V, p->d_fatoms, p->n_atoms, g.ny, g.nx, g.dz, p->d_fdist, st), "focal distance");
+    HIPCHK(launch_focal_kernel(p->d_fatoms, p->n_atoms, p->d_fdist, g.ly / g.ny, g.lx / g.nx, p->lambda, p->d_fker, st),
+           "focal kernels");
     HIPCHK(launch_focal_parents(p->d_win1, p->d_fatoms, p->n_atoms, p->d_fdist, p->d_par1, p->Bp1,
                                 p->focal_max_m, g.ny, g.nx, g.ly / g.ny, g.lx / g.nx, p->lambda, p->d_tw, p->L,
                                 st),
@@ -949,20 +952,18 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
   auto n1_of = [](int W) { return roundup((int64_t)W * W, 128); };  // ... to whole tiles
   auto ldf_of = [](int W) { return roundup((int64_t)W * W, 64); };  // DFT workspace pitch
   // per-atom blocks, in buffer order: [0] DFT workspace (complex64 elements),
-  // [1..3] contraction operands (plane elements), [4] in focal mode the probe
-  // at the centroid on the enlarged window (FP32 planes)
+  // [1..3] contraction operands (plane elements)
   auto sizes = [&](int a, int64_t* s) {
     const int W = p->W[a], W1 = p->W1[a];
     s[0] = (int64_t)P * ldf_of(W1);                                // X [S_y][S_x][r] (S1 window)
     s[1] = gram ? n1_of(W) * Dk : Dpad * kd_of(W);                 // S2~^T [r][d] | S2~ [d][r]
     s[2] = gram ? n1_of(W) * kd_of(W) : (int64_t)n_ch * Ppad * kd_of(W);  // Q [r][r'] | U_n [rho][r]
     s[3] = gram ? Ppad * kd_of(W) : 0;                             // psi^T [rho][r]
-    s[4] = p->focal ? Ppad * kd_of(W1) : 0;                        // psi at the centroid
   };
   auto atom_bytes = [&](int a) {
-    int64_t s[5];
+    int64_t s[4];
     sizes(a, s);
-    return s[0] * 8 + (s[1] + s[2] + s[3]) * csz + s[4] * 8;
+    return s[0] * 8 + (s[1] + s[2] + s[3]) * csz;
   };
   int max_n1_all = 0;
   for (int a : atoms) max_n1_all = std::max<int>(max_n1_all, (int)n1_of(p->W[a]));
@@ -1000,7 +1001,7 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
   const int64_t fixed = n_partial_tiles * Ppad * 4 +
                         (out_mode == BIP_OUT_QEELS ? (int64_t)P * p->ndet * 4 : 0) +
                         n_jobs_total * (int64_t)sizeof(GemmJob) +
-                        (int64_t)atoms.size() * (int64_t)(sizeof(ProbeJob) + sizeof(FocalProbeJob)) + 64 +
+                        (int64_t)atoms.size() * (int64_t)sizeof(ProbeJob) * (p->focal ? 2 : 1) + 64 +
                         (int64_t)cells.size() * 4 + (int64_t)tws.size() * 8 + (1 << 20);
   // chunking: consecutive atoms while the per-chunk operands fit the budget
   std::vector<std::pair<int, int>> chunks;
@@ -1077,7 +1078,7 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
   int32_t* d_cells = (int32_t*)ws.take(cells.size() * 4);
   float2* d_tws = (float2*)ws.take(tws.size() * 8);
   ReconAtom* d_ratoms = (ReconAtom*)ws.take(atoms.size() * sizeof(ReconAtom));
-  FocalProbeJob* d_fjobs = p->focal ? (FocalProbeJob*)ws.take(atoms.size() * sizeof(FocalProbeJob) + 64) : nullptr;
+  ProbeJob* d_fjobs = p->focal ? (ProbeJob*)ws.take(atoms.size() * sizeof(ProbeJob)) : nullptr;
   const size_t chunk_base = ws.used;
   if (ws.used > work_cap) return err(BIP_ENOMEM, "internal: tables exceed the workspace");
   HIPCHK(hipMemcpyAsync(d_cells, cells.data(), cells.size() * 4, hipMemcpyHostToDevice, st), "cells");
@@ -1091,22 +1092,22 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
   jprobe.clear();
   jdet.clear();
   jquad.clear();
-  std::vector<int64_t> off[5];
-  std::vector<int64_t> chunk_plane[5];
+  std::vector<int64_t> off[4];
+  std::vector<int64_t> chunk_plane[4];
   for (auto& v : chunk_plane) v.assign(chunks.size(), 0);
   for (size_t c = 0; c < chunks.size(); ++c) {
-    int64_t acc[5] = {0, 0, 0, 0, 0};
+    int64_t acc[4] = {0, 0, 0, 0};
     for (int i = chunks[c].first; i < chunks[c].second; ++i) {
-      int64_t s[5];
+      int64_t s[4];
       sizes(atoms[i], s);
-      for (int k = 0; k < 5; ++k) {
+      for (int k = 0; k < 4; ++k) {
         off[k].push_back(acc[k]);
         acc[k] += s[k];
       }
     }
-    for (int k = 0; k < 5; ++k) chunk_plane[k][c] = acc[k];
+    for (int k = 0; k < 4; ++k) chunk_plane[k][c] = acc[k];
   }
-  std::vector<FocalProbeJob>& jfocal = p->h_fjobs;
+  std::vector<ProbeJob>& jfocal = p->h_fjobs;
   jfocal.clear();
   std::vector<int64_t> det_first(atoms.size());
   for (size_t i = 0; i < atoms.size(); ++i) {
@@ -1126,16 +1127,15 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
     pj.ox = p->ox[a];
     pj.kd = kd;
     pj.ldf = (int32_t)ldf_of(W);
-    if (p->focal) {  // the probe at the centroid on the enlarged window, then the forward step
+    pj.atom = a;
+    if (p->focal) {  // folded on the enlarged window; after the forward step the window's own job follows
       const int W1 = p->W1[a];
-      pj.out_off = off[4][i];
+      pj.ldf = (int32_t)ldf_of(W1);
+      jfocal.push_back(pj);
       pj.W = W1;
       pj.oy = p->oy1[a];
       pj.ox = p->ox1[a];
       pj.kd = (int32_t)kd_of(W1);
-      pj.ldf = (int32_t)ldf_of(W1);
-      jfocal.push_back(FocalProbeJob{off[4][i], gram ? off[3][i] : off[2][i], H_off[a], W1, W, kd,
-                                     (int32_t)kd_of(W1), a, 0});
     }
     pj.t0 = jprobe.empty() ? 0 : jprobe.back().t0 + (jprobe.back().W * jprobe.back().W + 63) / 64;
     jprobe.push_back(pj);
@@ -1203,7 +1203,7 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
       gemm_gram_plan(&jdet[det_first[chunks[c].first]], chunks[c].second - chunks[c].first, gram_prec, fixed_order(p));
   HIPCHK(hipMemcpyAsync(d_probe, jprobe.data(), jprobe.size() * sizeof(ProbeJob), hipMemcpyHostToDevice, st), "jobs");
   if (p->focal && !jfocal.empty())
-    HIPCHK(hipMemcpyAsync(d_fjobs, jfocal.data(), jfocal.size() * sizeof(FocalProbeJob), hipMemcpyHostToDevice, st),
+    HIPCHK(hipMemcpyAsync(d_fjobs, jfocal.data(), jfocal.size() * sizeof(ProbeJob), hipMemcpyHostToDevice, st),
            "jobs");
   HIPCHK(hipMemcpyAsync(d_jdet, jdet.data(), jdet.size() * sizeof(GemmJob), hipMemcpyHostToDevice, st), "jobs");
   if (!jquad.empty())
@@ -1237,27 +1237,25 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
   for (size_t c = 0; c < chunks.size(); ++c) {
     ws.used = chunk_base;
     const int64_t pl0 = chunk_plane[0][c], pl1 = chunk_plane[1][c], pl2 = chunk_plane[2][c],
-                  pl3 = chunk_plane[3][c], pl4 = chunk_plane[4][c];
+                  pl3 = chunk_plane[3][c];
     float2* X = (float2*)ws.take(pl0 * 8);
     char* S2op = (char*)ws.take(pl1 * csz);
     char* X2 = (char*)ws.take(pl2 * csz);   // Q (Gram) or U (direct)
     char* PsiT = (char*)ws.take(std::max<int64_t>(pl3, 1) * csz);
-    float* PsiC = p->focal ? (float*)ws.take(std::max<int64_t>(pl4, 1) * 8) : nullptr;
     void* split_buf = split_bytes > 0 ? ws.take(split_bytes) : nullptr;
     if (ws.used > work_cap) return err(BIP_ENOMEM, "internal: chunk exceeds the workspace");
-    int max_n1 = 0, max_kd = 0, max_kd_w = 0, max_m = 0;
+    int max_n1 = 0, max_kd = 0, max_m = 0;
     const int c0 = chunks[c].first, c1 = chunks[c].second, nat = c1 - c0;
     for (int i = c0; i < c1; ++i) {
       const int a = atoms[i];
       const int W = p->W[a], W1 = p->W1[a];
-      int64_t s[5];
+      int64_t s[4];
       sizes(a, s);
       max_n1 = std::max<int>(max_n1, (int)n1_of(W));
-      max_kd = std::max<int>(max_kd, (int)kd_of(W1));
-      max_kd_w = std::max<int>(max_kd_w, (int)kd_of(W));
+      max_kd = std::max<int>(max_kd, (int)kd_of(W));
       max_m = std::max(max_m, W1);
       if (off[0][i] + s[0] > pl0 || off[1][i] + s[1] > pl1 || off[2][i] + s[2] > pl2 ||
-          off[3][i] + s[3] > pl3 || off[4][i] + s[4] > pl4)
+          off[3][i] + s[3] > pl3)
         return err(BIP_EINVAL, "internal: operand block outside its buffer");
       if (gram && !recon_batched) {
         ReconArgs ra = recon_args(p, a, 2);
@@ -1292,35 +1290,15 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
     const int n_units = jprobe[c1 - 1].t0 + (jprobe[c1 - 1].W * jprobe[c1 - 1].W + 63) / 64 - unit0;
     HIPCHK(timed(p, ST_FOLD, st, [&] { return launch_probe_fold_x(pa, unit0, n_units, nat, st); }),
            "probe fold");
-    if (!p->focal) {
-      HIPCHK(timed(p, ST_PROBE, st, [&] { return launch_probe_y(pa, precision, !gram, max_kd, nat, st); }),
-             "probe synthesis");
-    } else {
-      // the probe at the centroid (FP32) on the enlarged window, then its forward
-      // step to the ionization plane, cropped to the window, into the operand
-      pa.out = PsiC;
-      pa.out_plane = pl4;
-      HIPCHK(timed(p, ST_PROBE, st, [&] { return launch_probe_y(pa, BIP_PREC_FP32, false, max_kd, nat, st); }),
-             "probe synthesis");
-      FocalProbeArgs fp{};
-      fp.jobs = d_fjobs + c0;
-      fp.psi_c = PsiC;
-      fp.psi_plane = pl4;
-      fp.out = gram ? (void*)PsiT : (void*)X2;
-      fp.out_plane = gram ? pl3 : pl2;
-      fp.H = (const float2*)H;
-      fp.n_ch = n_ch;
-      fp.P = P;
-      fp.Ppad = (int)Ppad;
-      fp.L = p->L;
-      fp.tw = p->d_tw;
-      fp.dy = p->g.ly / p->g.ny;
-      fp.dx = p->g.lx / p->g.nx;
-      fp.lambda = p->lambda;
-      fp.dist = p->d_fdist;
-      HIPCHK(timed(p, ST_PROBE, st, [&] { return launch_focal_probe(fp, precision, !gram, nat, max_m, st); }),
+    if (p->focal) {  // step forward to the ionization plane, crop to the window
+      HIPCHK(timed(p, ST_PROBE, st, [&] {
+               return launch_focal_step(d_probe + c0, d_fjobs + c0, p->d_fker, X, P, nat, max_m, st);
+             }),
              "focal probe step");
+      pa.jobs = d_fjobs + c0;
     }
+    HIPCHK(timed(p, ST_PROBE, st, [&] { return launch_probe_y(pa, precision, !gram, max_kd, nat, st); }),
+           "probe synthesis");
     GemmArgs g{};
     g.H = (const float2*)H;
     g.n_ch = n_ch;
@@ -1365,7 +1343,7 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
       int zj = 1;
       u.ksplit = 1;
       if (fixed_order(p)) zj = quad_groups(Ppad / 128 * nt, nat, p->n_cu);
-      else quad_split((int64_t)mt * nt, nat, max_kd_w / gemm_bk(precision), p->n_cu, zj, u.ksplit);
+      else quad_split((int64_t)mt * nt, nat, max_kd / gemm_bk(precision), p->n_cu, zj, u.ksplit);
       u.zsplit = zj * u.ksplit;
       HIPCHK(timed(p, ST_DET, st, [&] { return launch_zgemm(precision, EPI_QUAD, u, mt, nt, u.zsplit, st); }),
              "quadratic form");

@@ -106,6 +106,7 @@ struct ProbeJob {
   int32_t kd;        // row pitch of the operand (padded window pixels)
   int32_t ldf;       // row pitch of the DFT workspace
   int32_t t0;        // first 64-pixel tile of this job: prefix of ceil(W^2 / 64) over the jobs
+  int32_t atom, pad;
 };
 
 struct ProbeArgs {
@@ -141,26 +142,6 @@ struct FocalAtom {
   int32_t M, W;     // enlarged window side (power of two) and the atom's window side
   int32_t oy, ox;   // enlarged window origin (pixels, mod N)
   int32_t plane, atom;
-};
-
-struct FocalProbeJob {
-  int64_t psi_off;  // the atom's psi at the centroid [Ppad][kd_c] (FP32 planes)
-  int64_t out_off;  // the atom's operand block (plane elements)
-  int64_t h_off;    // first H element of the atom
-  int32_t M, W, kd, kd_c, atom, pad;
-};
-
-struct FocalProbeArgs {
-  const FocalProbeJob* jobs;
-  const float* psi_c;
-  int64_t psi_plane;
-  void* out;
-  int64_t out_plane;
-  const float2* H;
-  int n_ch, P, Ppad, L;
-  const float2* tw;       // exp(-2 pi i m / L)
-  double dy, dx, lambda;  // pixel sizes (A) and wavelength (A)
-  const double* dist;     // back-step distance of each atom (A)
 };
 
 }  // namespace bip
@@ -214,7 +195,8 @@ struct bip_plan {
   int focal_max_m = 0;
   bip::FocalAtom* d_fatoms = nullptr;
   double* d_fdist = nullptr;       // back-step distance per atom (A), set by each build
-  std::vector<bip::FocalProbeJob> h_fjobs;
+  float2* d_fker = nullptr;        // forward-step kernels [atom][axis], set by each build
+  std::vector<bip::ProbeJob> h_fjobs;
   int64_t *d_off1 = nullptr, *d_off2 = nullptr;
   bip::GatherRec *d_grec1 = nullptr, *d_grec2 = nullptr;  // gather records in plane order
   float2* d_state1 = nullptr;   // [Bp1][G]
@@ -399,8 +381,14 @@ hipError_t launch_focal_dist(const float* V, const FocalAtom* atoms, int n_atoms
 hipError_t launch_focal_parents(float2* win, const FocalAtom* atoms, int n_atoms, const double* dist,
                                 const int2* parents, int n_par, int max_m, int ny, int nx, double dy,
                                 double dx, double lambda, const float2* tw, int L, hipStream_t s);
-hipError_t launch_focal_probe(const FocalProbeArgs& fp, int prec, bool u, int n_jobs, int max_m,
-                              hipStream_t s);
+// periodic kernels of the forward step, focal_kernel_elems() complex values per atom
+int focal_kernel_elems();
+hipError_t launch_focal_kernel(const FocalAtom* atoms, int n_atoms, const double* dist, double dy, double dx,
+                               double lambda, float2* ker, hipStream_t s);
+// forward step and crop of `rows` rows of each job's DFT workspace block: windows of jobs_m (M x M,
+// pitch ldf) to those of jobs_w (W x W, same pitch), in place
+hipError_t launch_focal_step(const ProbeJob* jobs_m, const ProbeJob* jobs_w, const float2* ker, float2* fx, int rows,
+                             int n_jobs, int max_m, hipStream_t s);
 
 // slice potentials (k_potential.hip).  Terms are (x, y, A, w) quadruples
 // grouped by slice: slice z holds terms start[z] .. start[z + 1] (device i64).

@@ -8,7 +8,11 @@
 // The Fresnel step of a window takes it as periodic: the window's 2-D DFT is
 // multiplied by exp(s i pi lambda dist |q|^2) with q the frequencies of the
 // window grid (k / (M delta) per axis, signed k), s = +1 back, -1 forward.
-// It runs in LDS: the window is placed at bit-reversed positions, transformed
+//
+// The forward step is linear in the probe, so it commutes with the sum over
+// beams: k_focal_step applies it, with the crop, between the two raster DFTs
+// of the probe synthesis, and the second one then runs on the W x W window.
+// The back-step of the parents runs in LDS: the window is placed at bit-reversed positions, transformed
 // by a radix-2 decimation-in-time pass (natural-order spectrum), multiplied,
 // and inverted by a decimation-in-frequency pass, whose bit-reversed output
 // is read back at bit-reversed positions.  M is a power of two from 8 to 128.
@@ -115,49 +119,115 @@ __global__ __launch_bounds__(NT) void k_focal_parents(float2* win, const FocalAt
   }
 }
 
-// Forward step of the probe of every scan position (grid: P x atoms of the
-// chunk): psi_c [rho][r] (FP32 planes, pitch kd_c) on the enlarged window,
-// stepped forward, cropped to the atom's W x W window and stored as the
-// contraction operand (psi^T, or U_n = H_n psi), rows P .. Ppad-1 zero.
-template <int PREC, bool U>
-__global__ __launch_bounds__(NT) void k_focal_probe(FocalProbeArgs fp) {
+// Periodic kernel of the forward step along one axis, per atom (grid: atoms x
+// axes, M threads): c[d] = 1/M sum_k exp(2 pi i k d / M) exp(-i pi lambda dist
+// q_k^2), in FP64, rounded once; ker[atom][axis][FOCAL_M].
+constexpr int FOCAL_M = 128;
+__global__ void k_focal_kernel(const FocalAtom* __restrict__ atoms, const double* __restrict__ dist, double dy,
+                               double dx, double lambda, float2* __restrict__ ker) {
+  const FocalAtom fa = atoms[blockIdx.x];
+  const int M = fa.M, d = threadIdx.x;
+  if (d >= M) return;
+  const double delta = blockIdx.y == 0 ? dy : dx;
+  const double pi = 3.14159265358979323846;
+  double re = 0.0, im = 0.0;
+  for (int k = 0; k < M; ++k) {
+    const int ks = k < M / 2 ? k : k - M;
+    const double q = ks / (M * delta);
+    double ph = -pi * lambda * dist[fa.atom] * q * q;
+    ph += 2.0 * pi * ((k * d) & (M - 1)) / M;
+    double s, c;
+    sincos(ph, &s, &c);
+    re += c;
+    im += s;
+  }
+  ker[((int64_t)fa.atom * 2 + blockIdx.y) * FOCAL_M + d] = make_float2((float)(re / M), (float)(im / M));
+}
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+// Complex 16 x 16 block product step on the FP32 matrix cores, K = 4: lane l
+// holds row l mod 16 and K index l / 16 of a, column l mod 16 and K index
+// l / 16 of b.
+__device__ inline void cmfma(float2 a, float2 b, v4f& re, v4f& im) {
+  re = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b.x, re, 0, 0, 0);
+  im = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b.y, im, 0, 0, 0);
+  re = __builtin_amdgcn_mfma_f32_16x16x4f32(-a.y, b.y, re, 0, 0, 0);
+  im = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, b.x, im, 0, 0, 0);
+}
+
+// Forward step and crop of one row of the DFT workspace (grid: rows x atoms of
+// the chunk): the M x M window X becomes Z = A_y X A_x^T, A[w][m] =
+// c[(w + pad - m) mod M] (W x M), stored at the head of the row.  Two FP32
+// matrix products: the step costs 8 W M (M + W) flop a row and one read of X,
+// against 40 M^2 log2 M for the two transforms and their FP64 phases, which
+// took 18.2 ms of the 34.8 ms of a 24-atom, 64 x 64-raster map (W = 32); this
+// kernel takes 1.42 ms there (4.0 GB moved, 2.8 TB/s; 109 TFLOP/s of FP32
+// products), and the second DFT, on W^2 instead of M^2 pixels, 0.65 instead of
+// 2.36 ms.  A wave owns 16 columns
+// of X at a time and all W rows of Y = A_y X, so X is read once, from memory
+// straight into the operand registers.  NR: row blocks of 16 that the widest
+// window of the launch needs.
+template <int NR>
+__global__ __launch_bounds__(NT, 4) void k_focal_step(const ProbeJob* __restrict__ jobs_m,
+                                                   const ProbeJob* __restrict__ jobs_w,
+                                                   const float2* __restrict__ ker, float2* __restrict__ fx) {
   extern __shared__ float2 sm[];
-  const FocalProbeJob job = fp.jobs[blockIdx.y];
-  const int M = job.M, logm = ilog2(M), W = job.W, W2 = W * W, pad = (M - W) / 2;
-  const int rho = blockIdx.x;
-  float2* a = sm;
-  float2* tw = sm + M * M;
-  auto put = [&](int row, int r, float re, float im) {
-    if constexpr (U) {
-      for (int n = 0; n < fp.n_ch; ++n) {
-        const float2 hn = r < W2 ? fp.H[job.h_off + (int64_t)n * W2 + r] : make_float2(0.f, 0.f);
-        store_planes<PREC>(fp.out, job.out_off + ((int64_t)n * fp.Ppad + row) * job.kd + r, fp.out_plane,
-                           hn.x * re - hn.y * im, hn.x * im + hn.y * re);
-      }
-    } else {
-      store_planes<PREC>(fp.out, job.out_off + (int64_t)row * job.kd + r, fp.out_plane, re, im);
-    }
-  };
-  if (rho >= fp.P) {  // padding rows
-    for (int r = threadIdx.x; r < job.kd; r += NT) put(rho, r, 0.f, 0.f);
-    return;
-  }
-  for (int k = threadIdx.x; k < M; k += NT) tw[k] = fp.tw[(int64_t)k * (fp.L / M)];
-  const float* re = fp.psi_c + job.psi_off + (int64_t)rho * job.kd_c;
-  const float* im = re + fp.psi_plane;
-  for (int e = threadIdx.x; e < M * M; e += NT) {
-    const int ry = e / M, rx = e - ry * M;
-    a[bitrev(ry, logm) * M + bitrev(rx, logm)] = make_float2(re[e], im[e]);
-  }
+  const ProbeJob jm = jobs_m[blockIdx.y];
+  const int M = jm.W, W = jobs_w[blockIdx.y].W, pad = (M - W) / 2;
+  const int ly = M + 1;                // LDS pitch of Y
+  float2* cy = sm;                     // [M]
+  float2* cx = sm + M;                 // [M]
+  float2* Y = sm + 2 * M;              // [16 NR][ly]
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int li = lane & 15, lk = lane >> 4;
+  float2* row = fx + jm.fx_off + (int64_t)blockIdx.x * jm.ldf;
+  for (int i = threadIdx.x; i < 2 * M; i += NT)
+    sm[i] = ker[((int64_t)jm.atom * 2 + (i >= M)) * FOCAL_M + (i & (M - 1))];
   __syncthreads();
-  window_fresnel(a, M, logm, tw, fp.dy, fp.dx, fp.lambda, fp.dist[job.atom], -1);
-  for (int r = threadIdx.x; r < job.kd; r += NT) {
-    float2 v = make_float2(0.f, 0.f);
-    if (r < W2) {
-      const int ry = r / W + pad, rx = r % W + pad;
-      v = a[bitrev(ry, logm) * M + bitrev(rx, logm)];
+  constexpr int KB = 8;  // K steps (of 4 rows) loaded at a time, zero beyond M
+  for (int cb = wave; cb * 16 < M; cb += NT / 64) {
+    const int x = cb * 16 + li;
+    v4f re[NR], im[NR];
+#pragma unroll
+    for (int rb = 0; rb < NR; ++rb) re[rb] = im[rb] = v4f{0.f, 0.f, 0.f, 0.f};
+    for (int k0 = 0; k0 < M; k0 += 4 * KB) {
+      float2 b[KB];
+#pragma unroll
+      for (int k = 0; k < KB; ++k) {
+        const int y = k0 + 4 * k + lk;
+        b[k] = (y < M && x < M) ? row[y * M + x] : make_float2(0.f, 0.f);
+      }
+#pragma unroll
+      for (int k = 0; k < KB; ++k) {
+        const int y = k0 + 4 * k + lk;
+#pragma unroll
+        for (int rb = 0; rb < NR; ++rb)
+          cmfma(cy[(16 * rb + li + pad - y) & (M - 1)], b[k], re[rb], im[rb]);
+      }
     }
-    put(rho, r, v.x, v.y);
+    if (x < M) {
+#pragma unroll
+      for (int rb = 0; rb < NR; ++rb)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) Y[(16 * rb + 4 * lk + q) * ly + x] = make_float2(re[rb][q], im[rb][q]);
+    }
+  }
+  __syncthreads();  // Y complete; X read
+  for (int blk = wave; blk < NR * NR; blk += NT / 64) {
+    const int rb = blk / NR, vb = blk - rb * NR;
+    if (16 * rb >= W || 16 * vb >= W) continue;  // wave-uniform
+    v4f re = v4f{0.f, 0.f, 0.f, 0.f}, im = re;
+    for (int x = lk; x < M; x += 4)
+      cmfma(Y[(16 * rb + li) * ly + x], cx[(16 * vb + li + pad - x) & (M - 1)], re, im);
+    const int v = 16 * vb + li;
+    if (v < W) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int w = 16 * rb + 4 * lk + q;
+        if (w < W) row[w * W + v] = make_float2(re[q], im[q]);
+      }
+    }
   }
 }
 
@@ -217,28 +287,35 @@ hipError_t launch_focal_parents(float2* win, const FocalAtom* atoms, int n_atoms
   return hipGetLastError();
 }
 
-hipError_t launch_focal_probe(const FocalProbeArgs& fp, int prec, bool u, int n_jobs, int max_m,
-                              hipStream_t s) {
-  if (n_jobs <= 0) return hipSuccess;
-  const size_t lds = (size_t)(max_m * max_m + max_m) * sizeof(float2);
-  const dim3 grid((unsigned)fp.Ppad, (unsigned)n_jobs);
-#define FP(P)                                                                                      \
-  if (prec == P) {                                                                                 \
-    const void* f = u ? (const void*)k_focal_probe<P, true> : (const void*)k_focal_probe<P, false>; \
-    hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);   \
-    if (e != hipSuccess) return e;                                                                 \
-    if (u)                                                                                         \
-      hipLaunchKernelGGL((k_focal_probe<P, true>), grid, dim3(NT), lds, s, fp);                    \
-    else                                                                                           \
-      hipLaunchKernelGGL((k_focal_probe<P, false>), grid, dim3(NT), lds, s, fp);                   \
-    return hipGetLastError();                                                                      \
+hipError_t launch_focal_kernel(const FocalAtom* atoms, int n_atoms, const double* dist, double dy, double dx,
+                               double lambda, float2* ker, hipStream_t s) {
+  if (n_atoms <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_focal_kernel, dim3(n_atoms, 2), dim3(FOCAL_M), 0, s, atoms, dist, dy, dx, lambda, ker);
+  return hipGetLastError();
+}
+
+hipError_t launch_focal_step(const ProbeJob* jobs_m, const ProbeJob* jobs_w, const float2* ker, float2* fx, int rows,
+                             int n_jobs, int max_m, hipStream_t s) {
+  if (n_jobs <= 0 || rows <= 0) return hipSuccess;
+  if (max_m > FOCAL_M || n_jobs > 65535) return hipErrorInvalidValue;
+  const int nr = std::max(1, max_m / 32);  // W <= M / 2
+  const size_t lds = (size_t)(2 * max_m + 16 * nr * (max_m + 1)) * sizeof(float2);
+  const dim3 grid((unsigned)rows, (unsigned)n_jobs);
+#define FS(N)                                                                                              \
+  if (nr == N) {                                                                                           \
+    hipError_t e =                                                                                         \
+        hipFuncSetAttribute((const void*)k_focal_step<N>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
+    if (e != hipSuccess) return e;                                                                         \
+    hipLaunchKernelGGL(k_focal_step<N>, grid, dim3(NT), lds, s, jobs_m, jobs_w, ker, fx);                  \
+    return hipGetLastError();                                                                              \
   }
-  FP(BIP_PREC_FP32)
-  FP(BIP_PREC_SPLIT_BF16)
-  FP(BIP_PREC_BF16)
-  FP(BIP_PREC_FP16)
-#undef FP
+  FS(1)
+  FS(2)
+  FS(4)
+#undef FS
   return hipErrorInvalidValue;
 }
+
+int focal_kernel_elems() { return 2 * FOCAL_M; }
 
 }  // namespace bip

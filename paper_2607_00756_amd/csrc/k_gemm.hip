@@ -938,6 +938,7 @@ __global__ void k_reduce_map(const float* __restrict__ partial, int ntiles, int 
   const int rho = blockIdx.x * blockDim.x + threadIdx.x;
   if (rho >= P) return;
   float s = 0.f;
+#pragma unroll 16  // loads in flight; the sum stays in order
   for (int t = 0; t < ntiles; ++t) s += partial[(int64_t)t * Ppad + rho];
   out[rho] = accumulate ? out[rho] + s : s;
 }
