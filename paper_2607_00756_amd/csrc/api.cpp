@@ -1277,7 +1277,7 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
       ra.win = p->d_win2;
       ra.scale = gram_scale;
       HIPCHK(timed(p, ST_RECON, st, [&] {
-               return launch_recon_kblk_atoms(ra, d_ratoms + c0, nat, S2op, gram_prec, Dk, pl1, st);
+               return launch_recon_kblk_atoms(ra, d_ratoms + c0, nat, S2op, gram_prec, Dk, pl1, max_n1, st);
              }),
              "recon S2 operand");
     }

@@ -338,9 +338,10 @@ struct ReconArgs {
 hipError_t launch_recon_plain(const ReconArgs& a, float2* out, hipStream_t s);
 // K-blocked operands (kind 0) of n_atoms atoms in one launch; a.win is the
 // window stack, the per-atom fields of a are taken from atoms (device).
-// Needs a.tile_np <= 64 (square-lattice parents).
+// Needs a.tile_np <= 64 (square-lattice parents).  max_nr: the most operand rows of an atom.
 hipError_t launch_recon_kblk_atoms(const ReconArgs& a, const ReconAtom* atoms, int n_atoms, void* out,
-                                   int prec, int64_t ncols_pad, int64_t plane_stride, hipStream_t s);
+                                   int prec, int64_t ncols_pad, int64_t plane_stride, int max_nr,
+                                   hipStream_t s);
 // GEMM operand outputs; layout kind 0: [r][b] (b fastest, ld = ldk, rows up to nrows)
 // kind 1: [b][r] (r fastest).  prec: BIP_PREC_*; planes at stride plane_stride elements.
 hipError_t launch_recon_operand(const ReconArgs& a, void* out, int kind, int prec, int64_t ld,

@@ -382,41 +382,51 @@ __global__ __launch_bounds__(256) void k_recon_kblk(ReconArgs a, void* out, int 
   recon_kblk_tile<PREC>(a, out, nrows, ncols, plane, bt, ch * rpw, min(nrt, ch * rpw + rpw));
 }
 
-// Every atom of a chunk in one launch: a workgroup per (atom, beam tile) over
-// all the atom's pixel tiles; an XCD takes a contiguous range of them, so the
-// beam tiles of one atom, which share parents, meet in its L2.
+// Every atom of a chunk in one launch: a workgroup per (atom, run of rpw pixel
+// tiles, beam tile); an XCD takes a contiguous range of them, so the beam
+// tiles of one atom, which share parents, meet in its L2.
 template <int PREC>
 __global__ __launch_bounds__(256) void k_recon_kblk_atoms(ReconArgs a, const ReconAtom* __restrict__ atoms,
                                                           int n_atoms, char* out, int ncols,
-                                                          int64_t plane) {
+                                                          int64_t plane, int nch, int rpw) {
   const int nbt = (ncols + TB - 1) / TB;
   const int per = (int)(gridDim.x / 8);
   const int lin = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
-  if (lin >= nbt * n_atoms) return;
-  const int bt = lin % nbt;
-  const ReconAtom at = atoms[lin / nbt];
+  if (lin >= nbt * nch * n_atoms) return;
+  const int bt = lin % nbt, run = lin / nbt, ch = run % nch;
+  const ReconAtom at = atoms[run / nch];
+  const int nrt = (at.n_r + TR - 1) / TR;
+  if (ch * rpw >= nrt) return;  // a smaller window than the launch's largest: uniform per workgroup
   a.win += at.win_off;
   a.W = at.W;
   a.oy = at.oy;
   a.ox = at.ox;
   constexpr int ES = PREC == BIP_PREC_FP32 ? 4 : 2;
-  recon_kblk_tile<PREC>(a, out + at.out_off * ES, at.n_r, ncols, plane, bt, 0, (at.n_r + TR - 1) / TR);
+  recon_kblk_tile<PREC>(a, out + at.out_off * ES, at.n_r, ncols, plane, bt, ch * rpw, min(nrt, ch * rpw + rpw));
 }
 
 }  // namespace
 
 hipError_t launch_recon_kblk_atoms(const ReconArgs& a, const ReconAtom* atoms, int n_atoms, void* out,
-                                   int prec, int64_t ncols_pad, int64_t plane_stride, hipStream_t s) {
+                                   int prec, int64_t ncols_pad, int64_t plane_stride, int max_nr,
+                                   hipStream_t s) {
   if (n_atoms <= 0 || ncols_pad <= 0) return hipSuccess;
   if (a.tile_np > TILE_NP || ncols_pad > INT32_MAX) return hipErrorInvalidValue;
-  const int64_t nt = ((ncols_pad + TB - 1) / TB) * n_atoms;
+  // A run stages its tile's weights once and prefetches slab by slab, so runs
+  // are as long as they can be while the launch has about 2048 workgroups (8 a
+  // CU): one 32 x 32 window against 2053 beams took 115 us in 33 workgroups
+  // of 32 slabs, and 20 us in 33 x 32.
+  const int64_t nbt = (ncols_pad + TB - 1) / TB, nrt = (max_nr + TR - 1) / TR;
+  const int64_t want = std::max<int64_t>(1, std::min<int64_t>(nrt, (2048 + nbt * n_atoms - 1) / (nbt * n_atoms)));
+  const int64_t rpw = (nrt + want - 1) / want, nch = (nrt + rpw - 1) / rpw;
+  const int64_t nt = nbt * nch * n_atoms;
   const int64_t nblk = (nt + 7) / 8 * 8;
   if (nblk > INT32_MAX) return hipErrorInvalidValue;
 #define RA(P)                                                                                    \
   if (prec == P) {                                                                               \
     hipLaunchKernelGGL((k_recon_kblk_atoms<P>), dim3((unsigned)nblk), dim3(256),                 \
                        a.L * sizeof(float2), s, a, atoms, n_atoms, (char*)out, (int)ncols_pad,   \
-                       plane_stride);                                                            \
+                       plane_stride, (int)nch, (int)rpw);                                                            \
     return hipGetLastError();                                                                    \
   }
   RA(BIP_PREC_FP32)
