@@ -149,11 +149,20 @@ __device__ inline void exchange_sync() {
   }
 }
 
+// Twiddles of the second (radix-16) stage, laid out as it reads them:
+// w[(j - 1) 16 + k] = exp(-2 pi i j k / 256), k = 0 .. 15.  Lanes read
+// consecutive k; in the exp(-2 pi i m / L) table they are j (L = 256), 2 j
+// (512) or 4 j (1024) entries apart, up to 8 lanes a bank.
+constexpr int TW16 = 15 * 16;
+__device__ inline void fill_tw16(float2* w, const float2* __restrict__ twg, int L, int tid, int nthreads) {
+  for (int i = tid; i < TW16; i += nthreads) w[i] = twg[(i / 16 + 1) * (i % 16) * (L / 256)];
+}
+
 // One Stockham stage.  v: strided-layout registers.  tw: exp(-2 pi i m/L)
-// table; twstep = L / N.
-template <int N, int R, int P, bool LAST, bool INV, int STRIDE, bool PAD, bool WAVE = false>
+// table, twstep = L / N; TAB: the second (16 x 16) stage reads tw16 instead.
+template <int N, int R, int P, bool LAST, bool INV, int STRIDE, bool PAD, bool WAVE, bool TAB>
 __device__ inline void stage(float2 (&v)[16], float2* lds, int t, const float2* __restrict__ tw,
-                             int twstep) {
+                             int twstep, const float2* __restrict__ tw16) {
   constexpr int T = N / 16;
   constexpr int NB = 16 / R;
 #pragma unroll
@@ -166,7 +175,7 @@ __device__ inline void stage(float2 (&v)[16], float2* lds, int t, const float2* 
     if (P > 1) {
 #pragma unroll
       for (int j = 1; j < R; ++j) {
-        const float2 w = tw[(j * k * (N / (P * R))) * twstep];
+        const float2 w = TAB && P == 16 && R == 16 ? tw16[(j - 1) * 16 + k] : tw[(j * k * (N / (P * R))) * twstep];
         u[j] = INV ? cmulc(u[j], w) : cmul(u[j], w);
       }
     }
@@ -189,29 +198,31 @@ __device__ inline void stage(float2 (&v)[16], float2* lds, int t, const float2* 
 }
 
 // Full transform (unnormalized; inverse uses exp(+2 pi i ...)).  WAVE: see
-// exchange_sync (STRIDE 1 with N/16 consecutive lanes per transform).
-template <int N, bool INV, int STRIDE, bool PAD, bool WAVE = false>
-__device__ inline void transform(float2 (&v)[16], float2* lds, int t, const float2* tw, int L) {
+// exchange_sync (STRIDE 1 with N/16 consecutive lanes per transform).  TAB: see
+// stage.
+template <int N, bool INV, int STRIDE, bool PAD, bool WAVE = false, bool TAB = false>
+__device__ inline void transform(float2 (&v)[16], float2* lds, int t, const float2* tw, int L,
+                                 const float2* tw16 = nullptr) {
   static_assert(!WAVE || (STRIDE == 1 && N / 16 <= 64), "a wave-synchronized transform must fit one wave");
   const int twstep = L / N;
   if constexpr (N == 64) {
-    stage<64, 16, 1, false, INV, STRIDE, PAD, WAVE>(v, lds, t, tw, twstep);
-    stage<64, 4, 16, true, INV, STRIDE, PAD, WAVE>(v, lds, t, tw, twstep);
+    stage<64, 16, 1, false, INV, STRIDE, PAD, WAVE, TAB>(v, lds, t, tw, twstep, tw16);
+    stage<64, 4, 16, true, INV, STRIDE, PAD, WAVE, TAB>(v, lds, t, tw, twstep, tw16);
   } else if constexpr (N == 128) {
-    stage<128, 16, 1, false, INV, STRIDE, PAD, WAVE>(v, lds, t, tw, twstep);
-    stage<128, 8, 16, true, INV, STRIDE, PAD, WAVE>(v, lds, t, tw, twstep);
+    stage<128, 16, 1, false, INV, STRIDE, PAD, WAVE, TAB>(v, lds, t, tw, twstep, tw16);
+    stage<128, 8, 16, true, INV, STRIDE, PAD, WAVE, TAB>(v, lds, t, tw, twstep, tw16);
   } else if constexpr (N == 256) {
-    stage<256, 16, 1, false, INV, STRIDE, PAD, WAVE>(v, lds, t, tw, twstep);
-    stage<256, 16, 16, true, INV, STRIDE, PAD, WAVE>(v, lds, t, tw, twstep);
+    stage<256, 16, 1, false, INV, STRIDE, PAD, WAVE, TAB>(v, lds, t, tw, twstep, tw16);
+    stage<256, 16, 16, true, INV, STRIDE, PAD, WAVE, TAB>(v, lds, t, tw, twstep, tw16);
   } else if constexpr (N == 512) {
-    stage<512, 16, 1, false, INV, STRIDE, PAD, WAVE>(v, lds, t, tw, twstep);
-    stage<512, 16, 16, false, INV, STRIDE, PAD, WAVE>(v, lds, t, tw, twstep);
-    stage<512, 2, 256, true, INV, STRIDE, PAD, WAVE>(v, lds, t, tw, twstep);
+    stage<512, 16, 1, false, INV, STRIDE, PAD, WAVE, TAB>(v, lds, t, tw, twstep, tw16);
+    stage<512, 16, 16, false, INV, STRIDE, PAD, WAVE, TAB>(v, lds, t, tw, twstep, tw16);
+    stage<512, 2, 256, true, INV, STRIDE, PAD, WAVE, TAB>(v, lds, t, tw, twstep, tw16);
   } else {
     static_assert(N == 1024, "unsupported FFT length");
-    stage<1024, 16, 1, false, INV, STRIDE, PAD, WAVE>(v, lds, t, tw, twstep);
-    stage<1024, 16, 16, false, INV, STRIDE, PAD, WAVE>(v, lds, t, tw, twstep);
-    stage<1024, 4, 256, true, INV, STRIDE, PAD, WAVE>(v, lds, t, tw, twstep);
+    stage<1024, 16, 1, false, INV, STRIDE, PAD, WAVE, TAB>(v, lds, t, tw, twstep, tw16);
+    stage<1024, 16, 16, false, INV, STRIDE, PAD, WAVE, TAB>(v, lds, t, tw, twstep, tw16);
+    stage<1024, 4, 256, true, INV, STRIDE, PAD, WAVE, TAB>(v, lds, t, tw, twstep, tw16);
   }
 }
 
