@@ -8,6 +8,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <numeric>
 #include <string>
 #include <vector>
 
@@ -948,6 +949,18 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
   // not average.
   const int gram_prec = gram_precision(precision, p->ndet);
   const float gram_scale = gram_prec == BIP_PREC_FP16 ? 256.f : 1.f;
+  // the scans of each atom's crop mask (all of them at f = 1): raster rows and columns
+  struct Crop {
+    int32_t u0, nu, v0, nv;
+  };
+  std::vector<Crop> crop(p->n_atoms, Crop{0, scan_sy, 0, scan_sx});
+  if (p->f > 1)
+    for (int a : atoms) {
+      crop_run(p->tau_y[a], p->g.ny, scan_sy, p->f, crop[a].u0, crop[a].nu);
+      crop_run(p->tau_x[a], p->g.nx, scan_sx, p->f, crop[a].v0, crop[a].nv);
+    }
+  // rows of an atom's psi^T operand: the scans of its mask, to whole tiles
+  auto prow_of = [&](int a) { return p->f > 1 ? roundup((int64_t)crop[a].nu * crop[a].nv, 128) : Ppad; };
   auto kd_of = [](int W) { return roundup((int64_t)W * W, 32); };   // padded window pixels
   auto n1_of = [](int W) { return roundup((int64_t)W * W, 128); };  // ... to whole tiles
   auto ldf_of = [](int W) { return roundup((int64_t)W * W, 64); };  // DFT workspace pitch
@@ -958,7 +971,7 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
     s[0] = (int64_t)P * ldf_of(W1);                                // X [S_y][S_x][r] (S1 window)
     s[1] = gram ? n1_of(W) * Dk : Dpad * kd_of(W);                 // S2~^T [r][d] | S2~ [d][r]
     s[2] = gram ? n1_of(W) * kd_of(W) : (int64_t)n_ch * Ppad * kd_of(W);  // Q [r][r'] | U_n [rho][r]
-    s[3] = gram ? Ppad * kd_of(W) : 0;                             // psi^T [rho][r]
+    s[3] = gram ? prow_of(a) * kd_of(W) : 0;                       // psi^T [rho][r]
   };
   auto atom_bytes = [&](int a) {
     int64_t s[4];
@@ -1114,9 +1127,7 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
     const int a = atoms[i];
     const int W = p->W[a];
     const int32_t W2 = W * W, kd = (int32_t)kd_of(W);
-    int32_t cu0, cnu, cv0, cnv;
-    crop_run(p->tau_y[a], p->g.ny, scan_sy, p->f, cu0, cnu);
-    crop_run(p->tau_x[a], p->g.nx, scan_sx, p->f, cv0, cnv);
+    const int32_t cu0 = crop[a].u0, cnu = crop[a].nu, cv0 = crop[a].v0, cnv = crop[a].nv;
     ProbeJob pj{};
     pj.win_off = p->off1[a];
     pj.fx_off = off[0][i];
@@ -1128,6 +1139,10 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
     pj.kd = kd;
     pj.ldf = (int32_t)ldf_of(W);
     pj.atom = a;
+    pj.cu0 = cu0;
+    pj.cnu = cnu;
+    pj.cv0 = cv0;
+    pj.cnv = cnv;
     if (p->focal) {  // folded on the enlarged window; after the forward step the window's own job follows
       const int W1 = p->W1[a];
       pj.ldf = (int32_t)ldf_of(W1);
@@ -1158,7 +1173,7 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
       u.a_off = off[3][i];
       u.b_off = off[2][i];
       u.K = u.lda = u.ldb = kd;
-      u.m_lim = (int32_t)Ppad;
+      u.m_lim = (int32_t)prow_of(a);
       u.n_lim = W2;
       u.W2 = W2;
       u.cu0 = cu0;
@@ -1230,6 +1245,8 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
   pa.Sx = scan_sx;
   pa.P = P;
   pa.Ppad = (int)Ppad;
+  pa.gy = std::gcd(p->f, scan_sy);
+  pa.gx = std::gcd(p->f, scan_sx);
   // probe coefficients of the whole aperture; retained beams scaled by f^2
   pa.cb = (float)((double)p->f * p->f / std::sqrt((double)p->g.ny * p->g.nx * p->B_full));
   pa.H = (const float2*)H;
@@ -1244,7 +1261,8 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
     char* PsiT = (char*)ws.take(std::max<int64_t>(pl3, 1) * csz);
     void* split_buf = split_bytes > 0 ? ws.take(split_bytes) : nullptr;
     if (ws.used > work_cap) return err(BIP_ENOMEM, "internal: chunk exceeds the workspace");
-    int max_n1 = 0, max_kd = 0, max_m = 0;
+    int max_n1 = 0, max_kd = 0, max_m = 0, max_cnu = 0, max_cnv = 0;
+    int64_t max_prow = 0;
     const int c0 = chunks[c].first, c1 = chunks[c].second, nat = c1 - c0;
     for (int i = c0; i < c1; ++i) {
       const int a = atoms[i];
@@ -1254,6 +1272,9 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
       max_n1 = std::max<int>(max_n1, (int)n1_of(W));
       max_kd = std::max<int>(max_kd, (int)kd_of(W));
       max_m = std::max(max_m, W1);
+      max_cnu = std::max(max_cnu, crop[a].nu);
+      max_cnv = std::max(max_cnv, crop[a].nv);
+      max_prow = std::max(max_prow, prow_of(a));
       if (off[0][i] + s[0] > pl0 || off[1][i] + s[1] > pl1 || off[2][i] + s[2] > pl2 ||
           off[3][i] + s[3] > pl3)
         return err(BIP_EINVAL, "internal: operand block outside its buffer");
@@ -1288,16 +1309,17 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
     pa.out_plane = gram ? pl3 : pl2;
     const int unit0 = jprobe[c0].t0;
     const int n_units = jprobe[c1 - 1].t0 + (jprobe[c1 - 1].W * jprobe[c1 - 1].W + 63) / 64 - unit0;
-    HIPCHK(timed(p, ST_FOLD, st, [&] { return launch_probe_fold_x(pa, unit0, n_units, nat, st); }),
+    HIPCHK(timed(p, ST_FOLD, st, [&] { return launch_probe_fold_x(pa, unit0, n_units, nat, max_cnv, st); }),
            "probe fold");
     if (p->focal) {  // step forward to the ionization plane, crop to the window
       HIPCHK(timed(p, ST_PROBE, st, [&] {
-               return launch_focal_step(d_probe + c0, d_fjobs + c0, p->d_fker, X, P, nat, max_m, st);
+               return launch_focal_step(d_probe + c0, d_fjobs + c0, p->d_fker, X, scan_sy / pa.gy * scan_sx, scan_sx, nat,
+                                        max_m, st);
              }),
              "focal probe step");
       pa.jobs = d_fjobs + c0;
     }
-    HIPCHK(timed(p, ST_PROBE, st, [&] { return launch_probe_y(pa, precision, !gram, max_kd, nat, st); }),
+    HIPCHK(timed(p, ST_PROBE, st, [&] { return launch_probe_y(pa, precision, !gram, max_kd, max_cnu, max_cnv, nat, st); }),
            "probe synthesis");
     GemmArgs g{};
     g.H = (const float2*)H;
@@ -1338,6 +1360,27 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
       u.njobs = nat;
       u.partial = partial;
       u.qtri = 1;
+      if (p->f > 1) {
+        // each atom over the scans of its own mask, one partial row block per atom, as many atoms
+        // at a time as the partial rows hold (at least GEMM_MAX_ZSPLIT)
+        const int nt = max_n1 / quad_n, mt = (int)(max_prow / quad_m);
+        u.crop = 0;
+        u.Mpad = (int)max_prow;
+        u.ksplit = 1;
+        const int64_t most = max_prow > 0 ? n_partial_tiles * Ppad / (nt * max_prow) : 0;
+        const int group = (int)std::min<int64_t>({most, nat, 32768});
+        for (int j = 0; group > 0 && j < nat; j += group) {
+          u.jobs = d_jquad + c0 + j;
+          u.njobs = u.zsplit = std::min(group, nat - j);
+          HIPCHK(timed(p, ST_DET, st, [&] { return launch_zgemm(precision, EPI_QUAD, u, mt, nt, u.zsplit, st); }),
+                 "quadratic form");
+          HIPCHK(timed(p, ST_REDUCE, st, [&] {
+                   return launch_reduce_crop(partial, u.jobs, u.njobs, nt, (int)max_prow, scan_sy, scan_sx, out, st);
+                 }),
+                 "reduce");
+        }
+        continue;
+      }
       // job groups and K segments that fill the chip evenly; partial rows reduced in a fixed order
       const int mt = (int)(Ppad / quad_m), nt = max_n1 / quad_n;
       int zj = 1;

@@ -125,6 +125,8 @@ int bip_eels_backward(bip_plan* p, int32_t n_ch, const float* H, const int64_t* 
     j.ox = p->ox[a];
     j.kd = (int32_t)roundup((int64_t)p->W[a] * p->W[a], 32);
     j.ldf = (int32_t)roundup((int64_t)p->W[a] * p->W[a], 64);
+    j.cnu = scan_sy;
+    j.cnv = scan_sx;
     j.t0 = a == 0 ? 0 : jprobe[a - 1].t0 + (jprobe[a - 1].W * jprobe[a - 1].W + 63) / 64;
   }
   // transposed weights (parent -> beams), built once per plan
@@ -255,6 +257,7 @@ int bip_eels_backward(bip_plan* p, int32_t n_ch, const float* H, const int64_t* 
   pa.Sx = scan_sx;
   pa.P = P;
   pa.Ppad = (int)Ppad;
+  pa.gy = pa.gx = 1;
   pa.cb = cb;
   pa.fx = X;
   pa.out = psiT;
@@ -321,9 +324,9 @@ int bip_eels_backward(bip_plan* p, int32_t n_ch, const float* H, const int64_t* 
     // psi^T [rho][r] (FP32) of every atom of the chunk, exactly as the forward synthesis
     pa.jobs = d_probe + c0;
     const ProbeJob& jl = jprobe[c0 + nat - 1];
-    HIPCHK(launch_probe_fold_x(pa, jprobe[c0].t0, jl.t0 + (jl.W * jl.W + 63) / 64 - jprobe[c0].t0, nat, st),
+    HIPCHK(launch_probe_fold_x(pa, jprobe[c0].t0, jl.t0 + (jl.W * jl.W + 63) / 64 - jprobe[c0].t0, nat, scan_sx, st),
            "probe fold");
-    HIPCHK(launch_probe_y(pa, prec, false, max_kd, nat, st), "probe synthesis");
+    HIPCHK(launch_probe_y(pa, prec, false, max_kd, scan_sy, scan_sx, nat, st), "probe synthesis");
     for (int a = c0; a < c0 + nat; ++a) {
       const int64_t i = a - c0;
       const int W2 = p->W[a] * p->W[a];

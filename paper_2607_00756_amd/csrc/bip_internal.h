@@ -106,7 +106,10 @@ struct ProbeJob {
   int32_t kd;        // row pitch of the operand (padded window pixels)
   int32_t ldf;       // row pitch of the DFT workspace
   int32_t t0;        // first 64-pixel tile of this job: prefix of ceil(W^2 / 64) over the jobs
-  int32_t atom, pad;
+  int32_t atom;
+  int32_t cu0, cnu;  // raster rows u and columns v that the atom needs (its crop mask; all
+  int32_t cv0, cnv;  // of them at interpolation factor 1): (cu0 + i) mod S_y, i < cnu, ...
+  int32_t pad;
 };
 
 struct ProbeArgs {
@@ -126,6 +129,7 @@ struct ProbeArgs {
   const float2* tw;         // [L] exp(-2 pi i m / L)
   int L, ny, nx, mode;
   int Sy, Sx, P, Ppad;
+  int gy, gx;               // beams fall on residues that are multiples of these (dividing S_y, S_x)
   float cb;                 // probe coefficient c_b
   int unit0, n_units;       // the launch's pixel tiles (job t0 numbering) and their count
   int n_jobs;               // jobs of the launch
@@ -348,11 +352,17 @@ hipError_t launch_recon_operand(const ReconArgs& a, void* out, int kind, int pre
                                 int64_t nrows_pad, int64_t ncols_pad, int64_t plane_stride,
                                 hipStream_t s);
 
+// out[rho] += sum over the jobs, in order, whose crop mask holds rho, of their
+// ntiles partial rows (pitch pitch; entry = place in the job's mask)
+hipError_t launch_reduce_crop(const float* partial, const GemmJob* jobs, int njobs, int ntiles, int pitch, int Sy,
+                              int Sx, float* out, hipStream_t s);
+
 // probe synthesis (k_probe.hip); scan dimensions up to BIP_MAX_SCAN
 constexpr int BIP_MAX_SCAN = 256;
 size_t probe_lds_bytes(int S);
-hipError_t launch_probe_fold_x(const ProbeArgs& pa, int unit0, int n_units, int n_jobs, hipStream_t s);
-hipError_t launch_probe_y(const ProbeArgs& pa, int prec, bool u, int max_kd, int n_jobs,
+// max_cnv / max_cnu: the most scan columns / rows a job needs
+hipError_t launch_probe_fold_x(const ProbeArgs& pa, int unit0, int n_units, int n_jobs, int max_cnv, hipStream_t s);
+hipError_t launch_probe_y(const ProbeArgs& pa, int prec, bool u, int max_kd, int max_cnu, int max_cnv, int n_jobs,
                           hipStream_t s);
 
 // strided DFT pass of the probe-sum adjoint (k_probe.hip)
@@ -388,8 +398,9 @@ hipError_t launch_focal_kernel(const FocalAtom* atoms, int n_atoms, const double
                                double lambda, float2* ker, hipStream_t s);
 // forward step and crop of `rows` rows of each job's DFT workspace block: windows of jobs_m (M x M,
 // pitch ldf) to those of jobs_w (W x W, same pitch), in place
+// (row i S_x + v of a block: residue row i, scan column v; columns outside the atom's are skipped)
 hipError_t launch_focal_step(const ProbeJob* jobs_m, const ProbeJob* jobs_w, const float2* ker, float2* fx, int rows,
-                             int n_jobs, int max_m, hipStream_t s);
+                             int Sx, int n_jobs, int max_m, hipStream_t s);
 
 // slice potentials (k_potential.hip).  Terms are (x, y, A, w) quadruples
 // grouped by slice: slice z holds terms start[z] .. start[z + 1] (device i64).

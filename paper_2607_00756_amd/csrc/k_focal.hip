@@ -171,9 +171,12 @@ __device__ inline void cmfma(float2 a, float2 b, v4f& re, v4f& im) {
 template <int NR>
 __global__ __launch_bounds__(NT, 4) void k_focal_step(const ProbeJob* __restrict__ jobs_m,
                                                    const ProbeJob* __restrict__ jobs_w,
-                                                   const float2* __restrict__ ker, float2* __restrict__ fx) {
+                                                   const float2* __restrict__ ker, float2* __restrict__ fx,
+                                                   int Sx) {
   extern __shared__ float2 sm[];
   const ProbeJob jm = jobs_m[blockIdx.y];
+  const int v = (int)blockIdx.x % Sx;
+  if ((v - jm.cv0 + Sx) % Sx >= jm.cnv) return;  // a scan column off the atom's mask: uniform per workgroup
   const int M = jm.W, W = jobs_w[blockIdx.y].W, pad = (M - W) / 2;
   const int ly = M + 1;                // LDS pitch of Y
   float2* cy = sm;                     // [M]
@@ -295,7 +298,7 @@ hipError_t launch_focal_kernel(const FocalAtom* atoms, int n_atoms, const double
 }
 
 hipError_t launch_focal_step(const ProbeJob* jobs_m, const ProbeJob* jobs_w, const float2* ker, float2* fx, int rows,
-                             int n_jobs, int max_m, hipStream_t s) {
+                             int Sx, int n_jobs, int max_m, hipStream_t s) {
   if (n_jobs <= 0 || rows <= 0) return hipSuccess;
   if (max_m > FOCAL_M || n_jobs > 65535) return hipErrorInvalidValue;
   const int nr = std::max(1, max_m / 32);  // W <= M / 2
@@ -306,7 +309,7 @@ hipError_t launch_focal_step(const ProbeJob* jobs_m, const ProbeJob* jobs_w, con
     hipError_t e =                                                                                         \
         hipFuncSetAttribute((const void*)k_focal_step<N>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
     if (e != hipSuccess) return e;                                                                         \
-    hipLaunchKernelGGL(k_focal_step<N>, grid, dim3(NT), lds, s, jobs_m, jobs_w, ker, fx);                  \
+    hipLaunchKernelGGL(k_focal_step<N>, grid, dim3(NT), lds, s, jobs_m, jobs_w, ker, fx, Sx);                  \
     return hipGetLastError();                                                                              \
   }
   FS(1)

@@ -943,6 +943,25 @@ __global__ void k_reduce_map(const float* __restrict__ partial, int ntiles, int 
   out[rho] = accumulate ? out[rho] + s : s;
 }
 
+// The quadratic form at f > 1 runs one job (atom) at a time over the scans of
+// its crop mask; here every scan collects its atoms, in job order.
+__global__ void k_reduce_crop(const float* __restrict__ partial, const GemmJob* __restrict__ jobs, int njobs, int ntiles,
+                              int pitch, int Sy, int Sx, float* out) {
+  const int rho = blockIdx.x * blockDim.x + threadIdx.x;
+  if (rho >= Sy * Sx) return;
+  const int u = rho / Sx, v = rho - u * Sx;
+  float s = 0.f;
+  for (int j = 0; j < njobs; ++j) {
+    const GemmJob& q = jobs[j];
+    const int iu = (u - q.cu0 + Sy) % Sy, iv = (v - q.cv0 + Sx) % Sx;
+    if (iu >= q.cnu || iv >= q.cnv) continue;
+    const int nt = min(ntiles, (q.n_lim + GRAM_TILE - 1) / GRAM_TILE);  // the job's column tiles
+    const float* p = partial + (int64_t)j * ntiles * pitch + iu * q.cnv + iv;
+    for (int t = 0; t < nt; ++t) s += p[(int64_t)t * pitch];
+  }
+  out[rho] += s;
+}
+
 // qEELS: sum the per-beam intensities over h_y at fixed h_x, in detector order
 __global__ void k_qeels(const float* __restrict__ beams_out, const int32_t* __restrict__ bin_start,
                         const int32_t* __restrict__ bin_list, int ndet, int P, int nq,
@@ -1109,6 +1128,14 @@ hipError_t launch_reduce_map(const float* partial, int ntiles, int Ppad, int P, 
                              int accumulate, hipStream_t s) {
   hipLaunchKernelGGL(k_reduce_map, dim3((P + 255) / 256), dim3(256), 0, s, partial, ntiles, Ppad,
                      P, out, accumulate);
+  return hipGetLastError();
+}
+
+hipError_t launch_reduce_crop(const float* partial, const GemmJob* jobs, int njobs, int ntiles, int pitch, int Sy,
+                              int Sx, float* out, hipStream_t s) {
+  if (njobs <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_reduce_crop, dim3((Sy * Sx + 63) / 64), dim3(64), 0, s, partial, jobs, njobs, ntiles, pitch, Sy,
+                     Sx, out);
   return hipGetLastError();
 }
 
