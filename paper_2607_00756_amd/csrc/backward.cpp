@@ -16,6 +16,7 @@
 
 #include "bip_internal.h"
 #include "host_common.h"
+#include "recon_core.h"
 
 namespace bip {
 namespace {
@@ -158,12 +159,14 @@ int bip_eels_backward(bip_plan* p, int32_t n_ch, const float* H, const int64_t* 
   const int64_t bGp = Ppad * kdm;        // g_psi (complex)
   const int64_t bGs = Dpad * kdm;        // g_S2~ (complex)
   const int64_t per_atom = 8 * (bX + bPsi + bS2b + bS2d + 4 * bQ + 2 * bA + bGp + bGs) + 16 * 256;
+  // The reconstruction adjoints run batched too.  Their buffers (Z, g_z, gamma
+  // and the g_H scratch of an atom) lie where the operands of the products
+  // were, which nothing reads by then: nsub atoms at a time, at least one.
+  const int64_t sub_bytes = roundup(bX * 8, 256) + roundup(nbmax * W2m * 8, 256) + roundup(nbmax * W2m * 4, 256) +
+                            roundup((int64_t)n_ch * W2m * 8, 256);
+  const int64_t dead_atom = 8 * (bPsi + bS2b + bS2d + 2 * bQ + 2 * bA);  // operand bytes of an atom
   size_t fixed = 0;
   auto sz = [&](size_t bytes) { fixed += (size_t)roundup((int64_t)bytes, 256); };
-  sz((size_t)bX * 8);              // Z
-  sz((size_t)nbmax * W2m * 8);     // g_z
-  sz((size_t)nbmax * W2m * 4);     // gamma
-  sz((size_t)n_ch * W2m * 8);      // g_H scratch
   sz((size_t)Ppad * 4);            // Ibar
   sz((size_t)p->n_atoms * 16);     // dtau
   sz((size_t)groups * G * 4);      // dV partials
@@ -171,6 +174,8 @@ int bip_eels_backward(bip_plan* p, int32_t n_ch, const float* H, const int64_t* 
   sz(tws.size() * 8);
   sz(jprobe.size() * sizeof(ProbeJob));
   sz(4 * (size_t)p->n_atoms * sizeof(GemmJob));
+  sz((size_t)p->n_atoms * sizeof(AdjAtom));
+  sz(2 * (size_t)p->n_atoms * sizeof(ReconAtom));
   // checkpoint segments longer than one slice are recomputed per column batch:
   // a forward state [batch][G] and the K - 1 recomputed slices [K - 1][batch][G]
   const int K = p->o.ckpt_stride;
@@ -191,13 +196,10 @@ int bip_eels_backward(bip_plan* p, int32_t n_ch, const float* H, const int64_t* 
   }
   int gt, gtn;
   gemm_tile(prec, EPI_STORE, gt, gtn);
-  int rc = ensure_work(p, fixed + (size_t)nat_max * per_atom + 4096, st);
+  const int64_t sub_more = std::max<int64_t>(0, sub_bytes - nat_max * dead_atom);
+  int rc = ensure_work(p, fixed + (size_t)nat_max * per_atom + (size_t)sub_more + 4096, st);
   if (rc) return rc;
   Workspace ws{(char*)p->d_work, 0};
-  float2* Z = (float2*)ws.take((size_t)bX * 8);
-  float2* gz = (float2*)ws.take((size_t)nbmax * W2m * 8);
-  float* gam = (float*)ws.take((size_t)nbmax * W2m * 4);
-  float2* gHs = (float2*)ws.take((size_t)n_ch * W2m * 8);
   float* ibar = (float*)ws.take((size_t)Ppad * 4);
   double* dtau = (double*)ws.take((size_t)p->n_atoms * 16);
   float* dvp = (float*)ws.take((size_t)groups * G * 4);
@@ -205,19 +207,30 @@ int bip_eels_backward(bip_plan* p, int32_t n_ch, const float* H, const int64_t* 
   float2* d_tws = (float2*)ws.take(tws.size() * 8);
   ProbeJob* d_probe = (ProbeJob*)ws.take(jprobe.size() * sizeof(ProbeJob));
   GemmJob* d_jobs = (GemmJob*)ws.take(4 * (size_t)p->n_atoms * sizeof(GemmJob));
+  AdjAtom* d_adj = (AdjAtom*)ws.take((size_t)p->n_atoms * sizeof(AdjAtom));
+  ReconAtom* d_ratoms = (ReconAtom*)ws.take(2 * (size_t)p->n_atoms * sizeof(ReconAtom));
   const int64_t NA = nat_max;
   float2* X = (float2*)ws.take((size_t)(NA * bX) * 8);
+  const size_t dead0 = ws.used;
   // operand planes: 8 bytes per element in FP32 (two planes) and in split
   // precision (four 2-byte planes); plane strides below are in elements
   char* psiT = (char*)ws.take((size_t)(2 * NA * bPsi) * 4);
   char* S2b = (char*)ws.take((size_t)(2 * NA * bS2b) * 4);
   char* S2d = (char*)ws.take((size_t)(2 * NA * bS2d) * 4);
   char* Qp = (char*)ws.take((size_t)(2 * NA * bQ) * 4);
-  float2* Gm = (float2*)ws.take((size_t)(NA * bQ) * 8);
   char* A1 = (char*)ws.take((size_t)(2 * NA * bA) * 4);
   char* B1 = (char*)ws.take((size_t)(2 * NA * bA) * 4);
-  float2* R = (float2*)ws.take((size_t)(NA * bQ) * 8);
   char* Kp = (char*)ws.take((size_t)(2 * NA * bQ) * 4);
+  if (sub_more > 0) ws.take((size_t)sub_more);
+  const int nsub = (int)std::max<int64_t>(1, std::min<int64_t>(NA, (int64_t)(ws.used - dead0) / sub_bytes));
+  Workspace sub{(char*)p->d_work + dead0, 0};
+  float2* Z = (float2*)sub.take((size_t)(nsub * bX) * 8);
+  float2* gz = (float2*)sub.take((size_t)nsub * nbmax * W2m * 8);
+  float* gam = (float*)sub.take((size_t)nsub * nbmax * W2m * 4);
+  float2* gHs = (float2*)sub.take((size_t)nsub * n_ch * W2m * 8);
+  if (sub.used > ws.used - dead0) return err(BIP_ENOMEM, "internal: backward workspace");
+  float2* Gm = (float2*)ws.take((size_t)(NA * bQ) * 8);
+  float2* R = (float2*)ws.take((size_t)(NA * bQ) * 8);
   float2* gpsi = (float2*)ws.take((size_t)(NA * bGp) * 8);
   float2* gS2 = (float2*)ws.take((size_t)(NA * bGs) * 8);
   float2* rec = K > 1 ? (float2*)ws.take((size_t)K * bmax * G * 8) : nullptr;
@@ -313,11 +326,25 @@ int bip_eels_backward(bip_plan* p, int32_t n_ch, const float* H, const int64_t* 
   }
   for (int c0 = 0; c0 < na; c0 += nat_max) gemm_gram_plan(&hj[c0], std::min(nat_max, na - c0), gprec, 1);
   HIPCHK(hipMemcpyAsync(d_jobs, hj.data(), hj.size() * sizeof(GemmJob), hipMemcpyHostToDevice, st), "jobs");
+  std::vector<AdjAtom>& hadj = p->h_adj;
+  std::vector<ReconAtom>& hra = p->h_ratoms;  // the K-blocked operands of every atom, then the [d][r] ones
+  hadj.clear();
+  hra.assign(2 * (size_t)na, ReconAtom{});
+  for (int a = 0; a < na; ++a) {
+    const int i = a % nat_max;
+    const int W2 = p->W[a] * p->W[a];
+    hadj.push_back(AdjAtom{p->off1[a], p->off2[a], H_off[a], p->W[a], p->oy[a], p->ox[a], i, i % nsub, 0});
+    hra[a] = ReconAtom{p->off2[a], i * bS2b, p->W[a], p->oy[a], p->ox[a], (int32_t)roundup(W2, 128)};
+    hra[na + a] = ReconAtom{p->off2[a], i * bS2d, p->W[a], p->oy[a], p->ox[a], (int32_t)roundup(W2, 32)};
+  }
+  HIPCHK(hipMemcpyAsync(d_adj, hadj.data(), hadj.size() * sizeof(AdjAtom), hipMemcpyHostToDevice, st), "atoms");
+  HIPCHK(hipMemcpyAsync(d_ratoms, hra.data(), hra.size() * sizeof(ReconAtom), hipMemcpyHostToDevice, st), "atoms");
   for (int c0 = 0; c0 < na; c0 += nat_max) {
     const int nat = std::min(nat_max, na - c0);
-    int max_n1 = 0, max_kd = 0;
+    int max_n1 = 0, max_kd = 0, max_w2 = 0;
     for (int a = c0; a < c0 + nat; ++a) {
       const int W2 = p->W[a] * p->W[a];
+      max_w2 = std::max(max_w2, W2);
       max_n1 = std::max(max_n1, (int)roundup(W2, 128));
       max_kd = std::max(max_kd, (int)roundup(W2, 32));
     }
@@ -327,22 +354,26 @@ int bip_eels_backward(bip_plan* p, int32_t n_ch, const float* H, const int64_t* 
     HIPCHK(launch_probe_fold_x(pa, jprobe[c0].t0, jl.t0 + (jl.W * jl.W + 63) / 64 - jprobe[c0].t0, nat, scan_sx, st),
            "probe fold");
     HIPCHK(launch_probe_y(pa, prec, false, max_kd, scan_sy, scan_sx, nat, st), "probe synthesis");
-    for (int a = c0; a < c0 + nat; ++a) {
-      const int64_t i = a - c0;
-      const int W2 = p->W[a] * p->W[a];
-      const int64_t kd = roundup(W2, 32), n1 = roundup(W2, 128);
-      // S2~ K-blocked (Gram) and [d][r] (gradient product)
-      ReconArgs ra = recon_args(p, a, 2);
-      ra.scale = gsc;
-      HIPCHK(launch_recon_operand(ra, S2b + i * bS2b * gesz, 0, gprec, Dk, n1, Dk, NA * bS2b, st),
-             "recon S2");
-      HIPCHK(launch_recon_operand(recon_args(p, a, 2), S2d + i * bS2d * esz, 1, prec, kd, Dpad, kd,
-                                  NA * bS2d, st), "recon S2");
-      // conj(psi) and Ibar psi as [r][rho] operands of R
-      HIPCHK(launch_psi_transpose(prec, psiT + i * bPsi * esz, NA * bPsi, (int)kd, W2, P, (int)Ppad,
-                                  (int)n1, ibar, A1 + i * bA * esz, B1 + i * bA * esz, NA * bA, st),
-             "psi transpose");
+    // S2~ K-blocked (Gram) and [d][r] (gradient product)
+    ReconArgs ra = recon_args(p, 0, 2);
+    ra.win = p->d_win2;
+    ra.scale = gsc;
+    if (p->tile_np2 <= TILE_NP) {
+      HIPCHK(launch_recon_kblk_atoms(ra, d_ratoms + c0, nat, S2b, gprec, Dk, NA * bS2b, max_n1, st), "recon S2");
+    } else {
+      for (int a = c0; a < c0 + nat; ++a) {
+        ReconArgs r1 = recon_args(p, a, 2);
+        r1.scale = gsc;
+        HIPCHK(launch_recon_operand(r1, S2b + hra[a].out_off * gesz, 0, gprec, Dk, hra[a].n_r, Dk, NA * bS2b, st),
+               "recon S2");
+      }
     }
+    ra.scale = 1.f;
+    HIPCHK(launch_recon_rows_atoms(ra, d_ratoms + na + c0, nat, S2d, prec, Dpad, NA * bS2d, max_kd, st), "recon S2");
+    // conj(psi) and Ibar psi as [r][rho] operands of R
+    HIPCHK(launch_psi_transpose(prec, d_adj + c0, nat, max_w2, psiT, bPsi, NA * bPsi, P, (int)Ppad, ibar, A1, B1, bA,
+                                NA * bA, st),
+           "psi transpose");
     // Gram matrix G and Q = G o Hc
     GemmArgs ga{};
     ga.H = (const float2*)H;
@@ -368,13 +399,7 @@ int bip_eels_backward(bip_plan* p, int32_t n_ch, const float* H, const int64_t* 
     gr.out = R;
     gr.m_store = max_n1;
     HIPCHK(launch_zgemm(prec, EPI_STORE + EPI_CONJ_A, gr, max_n1 / gt, max_n1 / gtn, nat, st), "R");
-    for (int a = c0; a < c0 + nat; ++a) {
-      const int64_t i = a - c0;
-      const int W2 = p->W[a] * p->W[a];
-      const int64_t kd = roundup(W2, 32), n1 = roundup(W2, 128);
-      HIPCHK(launch_kmat(prec, R + i * bQ, (const float2*)H + H_off[a], n_ch, W2, (int)kd, (int)n1,
-                         Kp + i * bQ * esz, NA * bQ, st), "K");
-    }
+    HIPCHK(launch_kmat(prec, d_adj + c0, nat, max_w2, R, bQ, (const float2*)H, n_ch, Kp, NA * bQ, st), "K");
     // g_psi = Ibar (Q psi) and g_S2~ = S2~ K^T
     GemmArgs gp{};
     gp.A = psiT;
@@ -397,29 +422,29 @@ int bip_eels_backward(bip_plan* p, int32_t n_ch, const float* H, const int64_t* 
     gs.out = gS2;
     gs.m_store = (int)Dpad;
     HIPCHK(launch_zgemm(prec, EPI_STORE, gs, (int)(Dpad / gt), max_n1 / gtn, nat, st), "g_S2");
-    for (int a = c0; a < c0 + nat; ++a) {
-      const int64_t i = a - c0;
-      const int W2 = p->W[a] * p->W[a];
-      const int64_t kd = roundup(W2, 32), ldf = roundup(W2, 64);
-      const float2* Ha = (const float2*)H + H_off[a];
+    for (int s0 = c0; s0 < c0 + nat; s0 += nsub) {
+      const int ns = std::min(nsub, c0 + nat - s0);
+      const AdjAtom* da = d_adj + s0;
       // transition-potential cotangent and the position gradient through H
-      float2* gH = dL_dHconj ? (float2*)dL_dHconj + H_off[a] : gHs;
-      HIPCHK(launch_grad_h(Gm + i * bQ, R + i * bQ, Ha, n_ch, W2, (int)kd, gH, st), "g_H");
+      HIPCHK(launch_grad_h(da, ns, max_w2, Gm, R, bQ, (const float2*)H, n_ch, (float2*)dL_dHconj, gHs, n_ch * W2m, st),
+             "g_H");
       if (dHdx)
-        HIPCHK(launch_grad_tau(gH, (const float2*)dHdx + H_off[a], (const float2*)dHdy + H_off[a],
-                               n_ch * W2, dtau + 2 * a, st), "dtau");
+        HIPCHK(launch_grad_tau(da, ns, (const float2*)dL_dHconj, gHs, n_ch * W2m, (const float2*)dHdx,
+                               (const float2*)dHdy, n_ch, s0, dtau, st),
+               "dtau");
       // adjoint of the probe sum: Z[a][c][r] = sum_{u,v} exp(+2 pi i (a u/S_y + c v/S_x)) g_psi
-      HIPCHK(launch_dft_pass(gpsi + i * bGp, X, scan_sx, kd, scan_sx * kd, ldf, scan_sx * ldf, scan_sy, W2,
-                             twxc, st), "adjoint DFT x");
-      HIPCHK(launch_dft_pass(X, Z, scan_sy, scan_sx * ldf, ldf, scan_sx * ldf, ldf, scan_sx, W2, twyc, st),
-             "adjoint DFT y");
+      HIPCHK(launch_dft_adjoint(false, da, ns, max_w2, gpsi, bGp, X, bX, scan_sy, scan_sx, twxc, st), "adjoint DFT x");
+      HIPCHK(launch_dft_adjoint(true, da, ns, max_w2, X, bX, Z, bX, scan_sy, scan_sx, twyc, st), "adjoint DFT y");
       // reconstruction adjoints -> window cotangents
-      HIPCHK(launch_recon_adjoint(recon_args(p, a, 1), 1, Z, ldf, scan_sy, scan_sx, cb, gz, gam,
-                                  p->d_par1, p->Bp1, p->d_tp1_rp, p->d_tp1_b, p->d_tp1_w,
-                                  p->d_gwin1 + p->off1[a], st), "recon adjoint S1");
-      HIPCHK(launch_recon_adjoint(recon_args(p, a, 2), 2, gS2 + i * bGs, kd, scan_sy, scan_sx, cb, gz, gam,
-                                  p->d_par2, p->Bp2, p->d_tp2_rp, p->d_tp2_b, p->d_tp2_w,
-                                  p->d_gwin2 + p->off2[a], st), "recon adjoint S2");
+      ReconArgs r1 = recon_args(p, 0, 1), r2 = recon_args(p, 0, 2);
+      r1.win = p->d_win1;
+      r2.win = p->d_win2;
+      HIPCHK(launch_recon_adjoint(r1, 1, da, ns, max_w2, Z, bX, scan_sy, scan_sx, cb, gz, gam, nbmax * W2m, p->d_par1,
+                                  p->Bp1, p->d_tp1_rp, p->d_tp1_b, p->d_tp1_w, p->d_gwin1, st),
+             "recon adjoint S1");
+      HIPCHK(launch_recon_adjoint(r2, 2, da, ns, max_w2, gS2, bGs, scan_sy, scan_sx, cb, gz, gam, nbmax * W2m, p->d_par2,
+                                  p->Bp2, p->d_tp2_rp, p->d_tp2_b, p->d_tp2_w, p->d_gwin2, st),
+             "recon adjoint S2");
     }
   }
   // ----------------------------------------------------- reverse sweeps

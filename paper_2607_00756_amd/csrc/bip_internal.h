@@ -62,6 +62,15 @@ struct ReconAtom {
   int32_t n_r;      // operand rows (window pixels rounded up to whole tiles)
 };
 
+// One atom of the batched backward kernels (grid z = atom).
+struct AdjAtom {
+  int64_t win1, win2;  // the atom's blocks in the window (and window-cotangent) stacks
+  int64_t h_off;       // first H element
+  int32_t W, oy, ox;
+  int32_t slot;        // the atom's block in the chunk's operand and product buffers
+  int32_t sub, pad;    // and in the reconstruction-adjoint buffers
+};
+
 enum Epilogue { EPI_ABS2_MAP = 0, EPI_ABS2_BEAMS, EPI_GRAMQ, EPI_QUAD, EPI_STORE };
 
 struct GemmArgs {
@@ -224,6 +233,7 @@ struct bip_plan {
   // host tables read by asynchronous copies; kept alive until the next call
   std::vector<bip::GemmJob> h_jobs2, h_jobs3;
   std::vector<bip::ReconAtom> h_ratoms;
+  std::vector<bip::AdjAtom> h_adj;
   std::vector<int32_t> h_qstart, h_qlist;
   std::vector<bip::ProbeJob> h_probe;
   std::vector<int32_t> h_cells;   // cell_start then cell_beams
@@ -346,6 +356,9 @@ hipError_t launch_recon_plain(const ReconArgs& a, float2* out, hipStream_t s);
 hipError_t launch_recon_kblk_atoms(const ReconArgs& a, const ReconAtom* atoms, int n_atoms, void* out,
                                    int prec, int64_t ncols_pad, int64_t plane_stride, int max_nr,
                                    hipStream_t s);
+// kind 1 operands (below) of n_atoms atoms in one launch, any parents: [nrows_pad][n_r] blocks
+hipError_t launch_recon_rows_atoms(const ReconArgs& a, const ReconAtom* atoms, int n_atoms, void* out, int prec,
+                                   int64_t nrows_pad, int64_t plane_stride, int max_nr, hipStream_t s);
 // GEMM operand outputs; layout kind 0: [r][b] (b fastest, ld = ldk, rows up to nrows)
 // kind 1: [b][r] (r fastest).  prec: BIP_PREC_*; planes at stride plane_stride elements.
 hipError_t launch_recon_operand(const ReconArgs& a, void* out, int kind, int prec, int64_t ld,
@@ -365,26 +378,30 @@ hipError_t launch_probe_fold_x(const ProbeArgs& pa, int unit0, int n_units, int 
 hipError_t launch_probe_y(const ProbeArgs& pa, int prec, bool u, int max_kd, int max_cnu, int max_cnv, int n_jobs,
                           hipStream_t s);
 
-// strided DFT pass of the probe-sum adjoint (k_probe.hip)
-hipError_t launch_dft_pass(const float2* in, float2* out, int S, int64_t js, int64_t os, int64_t ks,
-                           int64_t os2, int n_outer, int W2, const float2* tws, hipStream_t s);
-
 // gradient kernels (k_backward.hip)
 // prec: BIP_PREC_FP32 or BIP_PREC_SPLIT_BF16 (operand planes)
-hipError_t launch_psi_transpose(int prec, const void* psiT, int64_t psp, int kd, int W2, int P,
-                                int Ppad, int n1, const float* ibar, void* A1, void* B1, int64_t apl,
-                                hipStream_t s);
-hipError_t launch_kmat(int prec, const float2* R, const float2* H, int n_ch, int W2, int kd, int n1,
-                       void* Kp, int64_t kpl, hipStream_t s);
-hipError_t launch_grad_h(const float2* G, const float2* R, const float2* H, int n_ch, int W2, int kd,
-                         float2* gH, hipStream_t s);
-hipError_t launch_grad_tau(const float2* gH, const float2* dHx, const float2* dHy, int n,
-                           double* out, hipStream_t s);
-hipError_t launch_recon_adjoint(const ReconArgs& a, int side, const float2* gsrc, int64_t ld_src,
-                                int Sy, int Sx, float cb, float2* gz, float* gam,
-                                const int2* parents, int Bp, const int32_t* tp_rp,
-                                const int32_t* tp_b, const float* tp_w, float2* gwin,
-                                hipStream_t s);
+// All take n atoms (device AdjAtom list), max_w2 pixels in the largest window; strides per slot
+// (or sub) in elements.
+hipError_t launch_psi_transpose(int prec, const AdjAtom* atoms, int n, int max_w2, const void* psiT, int64_t psi_stride,
+                                int64_t psp, int P, int Ppad, const float* ibar, void* A1, void* B1, int64_t a_stride,
+                                int64_t apl, hipStream_t s);
+hipError_t launch_kmat(int prec, const AdjAtom* atoms, int n, int max_w2, const float2* R, int64_t stride,
+                       const float2* H, int n_ch, void* Kp, int64_t kpl, hipStream_t s);
+// gH: [h_off of the atom ..) of out, or the atom's sub block of scratch when out is null
+hipError_t launch_grad_h(const AdjAtom* atoms, int n, int max_w2, const float2* G, const float2* R, int64_t stride,
+                         const float2* H, int n_ch, float2* out, float2* scratch, int64_t scratch_stride, hipStream_t s);
+// dtau: two doubles per atom of the plan; a0: the plan index of atoms[0]
+hipError_t launch_grad_tau(const AdjAtom* atoms, int n, const float2* gH, const float2* scratch, int64_t scratch_stride,
+                           const float2* dHx, const float2* dHy, int n_ch, int a0, double* out, hipStream_t s);
+// side 1: gsrc is Z [cell][ldf] (stride per sub), side 2: g_S2~ [d][kd] (stride per slot); gz, gam per sub
+hipError_t launch_recon_adjoint(const ReconArgs& a, int side, const AdjAtom* atoms, int n, int max_w2,
+                                const float2* gsrc, int64_t src_stride, int Sy, int Sx, float cb, float2* gz, float* gam,
+                                int64_t gz_stride, const int2* parents, int Bp, const int32_t* tp_rp,
+                                const int32_t* tp_b, const float* tp_w, float2* gwin, hipStream_t s);
+// strided DFT pass of the probe-sum adjoint (k_probe.hip), along x (in: g_psi of each slot, pitch kd;
+// out: X of each slot, pitch ldf) or along y (in: X; out: Z of each sub, pitch ldf)
+hipError_t launch_dft_adjoint(bool along_y, const AdjAtom* atoms, int n, int max_w2, const float2* in, int64_t in_stride,
+                              float2* out, int64_t out_stride, int Sy, int Sx, const float2* tws, hipStream_t s);
 
 // focal back-propagation (k_focal.hip)
 hipError_t launch_focal_dist(const float* V, const FocalAtom* atoms, int n_atoms, int ny, int nx,

@@ -14,6 +14,14 @@
 // with phi = z/|z|, and for the parent windows D_p (z = sum w D, m = sum w |D|)
 //   g_D_p = sum_b w_bp (g_z,b + gamma_b D_p/|D_p|);
 // the cotangent of the parent column is conj(de-tilt carrier) g_D_p.
+//
+// Every kernel takes the atoms of a chunk in one launch (a grid dimension over
+// the AdjAtom list; the grid covers the largest window, and what lies outside an
+// atom's own returns at once).  One window of 24 x 24 pixels leaves most of the
+// chip idle: for 16 of them on the 256^2 grid, an atom at a time, phase B took
+// 1.60 ms in 32 launches, 0.84 in 2 so, and the differentiated map 42.5 ms, 40.7
+// so; for 4 windows of 20 x 20 on 128^2, 2.41 ms and 2.04.  An atom's sums keep
+// their order, so its gradient has the same bits in any chunk.
 #include "bip_internal.h"
 #include "planes.h"
 #include "recon_core.h"
@@ -26,16 +34,20 @@ namespace {
 // of precision PREC, rows up to n1, columns up to Ppad) from psi^T [rho][r]
 // (planes of the same precision).
 template <int PREC>
-__global__ void k_psi_transpose(const void* __restrict__ psiT, int64_t psp, int kd, int W2, int P,
-                                int Ppad, const float* __restrict__ ibar, void* A1, void* B1,
-                                int64_t apl) {
+__global__ void k_psi_transpose(const AdjAtom* __restrict__ atoms, const void* __restrict__ psiT, int64_t psi_stride,
+                                int64_t psp, int P, int Ppad, const float* __restrict__ ibar, void* A1, void* B1,
+                                int64_t a_stride, int64_t apl) {
   __shared__ float2 tile[32][33];
+  const AdjAtom at = atoms[blockIdx.z];
+  const int W2 = at.W * at.W, kd = (W2 + 31) & ~31, n1 = (W2 + 127) & ~127;
   const int rho0 = blockIdx.x * 32, r0 = blockIdx.y * 32;
+  if (r0 >= n1) return;
+  const int64_t p0 = (int64_t)at.slot * psi_stride, a0 = (int64_t)at.slot * a_stride;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8 threads
   for (int k = 0; k < 32; k += 8) {
     const int rho = rho0 + ty + k, r = r0 + tx;
     float2 v = make_float2(0.f, 0.f);
-    if (rho < P && r < W2) v = load_planes<PREC>(psiT, (int64_t)rho * kd + r, psp);
+    if (rho < P && r < W2) v = load_planes<PREC>(psiT, p0 + (int64_t)rho * kd + r, psp);
     tile[ty + k][tx] = v;
   }
   __syncthreads();
@@ -43,7 +55,7 @@ __global__ void k_psi_transpose(const void* __restrict__ psiT, int64_t psp, int 
     const int r = r0 + ty + k, rho = rho0 + tx;
     const float2 v = tile[tx][ty + k];
     const float s = rho < P ? ibar[rho] : 0.f;
-    const int64_t i = (int64_t)r * Ppad + rho;
+    const int64_t i = a0 + (int64_t)r * Ppad + rho;
     store_planes<PREC>(A1, i, apl, v.x, v.y);
     store_planes<PREC>(B1, i, apl, s * v.x, s * v.y);
   }
@@ -52,10 +64,14 @@ __global__ void k_psi_transpose(const void* __restrict__ psiT, int64_t psp, int 
 // K[r][r'] = R[r][r'] sum_n conj(H_n(r)) H_n(r') as operand planes of
 // precision PREC (zero outside the window), rows up to n1, columns up to kd.
 template <int PREC>
-__global__ void k_kmat(const float2* __restrict__ R, const float2* __restrict__ H, int n_ch, int W2,
-                       int kd, int n1, void* Kp, int64_t kpl) {
+__global__ void k_kmat(const AdjAtom* __restrict__ atoms, const float2* __restrict__ R_all, int64_t stride,
+                       const float2* __restrict__ H_all, int n_ch, void* Kp, int64_t kpl) {
+  const AdjAtom at = atoms[blockIdx.y];
+  const int W2 = at.W * at.W, kd = (W2 + 31) & ~31, n1 = (W2 + 127) & ~127;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= (int64_t)n1 * kd) return;
+  const float2* R = R_all + (int64_t)at.slot * stride;
+  const float2* H = H_all + at.h_off;
   const int r = (int)(i / kd), c = (int)(i - (int64_t)r * kd);
   float kr = 0.f, ki = 0.f;
   if (r < W2 && c < W2) {
@@ -69,7 +85,7 @@ __global__ void k_kmat(const float2* __restrict__ R, const float2* __restrict__ 
     kr = q.x * hr - q.y * hi;
     ki = q.x * hi + q.y * hr;
   }
-  store_planes<PREC>(Kp, i, kpl, kr, ki);
+  store_planes<PREC>(Kp, (int64_t)at.slot * stride + i, kpl, kr, ki);
 }
 
 // Fixed-order reduction of a float2 over a 256-thread block.
@@ -87,12 +103,18 @@ __device__ inline float2 block_sum(float2 v, float2* red) {
 }
 
 // g_H_n(r) = sum_r' G[r][r'] R[r][r'] H_n(r'), one workgroup per pixel r.
-__global__ __launch_bounds__(256) void k_grad_h(const float2* __restrict__ G,
-                                                const float2* __restrict__ R,
-                                                const float2* __restrict__ H, int n_ch, int W2,
-                                                int kd, float2* gH) {
+__global__ __launch_bounds__(256) void k_grad_h(const AdjAtom* __restrict__ atoms, const float2* __restrict__ G_all,
+                                                const float2* __restrict__ R_all, int64_t stride,
+                                                const float2* __restrict__ H_all, int n_ch, float2* out,
+                                                float2* scratch, int64_t scratch_stride) {
   __shared__ float2 red[4];
-  const int r = blockIdx.x;
+  const AdjAtom at = atoms[blockIdx.y];
+  const int W2 = at.W * at.W, kd = (W2 + 31) & ~31, r = blockIdx.x;
+  if (r >= W2) return;
+  const float2* G = G_all + (int64_t)at.slot * stride;
+  const float2* R = R_all + (int64_t)at.slot * stride;
+  const float2* H = H_all + at.h_off;
+  float2* gH = out ? out + at.h_off : scratch + (int64_t)at.sub * scratch_stride;
   for (int n = 0; n < n_ch; ++n) {
     float2 acc = make_float2(0.f, 0.f);
     for (int c = threadIdx.x; c < W2; c += 256) {
@@ -105,11 +127,18 @@ __global__ __launch_bounds__(256) void k_grad_h(const float2* __restrict__ G,
 }
 
 // dL/dtau = 2 Re sum conj(g_H) dH/dtau over one atom's channels and pixels.
-__global__ __launch_bounds__(256) void k_grad_tau(const float2* __restrict__ gH,
-                                                  const float2* __restrict__ dHx,
-                                                  const float2* __restrict__ dHy, int n,
-                                                  double* out) {
+__global__ __launch_bounds__(256) void k_grad_tau(const AdjAtom* __restrict__ atoms, const float2* __restrict__ gH_all,
+                                                  const float2* __restrict__ scratch, int64_t scratch_stride,
+                                                  const float2* __restrict__ dHx_all,
+                                                  const float2* __restrict__ dHy_all, int n_ch, int a0,
+                                                  double* out_all) {
   __shared__ double red[2][4];
+  const AdjAtom at = atoms[blockIdx.x];
+  const int n = n_ch * at.W * at.W;
+  const float2* gH = gH_all ? gH_all + at.h_off : scratch + (int64_t)at.sub * scratch_stride;
+  const float2* dHx = dHx_all + at.h_off;
+  const float2* dHy = dHy_all + at.h_off;
+  double* out = out_all + 2 * (a0 + (int)blockIdx.x);
   double sx = 0.0, sy = 0.0;
   for (int i = threadIdx.x; i < n; i += 256) {
     const float2 g = gH[i], ax = dHx[i], ay = dHy[i];
@@ -138,9 +167,19 @@ __global__ __launch_bounds__(256) void k_grad_tau(const float2* __restrict__ gH,
 // SIDE 1: the cotangent of S1~^b is c Z[cell(b)][r] (the adjoint of the
 // probe sum, see k_probe.hip); SIDE 2: g_S2~ [d][r] from the contraction.
 template <int SIDE>
-__global__ __launch_bounds__(256) void k_recon_adj_a(ReconArgs a, const float2* __restrict__ gsrc,
-                                                     int64_t ld_src, int Sy, int Sx, float cb,
-                                                     float2* gz, float* gam) {
+__global__ __launch_bounds__(256) void k_recon_adj_a(ReconArgs a, const AdjAtom* __restrict__ atoms,
+                                                     const float2* __restrict__ gsrc_all, int64_t src_stride, int Sy,
+                                                     int Sx, float cb, float2* gz_all, float* gam_all,
+                                                     int64_t gz_stride) {
+  const AdjAtom at = atoms[blockIdx.z];
+  a.W = at.W;
+  a.oy = at.oy;
+  a.ox = at.ox;
+  a.win += SIDE == 1 ? at.win1 : at.win2;
+  const float2* gsrc = gsrc_all + (int64_t)(SIDE == 1 ? at.sub : at.slot) * src_stride;
+  const int64_t ld_src = SIDE == 1 ? (a.W * a.W + 63) & ~63 : (a.W * a.W + 31) & ~31;
+  float2* gz = gz_all + (int64_t)at.sub * gz_stride;
+  float* gam = gam_all + (int64_t)at.sub * gz_stride;
   const int b = blockIdx.y * 4 + (threadIdx.x >> 6);
   if (b >= a.nb) return;
   const int W2 = a.W * a.W;
@@ -187,13 +226,23 @@ __global__ __launch_bounds__(256) void k_recon_adj_a(ReconArgs a, const float2* 
 // Phase B: per parent p (one wave) and pixel r (one lane), the cotangent of
 // the cropped parent column, conj(e_p) sum_b w_bp (g_z,b + gamma_b D_p/|D_p|)
 // over the beams that use p (transposed weights, fixed order).
-__global__ __launch_bounds__(256) void k_recon_adj_b(ReconArgs a, const int2* __restrict__ parents,
+__global__ __launch_bounds__(256) void k_recon_adj_b(ReconArgs a, const AdjAtom* __restrict__ atoms,
+                                                     const int2* __restrict__ parents,
                                                      int Bp, const int32_t* __restrict__ tp_rp,
                                                      const int32_t* __restrict__ tp_b,
                                                      const float* __restrict__ tp_w,
-                                                     const float2* __restrict__ gz,
-                                                     const float* __restrict__ gam, int detilt_sign,
-                                                     float2* gwin) {
+                                                     const float2* __restrict__ gz_all,
+                                                     const float* __restrict__ gam_all, int64_t gz_stride,
+                                                     int detilt_sign, float2* gwin_all) {
+  const AdjAtom at = atoms[blockIdx.z];
+  a.W = at.W;
+  a.oy = at.oy;
+  a.ox = at.ox;
+  const int64_t wo = detilt_sign > 0 ? at.win1 : at.win2;
+  a.win += wo;
+  float2* gwin = gwin_all + wo;
+  const float2* gz = gz_all + (int64_t)at.sub * gz_stride;
+  const float* gam = gam_all + (int64_t)at.sub * gz_stride;
   const int p = blockIdx.y * 4 + (threadIdx.x >> 6);
   if (p >= Bp) return;
   const int W2 = a.W * a.W;
@@ -204,6 +253,7 @@ __global__ __launch_bounds__(256) void k_recon_adj_b(ReconArgs a, const int2* __
   const float2 u = aD > 0.f ? cscale(D, 1.f / aD) : make_float2(0.f, 0.f);
   float2 acc = make_float2(0.f, 0.f);
   const int k1 = tp_rp[p + 1];
+#pragma unroll 4  // loads in flight; the sum stays in order
   for (int k = tp_rp[p]; k < k1; ++k) {
     const int b = tp_b[k];
     const float w = tp_w[k];
@@ -223,60 +273,59 @@ __global__ __launch_bounds__(256) void k_recon_adj_b(ReconArgs a, const int2* __
 
 }  // namespace
 
-hipError_t launch_psi_transpose(int prec, const void* psiT, int64_t psp, int kd, int W2, int P,
-                                int Ppad, int n1, const float* ibar, void* A1, void* B1, int64_t apl,
-                                hipStream_t s) {
-  const dim3 grid(Ppad / 32, n1 / 32);
+hipError_t launch_psi_transpose(int prec, const AdjAtom* atoms, int n, int max_w2, const void* psiT, int64_t psi_stride,
+                                int64_t psp, int P, int Ppad, const float* ibar, void* A1, void* B1, int64_t a_stride,
+                                int64_t apl, hipStream_t s) {
+  const dim3 grid(Ppad / 32, (max_w2 + 127) / 128 * 4, n);
   if (prec == BIP_PREC_FP32)
-    hipLaunchKernelGGL(k_psi_transpose<BIP_PREC_FP32>, grid, dim3(256), 0, s, psiT, psp, kd, W2, P,
-                       Ppad, ibar, A1, B1, apl);
+    hipLaunchKernelGGL(k_psi_transpose<BIP_PREC_FP32>, grid, dim3(256), 0, s, atoms, psiT, psi_stride, psp, P, Ppad,
+                       ibar, A1, B1, a_stride, apl);
   else if (prec == BIP_PREC_SPLIT_BF16)
-    hipLaunchKernelGGL(k_psi_transpose<BIP_PREC_SPLIT_BF16>, grid, dim3(256), 0, s, psiT, psp, kd, W2,
-                       P, Ppad, ibar, A1, B1, apl);
+    hipLaunchKernelGGL(k_psi_transpose<BIP_PREC_SPLIT_BF16>, grid, dim3(256), 0, s, atoms, psiT, psi_stride, psp, P,
+                       Ppad, ibar, A1, B1, a_stride, apl);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
-hipError_t launch_kmat(int prec, const float2* R, const float2* H, int n_ch, int W2, int kd, int n1,
-                       void* Kp, int64_t kpl, hipStream_t s) {
-  const int64_t n = (int64_t)n1 * kd;
-  const dim3 grid((unsigned)((n + 255) / 256));
+hipError_t launch_kmat(int prec, const AdjAtom* atoms, int n, int max_w2, const float2* R, int64_t stride,
+                       const float2* H, int n_ch, void* Kp, int64_t kpl, hipStream_t s) {
+  const int64_t m = (int64_t)((max_w2 + 127) & ~127) * ((max_w2 + 31) & ~31);
+  const dim3 grid((unsigned)((m + 255) / 256), n);
   if (prec == BIP_PREC_FP32)
-    hipLaunchKernelGGL(k_kmat<BIP_PREC_FP32>, grid, dim3(256), 0, s, R, H, n_ch, W2, kd, n1, Kp, kpl);
+    hipLaunchKernelGGL(k_kmat<BIP_PREC_FP32>, grid, dim3(256), 0, s, atoms, R, stride, H, n_ch, Kp, kpl);
   else if (prec == BIP_PREC_SPLIT_BF16)
-    hipLaunchKernelGGL(k_kmat<BIP_PREC_SPLIT_BF16>, grid, dim3(256), 0, s, R, H, n_ch, W2, kd, n1, Kp, kpl);
+    hipLaunchKernelGGL(k_kmat<BIP_PREC_SPLIT_BF16>, grid, dim3(256), 0, s, atoms, R, stride, H, n_ch, Kp, kpl);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
-hipError_t launch_grad_h(const float2* G, const float2* R, const float2* H, int n_ch, int W2, int kd,
-                         float2* gH, hipStream_t s) {
-  hipLaunchKernelGGL(k_grad_h, dim3(W2), dim3(256), 0, s, G, R, H, n_ch, W2, kd, gH);
+hipError_t launch_grad_h(const AdjAtom* atoms, int n, int max_w2, const float2* G, const float2* R, int64_t stride,
+                         const float2* H, int n_ch, float2* out, float2* scratch, int64_t scratch_stride, hipStream_t s) {
+  hipLaunchKernelGGL(k_grad_h, dim3(max_w2, n), dim3(256), 0, s, atoms, G, R, stride, H, n_ch, out, scratch,
+                     scratch_stride);
   return hipGetLastError();
 }
 
-hipError_t launch_grad_tau(const float2* gH, const float2* dHx, const float2* dHy, int n,
-                           double* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_grad_tau, dim3(1), dim3(256), 0, s, gH, dHx, dHy, n, out);
+hipError_t launch_grad_tau(const AdjAtom* atoms, int n, const float2* gH, const float2* scratch, int64_t scratch_stride,
+                           const float2* dHx, const float2* dHy, int n_ch, int a0, double* out, hipStream_t s) {
+  hipLaunchKernelGGL(k_grad_tau, dim3(n), dim3(256), 0, s, atoms, gH, scratch, scratch_stride, dHx, dHy, n_ch, a0, out);
   return hipGetLastError();
 }
 
-hipError_t launch_recon_adjoint(const ReconArgs& a, int side, const float2* gsrc, int64_t ld_src,
-                                int Sy, int Sx, float cb, float2* gz, float* gam,
-                                const int2* parents, int Bp, const int32_t* tp_rp,
-                                const int32_t* tp_b, const float* tp_w, float2* gwin,
-                                hipStream_t s) {
-  const int W2 = a.W * a.W;
-  const dim3 ga((W2 + 63) / 64, (a.nb + 3) / 4), gb((W2 + 63) / 64, (Bp + 3) / 4);
+hipError_t launch_recon_adjoint(const ReconArgs& a, int side, const AdjAtom* atoms, int n, int max_w2,
+                                const float2* gsrc, int64_t src_stride, int Sy, int Sx, float cb, float2* gz, float* gam,
+                                int64_t gz_stride, const int2* parents, int Bp, const int32_t* tp_rp,
+                                const int32_t* tp_b, const float* tp_w, float2* gwin, hipStream_t s) {
+  const dim3 ga((max_w2 + 63) / 64, (a.nb + 3) / 4, n), gb((max_w2 + 63) / 64, (Bp + 3) / 4, n);
   if (side == 1)
-    hipLaunchKernelGGL(k_recon_adj_a<1>, ga, dim3(256), 0, s, a, gsrc, ld_src, Sy, Sx, cb, gz, gam);
+    hipLaunchKernelGGL(k_recon_adj_a<1>, ga, dim3(256), 0, s, a, atoms, gsrc, src_stride, Sy, Sx, cb, gz, gam, gz_stride);
   else
-    hipLaunchKernelGGL(k_recon_adj_a<2>, ga, dim3(256), 0, s, a, gsrc, ld_src, Sy, Sx, cb, gz, gam);
+    hipLaunchKernelGGL(k_recon_adj_a<2>, ga, dim3(256), 0, s, a, atoms, gsrc, src_stride, Sy, Sx, cb, gz, gam, gz_stride);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_recon_adj_b, gb, dim3(256), 0, s, a, parents, Bp, tp_rp, tp_b, tp_w, gz, gam,
+  hipLaunchKernelGGL(k_recon_adj_b, gb, dim3(256), 0, s, a, atoms, parents, Bp, tp_rp, tp_b, tp_w, gz, gam, gz_stride,
                      side == 1 ? +1 : -1, gwin);
   return hipGetLastError();
 }

@@ -283,18 +283,29 @@ __global__ __launch_bounds__(NT) void k_probe_y(const ProbeArgs pa) {
     for (int rho = pa.P + lk; rho < pa.Ppad; rho += 4) put(rho, 0.f, 0.f);
 }
 
-// One strided DFT pass of the probe-sum adjoint: for every outer index o and
-// window pixel r < W2,
-//   out[k ks + o os2 + r] = sum_j T[(j k) mod S] in[j js + o os + r],
-// with T = exp(+2 pi i k/S) (the conjugate of the synthesis twiddles).
-__global__ __launch_bounds__(NT) void k_dft_pass(const float2* __restrict__ in, float2* out, int S,
-                                                 int64_t js, int64_t os, int64_t ks, int64_t os2,
-                                                 int W2, const float2* __restrict__ tws) {
+// One DFT pass of the probe-sum adjoint: for every outer index o and window
+// pixel r < W2 of an atom (grid z),
+//   out[k][o][r] = sum_j T[(j k) mod S] in[j][o][r],
+// with T = exp(+2 pi i k/S) (the conjugate of the synthesis twiddles).  Along
+// x (j = v, o = u) the rows of g_psi [u][v][kd] become X [u][k][ldf]; along y
+// (j = u, o = k_x) X becomes Z [k][k_x][ldf].
+__global__ __launch_bounds__(NT) void k_dft_adjoint(int along_y, const AdjAtom* __restrict__ atoms,
+                                                    const float2* __restrict__ in_all, int64_t in_stride,
+                                                    float2* out_all, int64_t out_stride, int Sy, int Sx,
+                                                    const float2* __restrict__ tws) {
   extern __shared__ float2 sm[];
+  const AdjAtom at = atoms[blockIdx.z];
+  const int W2 = at.W * at.W, r0 = blockIdx.x * RT;
+  if (r0 >= W2) return;
+  const int S = along_y ? Sy : Sx;
+  const int64_t kd = (W2 + 31) & ~31, ldf = (W2 + 63) & ~63;
+  const float2* in = in_all + (int64_t)at.slot * in_stride;
+  float2* out = out_all + (int64_t)(along_y ? at.sub : at.slot) * out_stride;
+  const int64_t js = along_y ? Sx * ldf : kd, os = along_y ? ldf : Sx * kd;
+  const int64_t ks = along_y ? Sx * ldf : ldf, os2 = along_y ? ldf : Sx * ldf;
   float2* sF = sm;
   float2* sT = sm + ((S + 3) & ~3) * RT;
   const int o = blockIdx.y;
-  const int r0 = blockIdx.x * RT;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   for (int i = threadIdx.x; i < S; i += NT) sT[i] = tws[i];
@@ -345,15 +356,15 @@ hipError_t launch_lds(K kernel, dim3 grid, size_t lds, const ProbeArgs& pa, hipS
 
 size_t probe_lds_bytes(int S) { return (size_t)(((S + 3) & ~3) * RT + S) * sizeof(float2); }
 
-hipError_t launch_dft_pass(const float2* in, float2* out, int S, int64_t js, int64_t os, int64_t ks,
-                          int64_t os2, int n_outer, int W2, const float2* tws, hipStream_t s) {
-  if (n_outer <= 0 || W2 <= 0) return hipSuccess;
-  const size_t lds = probe_lds_bytes(S);
-  hipError_t e = hipFuncSetAttribute((const void*)k_dft_pass,
+hipError_t launch_dft_adjoint(bool along_y, const AdjAtom* atoms, int n, int max_w2, const float2* in, int64_t in_stride,
+                              float2* out, int64_t out_stride, int Sy, int Sx, const float2* tws, hipStream_t s) {
+  if (n <= 0 || max_w2 <= 0) return hipSuccess;
+  const size_t lds = probe_lds_bytes(along_y ? Sy : Sx);
+  hipError_t e = hipFuncSetAttribute((const void*)k_dft_adjoint,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_dft_pass, dim3((W2 + RT - 1) / RT, n_outer), dim3(NT), lds, s, in, out, S,
-                     js, os, ks, os2, W2, tws);
+  hipLaunchKernelGGL(k_dft_adjoint, dim3((max_w2 + RT - 1) / RT, along_y ? Sx : Sy, n), dim3(NT), lds, s, along_y ? 1 : 0,
+                     atoms, in, in_stride, out, out_stride, Sy, Sx, tws);
   return hipGetLastError();
 }
 

@@ -62,9 +62,19 @@ __global__ void k_recon_plain(ReconArgs a, float2* out) {
 // or the window are written as zeros.
 constexpr int TB = TILE_B, TR = 32;
 
+// scale s conj(w) (sign > 0) or scale s w.  The rounding is spelled out: the
+// compiler may contract these products either way, and the operand is to have
+// the same bits in each kernel that writes it.
+__device__ inline float2 retilt(float2 s, float2 w, int sign, float scale) {
+  const float q = s.y * w.y;
+  const float2 v = make_float2(fmaf(s.x, w.x, sign > 0 ? q : -q), fmaf(sign > 0 ? -s.x : s.x, w.y, s.y * w.x));
+  return cscale(v, scale);
+}
+
+// One beam tile bt over pixel tiles rt_lo .. rt_hi - 1 (a holds the window).
 template <int PREC, int KIND>
-__global__ __launch_bounds__(256) void k_recon_operand(ReconArgs a, void* out, int64_t ld,
-                                                       int nrows, int ncols, int64_t plane, int rpw) {
+__device__ inline void recon_operand_run(const ReconArgs& a, void* out, int64_t ld, int nrows, int ncols, int64_t plane,
+                                         int bt, int rt_lo, int rt_hi) {
   __shared__ float2 tile[TB][TR + 1];
   __shared__ float2 sP[TILE_NP][TR];  // the tile's parent windows on the current 32 pixels
   __shared__ float sM[TILE_NP][TR];   // and their magnitudes
@@ -75,17 +85,6 @@ __global__ __launch_bounds__(256) void k_recon_operand(ReconArgs a, void* out, i
   constexpr int NPF = TILE_NP * TR / 256;  // slab elements per thread
   const int n_b = KIND == 0 ? ncols : nrows;  // beams to write (padded)
   const int n_r = KIND == 0 ? nrows : ncols;  // pixels to write (padded)
-  const int nbt = (n_b + TB - 1) / TB, nrt = (n_r + TR - 1) / TR;
-  // one workgroup per beam tile and run of rpw pixel tiles.  Workgroup i runs
-  // on XCD i mod 8: each XCD takes a contiguous range of (run, beam tile)
-  // pairs, neighbouring beam tiles on the same pixels, so that the parents
-  // they share stay in its L2
-  const int nch = (nrt + rpw - 1) / rpw;
-  const int per = (int)(gridDim.x / 8);
-  const int lin = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
-  if (lin >= nbt * nch) return;
-  const int bt = lin % nbt, ch = lin / nbt;
-  const int rt_lo = ch * rpw, rt_hi = min(nrt, rt_lo + rpw);
   const int b0 = bt * TB;
   const int W2 = a.W * a.W;
   // the tile's distinct parents are staged in LDS when they fit (always, for
@@ -166,7 +165,7 @@ __global__ __launch_bounds__(256) void k_recon_operand(ReconArgs a, void* out, i
         recon_tail(z, m, a.win, W2, rr, s_ec[bl], a.col, a.w);
         const float2 sv = a.mode == BIP_RECON_MAGNITUDE ? mag_rescale(z, m) : z;
         float2 v = make_float2(0.f, 0.f);
-        if (b0 + bl < a.nb && live) v = cscale(a.retilt_sign > 0 ? cmulc(sv, tw) : cmul(sv, tw), a.scale);
+        if (b0 + bl < a.nb && live) v = retilt(sv, tw, a.retilt_sign, a.scale);
         tile[bl][px32] = v;
       }
     } else {
@@ -184,7 +183,7 @@ __global__ __launch_bounds__(256) void k_recon_operand(ReconArgs a, void* out, i
           const float2 tw = s_tw[(h.x * py + h.y * px) & (a.L - 1)];
           const float2 sv = recon_finish(D[i], a.win, W2, rr, s_ec[bl], s_ew[bl], a.col, a.w, a.mode);
           float2 v = make_float2(0.f, 0.f);
-          if (b0 + bl < a.nb && live) v = cscale(a.retilt_sign > 0 ? cmulc(sv, tw) : cmul(sv, tw), a.scale);
+          if (b0 + bl < a.nb && live) v = retilt(sv, tw, a.retilt_sign, a.scale);
           tile[bl][px32] = v;
         }
       }
@@ -218,6 +217,44 @@ __global__ __launch_bounds__(256) void k_recon_operand(ReconArgs a, void* out, i
     }
     __syncthreads();  // tile read out, next slab visible
   }
+}
+
+// One atom: a workgroup per beam tile and run of rpw pixel tiles.  Workgroup i
+// runs on XCD i mod 8: each XCD takes a contiguous range of (run, beam tile)
+// pairs, neighbouring beam tiles on the same pixels, so that the parents they
+// share stay in its L2.
+template <int PREC, int KIND>
+__global__ __launch_bounds__(256) void k_recon_operand(ReconArgs a, void* out, int64_t ld,
+                                                       int nrows, int ncols, int64_t plane, int rpw) {
+  const int n_b = KIND == 0 ? ncols : nrows, n_r = KIND == 0 ? nrows : ncols;
+  const int nbt = (n_b + TB - 1) / TB, nrt = (n_r + TR - 1) / TR;
+  const int nch = (nrt + rpw - 1) / rpw;
+  const int per = (int)(gridDim.x / 8);
+  const int lin = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
+  if (lin >= nbt * nch) return;
+  const int bt = lin % nbt, ch = lin / nbt;
+  recon_operand_run<PREC, KIND>(a, out, ld, nrows, ncols, plane, bt, ch * rpw, min(nrt, ch * rpw + rpw));
+}
+
+// Kind 1 operands of several atoms: as k_recon_kblk_atoms (the pitch is n_r).
+template <int PREC>
+__global__ __launch_bounds__(256) void k_recon_rows_atoms(ReconArgs a, const ReconAtom* __restrict__ atoms, int n_atoms,
+                                                          char* out, int nrows, int64_t plane, int nch, int rpw) {
+  const int nbt = (nrows + TB - 1) / TB;
+  const int per = (int)(gridDim.x / 8);
+  const int lin = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
+  if (lin >= nbt * nch * n_atoms) return;
+  const int bt = lin % nbt, run = lin / nbt, ch = run % nch;
+  const ReconAtom at = atoms[run / nch];
+  const int nrt = (at.n_r + TR - 1) / TR;
+  if (ch * rpw >= nrt) return;  // a smaller window than the launch's largest: uniform per workgroup
+  a.win += at.win_off;
+  a.W = at.W;
+  a.oy = at.oy;
+  a.ox = at.ox;
+  constexpr int ES = PREC == BIP_PREC_FP32 ? 4 : 2;
+  recon_operand_run<PREC, 1>(a, out + at.out_off * ES, at.n_r, nrows, at.n_r, plane, bt, ch * rpw,
+                             min(nrt, ch * rpw + rpw));
 }
 
 // K-blocked GEMM operand (kind 0) when every 64-beam tile has at most
@@ -434,6 +471,30 @@ hipError_t launch_recon_kblk_atoms(const ReconArgs& a, const ReconAtom* atoms, i
   RA(BIP_PREC_BF16)
   RA(BIP_PREC_FP16)
 #undef RA
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_recon_rows_atoms(const ReconArgs& a, const ReconAtom* atoms, int n_atoms, void* out, int prec,
+                                   int64_t nrows_pad, int64_t plane_stride, int max_nr, hipStream_t s) {
+  if (n_atoms <= 0 || nrows_pad <= 0) return hipSuccess;
+  if (nrows_pad > INT32_MAX) return hipErrorInvalidValue;
+  // runs of pixel tiles as in launch_recon_kblk_atoms
+  const int64_t nbt = (nrows_pad + TB - 1) / TB, nrt = (max_nr + TR - 1) / TR;
+  const int64_t want = std::max<int64_t>(1, std::min<int64_t>(nrt, (2048 + nbt * n_atoms - 1) / (nbt * n_atoms)));
+  const int64_t rpw = (nrt + want - 1) / want, nch = (nrt + rpw - 1) / rpw;
+  const int64_t nblk = (nbt * nch * n_atoms + 7) / 8 * 8;
+  if (nblk > INT32_MAX) return hipErrorInvalidValue;
+#define RR(P)                                                                                                        \
+  if (prec == P) {                                                                                                   \
+    hipLaunchKernelGGL((k_recon_rows_atoms<P>), dim3((unsigned)nblk), dim3(256), a.L * sizeof(float2), s, a, atoms,  \
+                       n_atoms, (char*)out, (int)nrows_pad, plane_stride, (int)nch, (int)rpw);                       \
+    return hipGetLastError();                                                                                        \
+  }
+  RR(BIP_PREC_FP32)
+  RR(BIP_PREC_SPLIT_BF16)
+  RR(BIP_PREC_BF16)
+  RR(BIP_PREC_FP16)
+#undef RR
   return hipErrorInvalidValue;
 }
 
