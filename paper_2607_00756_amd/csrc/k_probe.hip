@@ -25,6 +25,8 @@
 //   contraction operand psi^T[rho][r] (map) or as U_n = H_n psi (detector
 //   contraction), in the planes of the requested precision.
 // Both DFTs run on the FP32 matrix cores with twiddles rounded from FP64.
+#include <type_traits>
+
 #include "bip_internal.h"
 #include "planes.h"
 #include "recon_core.h"
@@ -89,6 +91,20 @@ __device__ inline void dft_mfma(const float2* sF, const float2* sT, int S, int o
 
 constexpr int FOLD_CH = 64;  // residue cells of the fold held in LDS at a time
 
+// The table rows of a beam of the fold (wave-uniform).
+struct FoldBeam {
+  int2 h;
+  int ec[ELL_W];
+  float ew[ELL_K];
+};
+__device__ inline void fold_beam(FoldBeam& q, const ProbeArgs& pa, int b) {
+  q.h = pa.beams[b];
+#pragma unroll
+  for (int j = 0; j < ELL_W; ++j) q.ec[j] = pa.ellc[(int64_t)b * ELL_W + j];
+#pragma unroll
+  for (int j = 0; j < ELL_K; ++j) q.ew[j] = pa.ellw[(int64_t)b * ELL_W + j];
+}
+
 // 1-D grid.  Workgroups are dispatched to the 8 XCDs in turn, so blocks x,
 // x + 8, x + 16, ... share XCD x: its slot s takes residue row s mod n_y of
 // pixel tile unit0 + 8 (s / n_y) + x, and the n_y rows of a tile run together
@@ -97,12 +113,18 @@ constexpr int FOLD_CH = 64;  // residue cells of the fold held in LDS at a time
 // The residue cells are folded FOLD_CH at a time into LDS, and each chunk's
 // share of the DFT over x is added to the NV = ceil(columns / 64) output blocks
 // held in registers (the products run in the same K order as one pass).
+// A wave's beam needs its table rows before its parent values, and these before
+// the sum: with each loaded when needed, three trips to L2 a beam, a map of 112
+// windows of 24 x 24 with 8.1k beams and a 64 x 64 raster took 3.3 ms, 12 windows
+// of 24 to 64 with a 128 x 128 raster 8.0, 24 of 64 x 64 with hex parents 4.9;
+// with both loaded ahead 2.6, 7.2 and 4.1 (the DFT's matrix products alone are
+// 0.9, and the 50 vector instructions a beam and 64 pixels 0.7, of the first).
 // Residue row i of the workspace is row i g_y of the grid.  (256 x 256, 112
 // atoms, 64 x 64 scans, f = 4: the fold takes 0.21 ms and the DFT over y 0.09,
 // against 2.48 and 1.67 with every residue and every scan, of which 15 of 16 are
 // zero or outside the masks.)
 template <int NV>
-__global__ __launch_bounds__(NT) void k_probe_fold_x(const ProbeArgs pa) {
+__global__ __launch_bounds__(NT, NV <= 2 ? 4 : NV == 3 ? 3 : 2) void k_probe_fold_x(const ProbeArgs pa) {
   extern __shared__ float2 sm[];
   const int Sx = pa.Sx, nc = Sx / pa.gx, nr = pa.Sy / pa.gy;  // residue columns and rows in use
   const int CH = min((nc + 3) & ~3, FOLD_CH);
@@ -155,30 +177,66 @@ __global__ __launch_bounds__(NT) void k_probe_fold_x(const ProbeArgs pa) {
   for (int cc = 0; cc < nc; cc += CH) {
     const int ce = min(nc, cc + CH);
     const int cp = cc + ((ce - cc + 3) & ~3);  // the chunk's K rows, zero beyond ce
-    for (int c = cc + wave; c < ce; c += 4) {
-      const int cell = a * Sx + c * pa.gx;
-      const int k1 = pa.cell_start[cell + 1];
-      float2 F = make_float2(0.f, 0.f);
-      for (int k = pa.cell_start[cell]; k < k1; ++k) {
-        const int b = pa.cell_beams[k];
-        const int2 h = pa.beams[b];
-        const float2 t = sW[(h.x * py + h.y * px) & (pa.L - 1)];  // exp(-2 pi i h.r/N)
-        const int32_t* ec = pa.ellc + (int64_t)b * ELL_W;
-        const float* ew = pa.ellw + (int64_t)b * ELL_W;
-        float2 D[ELL_K];
-        if (rsrc_ok) {
+    // The chunk's beams are consecutive in cell_beams (cells between two
+    // multiples of g_x hold none).  Lane i keeps the end of cell cc + i; each
+    // wave takes the cells that end within its quarter of the beams.
+    const int nce = ce - cc, cell0 = a * Sx + cc * pa.gx;
+    const int ends = lane < nce ? pa.cell_start[cell0 + lane * pa.gx + 1] : INT32_MAX;
+    const int kb = pa.cell_start[cell0], nk = __builtin_amdgcn_readlane(ends, nce - 1) - kb;
+    auto cells_to = [&](int w) { return w >= 4 ? nce : w <= 0 ? 0 : (int)__popcll(__ballot(ends <= kb + nk * w / 4)); };
+    auto end_of = [&](int c) { return c < 0 ? kb : __builtin_amdgcn_readlane(ends, c); };
+    int c = cells_to(wave);
+    const int c1 = cells_to(wave + 1);
+    int k = end_of(c - 1);
+    const int kl = end_of(c1 - 1);
+    float2 F = make_float2(0.f, 0.f);
+    auto store = [&] {  // cell c is complete
+      sF[c * RT + lane] = live ? F : make_float2(0.f, 0.f);
+      F = make_float2(0.f, 0.f);
+      ++c;
+    };
+    // The table rows are loaded two beams ahead of their use and the parent
+    // values one ahead (past the last beam, the last one's again), into D0 and
+    // D1 in turn.
+    auto beams = [&](auto buffered) {
+      if (k >= kl) return;
+      auto fetch = [&](const FoldBeam& q, float2 (&D)[ELL_K]) {
+        if constexpr (decltype(buffered)::value) {
 #pragma unroll
           for (int j = 0; j < ELL_K; ++j)
             D[j] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(
-                                                  rwin, voff, ec[j] * W2 * (int)sizeof(float2), 0));
+                                                  rwin, voff, q.ec[j] * W2 * (int)sizeof(float2), 0));
         } else {
-          recon_load(win, W2, rr, ec, D);
+          recon_load(win, W2, rr, q.ec, D);
         }
-        const float2 sv = recon_finish(D, win, W2, rr, ec, ew, pa.col, pa.w, pa.mode);
+      };
+      FoldBeam n1, n2;
+      float2 D0[ELL_K], D1[ELL_K];
+      fold_beam(n1, pa, pa.cell_beams[k]);
+      fold_beam(n2, pa, pa.cell_beams[min(k + 1, kl - 1)]);
+      int b3 = pa.cell_beams[min(k + 2, kl - 1)];  // the beam after n2
+      fetch(n1, D0);
+      auto step = [&](const float2 (&D)[ELL_K], float2 (&nD)[ELL_K]) {
+        while (k == end_of(c)) store();
+        const FoldBeam q = n1;
+        n1 = n2;
+        fetch(n1, nD);
+        fold_beam(n2, pa, b3);
+        b3 = pa.cell_beams[min(k + 3, kl - 1)];
+        const float2 t = sW[(q.h.x * py + q.h.y * px) & (pa.L - 1)];  // exp(-2 pi i h.r/N)
+        const float2 sv = recon_finish(D, win, W2, rr, q.ec, q.ew, pa.col, pa.w, pa.mode);
         F = cadd(F, cmulc(sv, t));  // re-tilt by exp(+2 pi i h.r/N)
+        ++k;
+      };
+      while (k + 1 < kl) {
+        step(D0, D1);
+        step(D1, D0);
       }
-      sF[(c - cc) * RT + lane] = live ? F : make_float2(0.f, 0.f);
-    }
+      if (k < kl) step(D0, D1);
+    };
+    if (rsrc_ok) beams(std::true_type{});
+    else beams(std::false_type{});
+    while (c < c1) store();
     for (int c = ce + wave; c < cp; c += 4) sF[(c - cc) * RT + lane] = make_float2(0.f, 0.f);
     __syncthreads();
 #pragma unroll
