@@ -669,8 +669,10 @@ int bip_build_smatrix(bip_plan* p, const float* V, void* stream) {
   const int batch = column_batch(G);
   p->column_batch = batch;
   // ---- S1: entrance -> deepest ionization plane
-  HIPCHK(timed(p, ST_INIT, st, [&] { return launch_init_planewaves(p->d_state1, p->d_par1, p->Bp1, g.ny, g.nx, p->d_tw, p->L, +1, 1.0f, st); }),
-         "init S1");
+  const bool start = !fixed_order(p);  // the first row pass makes the plane waves (ROW_START)
+  if (!start)
+    HIPCHK(timed(p, ST_INIT, st, [&] { return launch_init_planewaves(p->d_state1, p->d_par1, p->Bp1, g.ny, g.nx, p->d_tw, p->L, +1, 1.0f, st); }),
+           "init S1");
   GatherArgs g1 = gather_args(p, 1);
   const int batch1 = balanced_batch(p->Bp1, batch);
   for (int c0 = 0; c0 < p->Bp1; c0 += batch1) {
@@ -679,6 +681,7 @@ int bip_build_smatrix(bip_plan* p, const float* V, void* stream) {
     for (int j = 0; j <= p->i_max; ++j) {
       int flags = ROW_GATHER_BEFORE_T;
       if (j > 0) flags |= ROW_INV;
+      else if (start) flags |= ROW_START;
       if (j < p->i_max) flags |= ROW_T | ROW_FWD;
       float2* save = nullptr;
       if (p->d_ckpt1 && j < p->i_max && j % p->o.ckpt_stride == 0) {
@@ -686,7 +689,7 @@ int bip_build_smatrix(bip_plan* p, const float* V, void* stream) {
         save = p->d_ckpt1 + ((int64_t)(j / p->o.ckpt_stride) * p->Bp1 + c0) * G;
       }
       HIPCHK(timed(p, ST_S1_ROW, st, [&] { return launch_row_pass(flags, s1, nc, g.ny, g.nx, p->d_T + j * G, p->d_tw, p->L,
-                             p->d_par1, +1, g1, p->plane_start[j], p->plane_start[j + 1], c0, save, st); }),
+                             p->d_par1, +1, g1, p->plane_start[j], p->plane_start[j + 1], c0, save, RowStart{}, st); }),
              "S1 row pass");
       if (j < p->i_max)
         HIPCHK(timed(p, ST_S1_COL, st, [&] { return launch_col_pass(s1, nc, g.ny, g.nx, p->d_prop, p->d_tw, p->L, st); }),
@@ -721,8 +724,11 @@ int bip::sweep_s2(bip_plan* p, int j_hi, int j_lo, bool init, hipStream_t st) {
   const int batch = column_batch(G);
   p->column_batch = batch;
   const int batch2 = balanced_batch(p->Bp2, batch);
-  // The parents start row-transformed, the form the state keeps between passes.
-  if (init)
+  // The parents start propagated by the first row pass (ROW_START), or row-transformed, the form the
+  // state keeps between passes.
+  const bool start = init && !fixed_order(p);
+  const RowStart rs{p->d_prop, (float)(std::sqrt((double)G))};
+  if (init && !start)
     HIPCHK(timed(p, ST_INIT, st, [&] { return launch_init_planewaves_rowft(p->d_state2, p->d_par2, p->Bp2, g.ny, g.nx, p->d_tw,
                                   p->L, (float)(1.0 / std::sqrt((double)G)), st); }),
            "init S2");
@@ -731,9 +737,11 @@ int bip::sweep_s2(bip_plan* p, int j_hi, int j_lo, bool init, hipStream_t st) {
     const int nc = std::min(batch2, p->Bp2 - c0);
     float2* s2 = p->d_state2 + (int64_t)c0 * G;
     for (int j = j_hi; j >= j_lo; --j) {
-      HIPCHK(timed(p, ST_S2_COL, st, [&] { return launch_col_pass(s2, nc, g.ny, g.nx, p->d_prop, p->d_tw, p->L, st); }),
-             "S2 column pass");
-      int flags = ROW_INV | ROW_T | ROW_GATHER_AFTER_T;
+      const bool first = start && j == j_hi;
+      if (!first)
+        HIPCHK(timed(p, ST_S2_COL, st, [&] { return launch_col_pass(s2, nc, g.ny, g.nx, p->d_prop, p->d_tw, p->L, st); }),
+               "S2 column pass");
+      int flags = (first ? ROW_START : ROW_INV) | ROW_T | ROW_GATHER_AFTER_T;
       if (j > p->i_min) flags |= ROW_FWD;  // keep the state row-transformed until the last plane
       float2* save = nullptr;
       if (p->d_ckpt2 && (g.nz - 1 - j) % p->o.ckpt_stride == 0) {
@@ -741,7 +749,7 @@ int bip::sweep_s2(bip_plan* p, int j_hi, int j_lo, bool init, hipStream_t st) {
         save = p->d_ckpt2 + ((int64_t)((g.nz - 1 - j) / p->o.ckpt_stride) * p->Bp2 + c0) * G;
       }
       HIPCHK(timed(p, ST_S2_ROW, st, [&] { return launch_row_pass(flags, s2, nc, g.ny, g.nx, p->d_T + j * G, p->d_tw, p->L,
-                             p->d_par2, -1, g2, p->plane_start[j], p->plane_start[j + 1], c0, save, st); }),
+                             p->d_par2, -1, g2, p->plane_start[j], p->plane_start[j + 1], c0, save, rs, st); }),
              "S2 row pass");
     }
   }

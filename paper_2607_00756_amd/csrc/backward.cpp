@@ -461,13 +461,13 @@ int bip_eels_backward(bip_plan* p, int32_t n_ch, const float* H, const int64_t* 
     HIPCHK(hipMemcpyAsync(rec, ck, (size_t)nc * G * 8, hipMemcpyDeviceToDevice, st), "segment copy");
     GatherArgs none{nullptr, nullptr};
     HIPCHK(launch_row_pass(ROW_FWD, rec, nc, g.ny, g.nx, nullptr, p->d_tw, p->L, par, 0, none, 0, 0, 0,
-                           nullptr, st),
+                           nullptr, RowStart{}, st),
            "segment row transform");
     for (int r = 0; r < n_more; ++r) {
       const int j = slice_of(r);
       HIPCHK(launch_col_pass(rec, nc, g.ny, g.nx, p->d_prop, p->d_tw, p->L, st), "segment column pass");
       HIPCHK(launch_row_pass(ROW_INV | ROW_T | ROW_FWD | ROW_SAVE, rec, nc, g.ny, g.nx, p->d_T + j * G,
-                             p->d_tw, p->L, par, 0, none, 0, 0, 0, seg_slot(r), st),
+                             p->d_tw, p->L, par, 0, none, 0, 0, 0, seg_slot(r), RowStart{}, st),
              "segment row pass");
     }
     return BIP_OK;

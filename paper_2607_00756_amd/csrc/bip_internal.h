@@ -305,13 +305,20 @@ hipError_t launch_sibson_general(const int2* query, int nq, const int2* parents,
 // multislice (k_multislice.hip)
 enum RowFlags {
   ROW_INV = 1, ROW_T = 2, ROW_FWD = 4, ROW_GATHER_BEFORE_T = 8, ROW_GATHER_AFTER_T = 16,
-  ROW_SAVE = 32  // write the state after T_j to `save` (slice checkpoint, [ncols][ny][nx])
+  ROW_SAVE = 32,  // write the state after T_j to `save` (slice checkpoint, [ncols][ny][nx])
+  ROW_START = 64  // start from the parents' plane waves instead of reading the state (RowStart)
+};
+// The real-space wave a sweep starts its first row pass with: exp(2 pi i h.r/N) (S1, prop null), or
+// scale P(-h) exp(-2 pi i h.r/N) (S2: the exit wave after its first propagation, prop as the column passes take it).
+struct RowStart {
+  const float2* prop = nullptr;
+  float scale = 1.f;
 };
 // state (and save) point at the first column of the batch; col0 is that column's parent index
 hipError_t launch_row_pass(int flags, float2* state, int ncols, int ny, int nx, const float2* T,
                            const float2* tw, int L, const int2* parents, int detilt_sign,
                            const GatherArgs& ga, int gather_begin, int gather_end, int col0,
-                           float2* save, hipStream_t s);
+                           float2* save, const RowStart& start, hipStream_t s);
 // adjoint sweeps (the cotangent state replaces the forward state)
 enum AdjFlags {
   ADJ_ZERO = 1, ADJ_INV = 2, ADJ_INJ_BEFORE = 4, ADJ_DV = 8, ADJ_CONJT = 16, ADJ_INJ_AFTER = 32,
