@@ -621,11 +621,17 @@ int bip_plan_create(const bip_grid* grid, const bip_optics* optics, int32_t n_at
       (rc = upload(p, &p->d_ox, p->ox, st)) || (rc = upload(p, &p->d_off1, p->off1, st)) ||
       (rc = upload(p, &p->d_off2, p->off2, st)) ||
       (rc = upload(p, &p->d_grec1, grec1, st)) || (rc = upload(p, &p->d_grec2, grec2, st)) ||
-      (rc = dalloc(p, &p->d_state1, (size_t)p->Bp1 * G, st)) ||
-      (rc = dalloc(p, &p->d_state2, (size_t)p->Bp2 * G, st)) ||
       (rc = dalloc(p, &p->d_win1, (size_t)p->win1_elems, st)) ||
       (rc = dalloc(p, &p->d_win2, (size_t)p->win2_elems, st)))
     return fail(rc);
+  // small grids sweep in one launch, unless the state is wanted between slices
+  p->one_sweep = small_grid(g.ny, g.nx) && !fixed_order(p) && !p->s2_stream;
+  if (p->one_sweep) {
+    if ((rc = upload(p, &p->d_planes, p->plane_start, st))) return fail(rc);
+  } else if ((rc = dalloc(p, &p->d_state1, (size_t)p->Bp1 * G, st)) ||
+             (rc = dalloc(p, &p->d_state2, (size_t)p->Bp2 * G, st))) {
+    return fail(rc);
+  }
   std::vector<FocalAtom> fatoms;
   if (p->focal) {
     for (int a = 0; a < n_atoms; ++a)
@@ -656,18 +662,10 @@ int bip_plan_create(const bip_grid* grid, const bip_optics* optics, int32_t n_at
   return BIP_OK;
 }
 
-int bip_build_smatrix(bip_plan* p, const float* V, void* stream) {
-  if (!p || !V) return err(BIP_EINVAL, "NULL argument");
-  hipStream_t st = (hipStream_t)stream;
-  p->stream = st;
+static int sweep_s1(bip_plan* p, hipStream_t st) {
   const bip_grid& g = p->g;
   const int64_t G = (int64_t)g.ny * g.nx;
-  HIPCHK(timed(p, ST_TRANSMIT, st, [&] { return launch_transmit(p->d_T, V, G * g.nz, (float)p->sigma, st); }), "transmit");
-  // Columns are advanced in batches, every slice of a batch before the next
-  // batch, so that a batch (both passes of every slice) can stay resident in
-  // the last-level cache; a batch of all columns is the plain slice-major sweep.
-  const int batch = column_batch(G);
-  p->column_batch = batch;
+  const int batch = p->column_batch;
   // ---- S1: entrance -> deepest ionization plane
   const bool start = !fixed_order(p);  // the first row pass makes the plane waves (ROW_START)
   if (!start)
@@ -696,6 +694,36 @@ int bip_build_smatrix(bip_plan* p, const float* V, void* stream) {
                "S1 column pass");
     }
   }
+  return BIP_OK;
+}
+
+int bip_build_smatrix(bip_plan* p, const float* V, void* stream) {
+  if (!p || !V) return err(BIP_EINVAL, "NULL argument");
+  hipStream_t st = (hipStream_t)stream;
+  p->stream = st;
+  const bip_grid& g = p->g;
+  const int64_t G = (int64_t)g.ny * g.nx;
+  HIPCHK(timed(p, ST_TRANSMIT, st, [&] { return launch_transmit(p->d_T, V, G * g.nz, (float)p->sigma, st); }), "transmit");
+  // Columns are advanced in batches, every slice of a batch before the next
+  // batch, so that a batch (both passes of every slice) can stay resident in
+  // the last-level cache; a batch of all columns is the plain slice-major sweep.
+  const int batch = column_batch(G);
+  p->column_batch = batch;
+  if (p->one_sweep) {
+    SweepArgs sw{};
+    sw.side[0] = SweepSide{p->d_par1, gather_args(p, 1), p->Bp1, 0, p->i_max};
+    sw.side[1] = SweepSide{p->d_par2, gather_args(p, 2), p->Bp2, g.nz - 1, p->i_min};
+    sw.T = p->d_T;
+    sw.prop = p->d_prop;
+    sw.tw = p->d_tw;
+    sw.planes = p->d_planes;
+    sw.L = p->L;
+    sw.scale2 = (float)std::sqrt((double)G);
+    HIPCHK(timed(p, ST_S2_ROW, st, [&] { return launch_sweep(sw, g.ny, g.nx, st); }), "sweeps");
+  } else {
+    int rc = sweep_s1(p, st);
+    if (rc) return rc;
+  }
   // ---- focal back-propagation of the S1 windows to each atom's centroid plane
   if (p->focal) {
     HIPCHK(launch_focal_dist(V, p->d_fatoms, p->n_atoms, g.ny, g.nx, g.dz, p->d_fdist, st), "focal distance");
@@ -708,7 +736,7 @@ int bip_build_smatrix(bip_plan* p, const float* V, void* stream) {
   }
   // ---- S2: exit -> shallowest ionization plane (transpose multislice);
   // streamed plans sweep S2 inside bip_eels_signal, segment by segment
-  if (!p->s2_stream) {
+  if (!p->s2_stream && !p->one_sweep) {
     int rc = sweep_s2(p, g.nz - 1, p->i_min, true, st);
     if (rc) return rc;
   }

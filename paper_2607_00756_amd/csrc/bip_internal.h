@@ -212,6 +212,8 @@ struct bip_plan {
   std::vector<bip::ProbeJob> h_fjobs;
   int64_t *d_off1 = nullptr, *d_off2 = nullptr;
   bip::GatherRec *d_grec1 = nullptr, *d_grec2 = nullptr;  // gather records in plane order
+  bool one_sweep = false;       // both sweeps in one launch, no state in memory (launch_sweep)
+  int32_t* d_planes = nullptr;  // plane_start, for that launch
   float2* d_state1 = nullptr;   // [Bp1][G]
   float2* d_state2 = nullptr;   // [Bp2][G]
   float2* d_win1 = nullptr;     // window stacks
@@ -319,6 +321,22 @@ hipError_t launch_row_pass(int flags, float2* state, int ncols, int ny, int nx, 
                            const float2* tw, int L, const int2* parents, int detilt_sign,
                            const GatherArgs& ga, int gather_begin, int gather_end, int col0,
                            float2* save, const RowStart& start, hipStream_t s);
+// Both sweeps of a small grid in one launch (small_grid); side 0: S1, 1: S2.
+struct SweepSide {
+  const int2* parents;
+  GatherArgs ga;
+  int n;       // columns
+  int j0, j1;  // first and last slice (S1: up to the deepest plane, S2: down to the shallowest)
+};
+struct SweepArgs {
+  SweepSide side[2];
+  const float2 *T, *prop, *tw;
+  const int32_t* planes;  // [nz + 1] first gather record of each plane
+  int L;
+  float scale2;  // of the S2 start (RowStart)
+};
+inline bool small_grid(int ny, int nx) { return ny <= 128 && nx <= 128; }
+hipError_t launch_sweep(const SweepArgs& a, int ny, int nx, hipStream_t s);
 // adjoint sweeps (the cotangent state replaces the forward state)
 enum AdjFlags {
   ADJ_ZERO = 1, ADJ_INV = 2, ADJ_INJ_BEFORE = 4, ADJ_DV = 8, ADJ_CONJT = 16, ADJ_INJ_AFTER = 32,

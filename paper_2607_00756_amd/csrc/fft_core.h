@@ -149,17 +149,17 @@ __device__ inline void exchange_sync() {
   }
 }
 
-// Twiddles of the second (radix-16) stage, laid out as it reads them:
-// w[(j - 1) 16 + k] = exp(-2 pi i j k / 256), k = 0 .. 15.  Lanes read
-// consecutive k; in the exp(-2 pi i m / L) table they are j (L = 256), 2 j
-// (512) or 4 j (1024) entries apart, up to 8 lanes a bank.
+// Twiddles of the second stage (radix R, after the first one's 16), laid out as
+// it reads them: w[(j - 1) 16 + k] = exp(-2 pi i j k / (16 R)), k = 0 .. 15.
+// Lanes read consecutive k; in the exp(-2 pi i m / L) table they are j (L = 16
+// R) and more entries apart, up to 8 lanes a bank.
 constexpr int TW16 = 15 * 16;
-__device__ inline void fill_tw16(float2* w, const float2* __restrict__ twg, int L, int tid, int nthreads) {
-  for (int i = tid; i < TW16; i += nthreads) w[i] = twg[(i / 16 + 1) * (i % 16) * (L / 256)];
+__device__ inline void fill_tw16(float2* w, const float2* __restrict__ twg, int L, int tid, int nthreads, int R = 16) {
+  for (int i = tid; i < (R - 1) * 16; i += nthreads) w[i] = twg[(i / 16 + 1) * (i % 16) * (L / (16 * R))];
 }
 
 // One Stockham stage.  v: strided-layout registers.  tw: exp(-2 pi i m/L)
-// table, twstep = L / N; TAB: the second (16 x 16) stage reads tw16 instead.
+// table, twstep = L / N; TAB: the second stage reads tw16 instead.
 template <int N, int R, int P, bool LAST, bool INV, int STRIDE, bool PAD, bool WAVE, bool TAB>
 __device__ inline void stage(float2 (&v)[16], float2* lds, int t, const float2* __restrict__ tw,
                              int twstep, const float2* __restrict__ tw16) {
@@ -175,7 +175,7 @@ __device__ inline void stage(float2 (&v)[16], float2* lds, int t, const float2* 
     if (P > 1) {
 #pragma unroll
       for (int j = 1; j < R; ++j) {
-        const float2 w = TAB && P == 16 && R == 16 ? tw16[(j - 1) * 16 + k] : tw[(j * k * (N / (P * R))) * twstep];
+        const float2 w = TAB && P == 16 ? tw16[(j - 1) * 16 + k] : tw[(j * k * (N / (P * R))) * twstep];
         u[j] = INV ? cmulc(u[j], w) : cmul(u[j], w);
       }
     }

@@ -322,6 +322,106 @@ __global__ __launch_bounds__(ColShape<NY>::THREADS, ColShape<NY>::THREADS > 256 
   }
 }
 
+// Whole sweeps of small grids (sides of 64 or 128): one workgroup advances one
+// parent column of either side through all its slices, 16 elements of the state
+// per thread, the exchanges and transposes through LDS (one padded row or column
+// of the buffer per row or column of the grid), the windows cropped on the way.
+//   Only T_j, P and the windows are read or written, from L2, so a slice of a column
+// is bound by the instructions of its four transforms: at 128 x 128 some 1700 a
+// wave, 16 waves a CU, 10 us (14 with every CU busy).  The passes keep the state in
+// memory and are two launches a slice: over 10 slices, the sweeps' kernels took 231
+// us for the parents of a map (every fourth beam either way) and 1600 us with every
+// detector beam in passes, 98 and 1140 us here.
+//   Lane pairs four rows apart would share banks where a transpose reads 128 x
+// 128; swz moves every other group of four rows by four elements.
+template <int NY, int NX>
+struct SweepShape {
+  static constexpr int THREADS = NY * NX / 16, TX = NX / 16, TY = NY / 16;
+  static constexpr int PR = NX + TX, PC = NY + TY;  // LDS elements of a row, of a column
+  static constexpr int BUF = NY * PR > NX * PC ? NY * PR : NX * PC;
+  static constexpr int RX = NX / 16, RY = NY / 16;  // radix of the second stage
+  static __device__ int swz(int y, int x) { return NY == 128 && NX == 128 ? x ^ (y & 4) : x; }
+};
+
+template <int NY, int NX>
+__global__ __launch_bounds__(NY * NX / 16) void k_sweep(const SweepArgs a) {
+  using S = SweepShape<NY, NX>;
+  extern __shared__ float2 buf[];
+  float2* tw = buf + S::BUF;  // [L]
+  float2* tabx = tw + a.L;
+  float2* taby = tabx + (S::RX - 1) * 16;
+  for (int i = threadIdx.x; i < a.L; i += S::THREADS) tw[i] = a.tw[i];
+  fft::fill_tw16(tabx, a.tw, a.L, threadIdx.x, S::THREADS, S::RX);
+  fft::fill_tw16(taby, a.tw, a.L, threadIdx.x, S::THREADS, S::RY);
+  __syncthreads();
+  const bool s2 = (int)blockIdx.x < a.side[1].n;
+  const SweepSide& sd = a.side[s2 ? 1 : 0];
+  const int col = s2 ? blockIdx.x : blockIdx.x - a.side[1].n;
+  const int2 hp = sd.parents[col];
+  // row layout: elements (y, t + TX e); column layout: (tc + TY e, x)
+  const int t = threadIdx.x % S::TX, y = threadIdx.x / S::TX;
+  const int tc = threadIdx.x % S::TY, x = threadIdx.x / S::TY;
+  float2* rbuf = buf + y * S::PR;
+  float2* cbuf = buf + x * S::PC;
+  float2 v[16];
+  float2 c = make_float2(1.f, 0.f);  // the first row pass starts as in k_row_pass (ROW_START)
+  if (s2) c = cscale(a.prop[(-hp.x & (NY - 1)) * NX + (-hp.y & (NX - 1))], a.scale2);
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const float2 w = tw[(hp.x * y * (a.L / NY) + hp.y * (t + S::TX * e) * (a.L / NX)) & (a.L - 1)];
+    v[e] = s2 ? cmul(c, w) : make_float2(w.x, -w.y);
+  }
+  for (int j = sd.j0;; j += s2 ? -1 : 1) {
+    const bool last = j == sd.j1;
+    const float2* Tj = a.T + (int64_t)j * (NY * NX) + y * NX + t;
+    float2 w[16];
+    if (j != sd.j0) {
+      fft::transform<NY, false, 1, true, true, true>(v, cbuf, tc, tw, a.L, taby);
+      int po = tc * NX + x;
+      asm volatile("" : "+v"(po));  // not 16 addresses kept over the slices: no registers for them
+#pragma unroll
+      for (int e = 0; e < 16; ++e) w[e] = a.prop[po + S::TY * NX * e];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) v[e] = cmul(v[e], w[e]);
+      fft::transform<NY, true, 1, true, true, true>(v, cbuf, tc, tw, a.L, taby);
+      __syncthreads();  // every column's exchange is done
+#pragma unroll
+      for (int e = 0; e < 16; ++e) buf[(tc + S::TY * e) * S::PR + S::swz(tc + S::TY * e, x)] = v[e];
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < 16; ++e) v[e] = rbuf[S::swz(y, t + S::TX * e)];
+      fft::exchange_sync<true>();
+    }
+    if (j != sd.j0) fft::transform<NX, true, 1, true, true, true>(v, rbuf, t, tw, a.L, tabx);
+    const int gb = a.planes[j], ge = a.planes[j + 1];
+    auto times_T = [&] {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) v[e] = cmul(v[e], Tj[S::TX * e]);
+    };
+    if (s2) times_T();
+    if (ge > gb) gather_row<NX>(v, t, y, col, NY, sd.ga, sd.ga.rec + gb, gb, ge, hp, tw, a.L, s2 ? -1 : +1);
+    if (last) break;
+    if (!s2) times_T();
+    fft::transform<NX, false, 1, true, true, true>(v, rbuf, t, tw, a.L, tabx);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) rbuf[S::swz(y, t + S::TX * e)] = v[e];  // this wave's rows
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 16; ++e) v[e] = buf[(tc + S::TY * e) * S::PR + S::swz(tc + S::TY * e, x)];
+    __syncthreads();
+  }
+}
+
+template <int NY, int NX>
+hipError_t sweep_launch(const SweepArgs& a, hipStream_t s) {
+  using S = SweepShape<NY, NX>;
+  const size_t lds = (size_t)(S::BUF + a.L + 16 * (S::RX + S::RY - 2)) * sizeof(float2);
+  hipError_t e = hipFuncSetAttribute((const void*)k_sweep<NY, NX>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_sweep<NY, NX>), dim3(a.side[0].n + a.side[1].n), dim3(S::THREADS), lds, s, a);
+  return hipGetLastError();
+}
+
 // Columns advanced at a time by a launch of `parts` workgroups per column: as
 // many as give it `slots` workgroups, the columns shared evenly over the rounds.
 inline int columns_at_once(int ncols, int parts, int slots) {
@@ -469,6 +569,16 @@ hipError_t launch_col_pass(float2* state, int ncols, int ny, int nx, const float
       return hipErrorInvalidValue;
   }
 #undef COL_CASE
+}
+
+hipError_t launch_sweep(const SweepArgs& a, int ny, int nx, hipStream_t s) {
+  if (a.side[0].n < 0 || a.side[1].n < 0 || a.L != std::max(ny, nx)) return hipErrorInvalidValue;
+  if (a.side[0].n + a.side[1].n == 0) return hipSuccess;
+  if (ny == 64 && nx == 64) return sweep_launch<64, 64>(a, s);
+  if (ny == 64 && nx == 128) return sweep_launch<64, 128>(a, s);
+  if (ny == 128 && nx == 64) return sweep_launch<128, 64>(a, s);
+  if (ny == 128 && nx == 128) return sweep_launch<128, 128>(a, s);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace bip
