@@ -1130,8 +1130,9 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
   ProbeJob* d_fjobs = p->focal ? (ProbeJob*)ws.take(atoms.size() * sizeof(ProbeJob)) : nullptr;
   const size_t chunk_base = ws.used;
   if (ws.used > work_cap) return err(BIP_ENOMEM, "internal: tables exceed the workspace");
-  HIPCHK(hipMemcpyAsync(d_cells, cells.data(), cells.size() * 4, hipMemcpyHostToDevice, st), "cells");
-  HIPCHK(hipMemcpyAsync(d_tws, tws.data(), tws.size() * 8, hipMemcpyHostToDevice, st), "twiddles");
+  TableCopy tables(p->h_tables, d_jobs);
+  tables.add(d_cells, cells);
+  tables.add(d_tws, tws);
   if ((out_mode == BIP_OUT_MAP || map_direct) && !accumulate) HIPCHK(launch_zero(out, P, st), "zero");
   if (beams_out && (beams_tmp || !accumulate)) HIPCHK(launch_zero(beams_out, (int64_t)P * p->ndet, st), "zero");
   // job tables, chunk-relative offsets
@@ -1244,21 +1245,18 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
       const int a = atoms[i];
       ratoms.push_back(ReconAtom{p->off2[a], off[1][i], p->W[a], p->oy[a], p->ox[a], (int32_t)n1_of(p->W[a])});
     }
-    HIPCHK(hipMemcpyAsync(d_ratoms, ratoms.data(), ratoms.size() * sizeof(ReconAtom), hipMemcpyHostToDevice, st),
-           "recon atoms");
+    tables.add(d_ratoms, ratoms);
   }
   GemmJob* d_jdet = d_jobs;
   GemmJob* d_jquad = d_jdet + jdet.size();
   if (gram)  // Gram launches: one per chunk over its atoms' jobs (their tile offsets set here)
     for (size_t c = 0; c < chunks.size(); ++c)
       gemm_gram_plan(&jdet[det_first[chunks[c].first]], chunks[c].second - chunks[c].first, gram_prec, fixed_order(p));
-  HIPCHK(hipMemcpyAsync(d_probe, jprobe.data(), jprobe.size() * sizeof(ProbeJob), hipMemcpyHostToDevice, st), "jobs");
-  if (p->focal && !jfocal.empty())
-    HIPCHK(hipMemcpyAsync(d_fjobs, jfocal.data(), jfocal.size() * sizeof(ProbeJob), hipMemcpyHostToDevice, st),
-           "jobs");
-  HIPCHK(hipMemcpyAsync(d_jdet, jdet.data(), jdet.size() * sizeof(GemmJob), hipMemcpyHostToDevice, st), "jobs");
-  if (!jquad.empty())
-    HIPCHK(hipMemcpyAsync(d_jquad, jquad.data(), jquad.size() * sizeof(GemmJob), hipMemcpyHostToDevice, st), "jobs");
+  tables.add(d_probe, jprobe);
+  if (p->focal) tables.add(d_fjobs, jfocal);
+  tables.add(d_jdet, jdet);
+  tables.add(d_jquad, jquad);
+  HIPCHK(tables.copy(st), "tables");
   ProbeArgs pa{};
   pa.win = p->d_win1;
   pa.n_par = p->Bp1;

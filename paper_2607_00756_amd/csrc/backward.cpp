@@ -240,9 +240,10 @@ int bip_eels_backward(bip_plan* p, int32_t n_ch, const float* H, const int64_t* 
     jprobe[a].fx_off = (a % nat_max) * bX;
     jprobe[a].out_off = (a % nat_max) * bPsi;
   }
-  HIPCHK(hipMemcpyAsync(d_cells, cells.data(), cells.size() * 4, hipMemcpyHostToDevice, st), "cells");
-  HIPCHK(hipMemcpyAsync(d_tws, tws.data(), tws.size() * 8, hipMemcpyHostToDevice, st), "twiddles");
-  HIPCHK(hipMemcpyAsync(d_probe, jprobe.data(), jprobe.size() * sizeof(ProbeJob), hipMemcpyHostToDevice, st), "jobs");
+  TableCopy tables(p->h_tables, d_cells);
+  tables.add(d_cells, cells);
+  tables.add(d_tws, tws);
+  tables.add(d_probe, jprobe);
   HIPCHK(launch_zero(ibar, Ppad, st), "zero");
   HIPCHK(hipMemcpyAsync(ibar, dL_dI, (size_t)P * 4, hipMemcpyDeviceToDevice, st), "dL/dI");
   HIPCHK(launch_zero((float*)p->d_gwin1, 2 * p->win1_elems, st), "zero");
@@ -325,7 +326,7 @@ int bip_eels_backward(bip_plan* p, int32_t n_ch, const float* H, const int64_t* 
     sj.ldo = (int32_t)kd;
   }
   for (int c0 = 0; c0 < na; c0 += nat_max) gemm_gram_plan(&hj[c0], std::min(nat_max, na - c0), gprec, 1);
-  HIPCHK(hipMemcpyAsync(d_jobs, hj.data(), hj.size() * sizeof(GemmJob), hipMemcpyHostToDevice, st), "jobs");
+  tables.add(d_jobs, hj);
   std::vector<AdjAtom>& hadj = p->h_adj;
   std::vector<ReconAtom>& hra = p->h_ratoms;  // the K-blocked operands of every atom, then the [d][r] ones
   hadj.clear();
@@ -337,8 +338,9 @@ int bip_eels_backward(bip_plan* p, int32_t n_ch, const float* H, const int64_t* 
     hra[a] = ReconAtom{p->off2[a], i * bS2b, p->W[a], p->oy[a], p->ox[a], (int32_t)roundup(W2, 128)};
     hra[na + a] = ReconAtom{p->off2[a], i * bS2d, p->W[a], p->oy[a], p->ox[a], (int32_t)roundup(W2, 32)};
   }
-  HIPCHK(hipMemcpyAsync(d_adj, hadj.data(), hadj.size() * sizeof(AdjAtom), hipMemcpyHostToDevice, st), "atoms");
-  HIPCHK(hipMemcpyAsync(d_ratoms, hra.data(), hra.size() * sizeof(ReconAtom), hipMemcpyHostToDevice, st), "atoms");
+  tables.add(d_adj, hadj);
+  tables.add(d_ratoms, hra);
+  HIPCHK(tables.copy(st), "tables");
   for (int c0 = 0; c0 < na; c0 += nat_max) {
     const int nat = std::min(nat_max, na - c0);
     int max_n1 = 0, max_kd = 0, max_w2 = 0;
@@ -537,20 +539,20 @@ int bip_eels_backward(bip_plan* p, int32_t n_ch, const float* H, const int64_t* 
 
 namespace {
 
-// Device temporaries of the potential helpers, released in stream order.
+// Device temporaries of the potential helpers: one block, released in stream order.
 struct Temps {
   const bip_alloc* al;
   hipStream_t st;
-  std::vector<std::pair<void*, size_t>> blocks;
-  template <typename T>
-  T* take(size_t count) {
-    const size_t bytes = std::max<size_t>(count, 1) * sizeof(T);
-    void* p = raw_alloc(al, bytes, st);
-    if (p) blocks.push_back({p, bytes});
-    return (T*)p;
+  char* base = nullptr;
+  size_t bytes = 0;
+  static size_t room(size_t n) { return (size_t)roundup((int64_t)std::max<size_t>(n, 1), 256); }
+  bool reserve(size_t n) {
+    bytes = n;
+    base = (char*)raw_alloc(al, n, st);
+    return base != nullptr;
   }
   ~Temps() {
-    for (auto& b : blocks) raw_release(al, b.first, b.second, st);
+    if (base) raw_release(al, base, bytes, st);
   }
 };
 
@@ -601,16 +603,20 @@ int bip_potential_build(const bip_grid* grid, int32_t n_atoms, const double* xyz
   if (rc) return rc;
   hipStream_t st = (hipStream_t)stream;
   const int64_t nt_all = (int64_t)owner.size();
-  Temps tmp{alloc, st, {}};
-  double* d_terms = tmp.take<double>(terms.size());
-  double* d_prof = tmp.take<double>((size_t)nt_all * (g.ny + g.nx));
-  int64_t* d_start = tmp.take<int64_t>(start.size());
-  if (!d_terms || !d_prof || !d_start) return err(BIP_ENOMEM, "potential build temporaries");
-  // pageable host sources: HIP copies them synchronously, so the vectors may
-  // go out of scope when the calls return
-  if (!terms.empty())
-    HIPCHK(hipMemcpyAsync(d_terms, terms.data(), terms.size() * 8, hipMemcpyHostToDevice, st), "terms");
-  HIPCHK(hipMemcpyAsync(d_start, start.data(), start.size() * 8, hipMemcpyHostToDevice, st), "terms");
+  Temps tmp{alloc, st};
+  const size_t prof = (size_t)nt_all * (g.ny + g.nx) * 8;
+  if (!tmp.reserve(Temps::room(terms.size() * 8) + Temps::room(start.size() * 8) + Temps::room(prof)))
+    return err(BIP_ENOMEM, "potential build temporaries");
+  Workspace ws{tmp.base, 0};
+  double* d_terms = (double*)ws.take(terms.size() * 8);
+  int64_t* d_start = (int64_t*)ws.take(start.size() * 8);
+  double* d_prof = (double*)ws.take(prof);
+  std::vector<char> host;
+  TableCopy tables(host, tmp.base);
+  tables.add(d_terms, terms);
+  tables.add(d_start, start);
+  // a pageable host source: HIP copies it synchronously, so it may go out of scope when the call returns
+  HIPCHK(tables.copy(st), "terms");
   HIPCHK(launch_profiles(d_terms, nt_all, g.ny, g.nx, g.ly, g.lx, 0, d_prof, nullptr, st), "profiles");
   HIPCHK(launch_build_slices(d_terms, d_prof, d_start, g.nz, g.ny, g.nx, V, st), "potential build");
   return BIP_OK;
@@ -635,20 +641,25 @@ int bip_potential_grad(const bip_grid* grid, int32_t n_atoms, const double* xyz,
   // terms of one atom are consecutive: its first term
   std::vector<int64_t> first(std::max(n_atoms, 1), 0);
   for (int64_t t = nt_all - 1; t >= 0; --t) first[owner[t]] = t;
-  Temps tmp{alloc, st, {}};
-  double* d_terms = tmp.take<double>(terms.size());
-  double* d_prof = tmp.take<double>((size_t)nt_all * (g.ny + g.nx));
-  double* d_dprof = tmp.take<double>((size_t)nt_all * (g.ny + g.nx));
-  double* d_out = tmp.take<double>(2 * (size_t)nt_all);
-  double* d_part = tmp.take<double>((size_t)grad_part_doubles(nt_all, g.ny));
-  int64_t* d_start = tmp.take<int64_t>(start.size());
-  int64_t* d_first = tmp.take<int64_t>(first.size());
-  if (!d_terms || !d_prof || !d_dprof || !d_out || !d_part || !d_start || !d_first)
+  Temps tmp{alloc, st};
+  const size_t prof = (size_t)nt_all * (g.ny + g.nx) * 8, part = (size_t)grad_part_doubles(nt_all, g.ny) * 8;
+  if (!tmp.reserve(Temps::room(terms.size() * 8) + Temps::room(start.size() * 8) + Temps::room(first.size() * 8) +
+                   2 * Temps::room(prof) + Temps::room(2 * (size_t)nt_all * 8) + Temps::room(part)))
     return err(BIP_ENOMEM, "potential gradient temporaries");
-  if (!terms.empty())
-    HIPCHK(hipMemcpyAsync(d_terms, terms.data(), terms.size() * 8, hipMemcpyHostToDevice, st), "terms");
-  HIPCHK(hipMemcpyAsync(d_start, start.data(), start.size() * 8, hipMemcpyHostToDevice, st), "terms");
-  HIPCHK(hipMemcpyAsync(d_first, first.data(), first.size() * 8, hipMemcpyHostToDevice, st), "terms");
+  Workspace ws{tmp.base, 0};
+  double* d_terms = (double*)ws.take(terms.size() * 8);
+  int64_t* d_start = (int64_t*)ws.take(start.size() * 8);
+  int64_t* d_first = (int64_t*)ws.take(first.size() * 8);
+  double* d_prof = (double*)ws.take(prof);
+  double* d_dprof = (double*)ws.take(prof);
+  double* d_out = (double*)ws.take(2 * (size_t)nt_all * 8);
+  double* d_part = (double*)ws.take(part);
+  std::vector<char> host;
+  TableCopy tables(host, tmp.base);
+  tables.add(d_terms, terms);
+  tables.add(d_start, start);
+  tables.add(d_first, first);
+  HIPCHK(tables.copy(st), "terms");
   HIPCHK(launch_profiles(d_terms, nt_all, g.ny, g.nx, g.ly, g.lx, 1, d_prof, d_dprof, st), "profiles");
   HIPCHK(launch_grad_terms(d_terms, d_prof, d_dprof, d_start, nt_all, (int)most, g.nz, g.ny, g.nx, dL_dV,
                            d_part, d_out, st),

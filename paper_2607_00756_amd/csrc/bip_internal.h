@@ -236,6 +236,7 @@ struct bip_plan {
   std::vector<bip::GemmJob> h_jobs2, h_jobs3;
   std::vector<bip::ReconAtom> h_ratoms;
   std::vector<bip::AdjAtom> h_adj;
+  std::vector<char> h_tables;  // all of them, as copied to the device
   std::vector<int32_t> h_qstart, h_qlist;
   std::vector<bip::ProbeJob> h_probe;
   std::vector<int32_t> h_cells;   // cell_start then cell_beams

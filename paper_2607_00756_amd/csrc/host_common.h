@@ -1,6 +1,7 @@
 // Host-side helpers shared by the C-ABI entry points (not part of the ABI).
 #pragma once
 
+#include <cstring>
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -65,6 +66,29 @@ inline void raw_release(const bip_alloc* al, void* ptr, size_t bytes, hipStream_
   if (al && al->release) al->release(ptr, bytes, (void*)s, al->ctx);
   else (void)hipFreeAsync(ptr, s);
 }
+
+// Tables of a call that lie in one device block (from `base`): gathered on the
+// host and copied at once.  Every copy from pageable memory costs the host a
+// staging round of its own, 2.4 us (a map of one atom took 210 us with six copies,
+// 197 with one).  The host block outlives the call.
+class TableCopy {
+ public:
+  TableCopy(std::vector<char>& host, void* base) : host_(host), base_((char*)base) { host_.clear(); }
+  template <typename T>
+  void add(const T* dst, const std::vector<T>& v) {
+    const size_t at = (const char*)dst - base_, n = v.size() * sizeof(T);
+    if (n == 0) return;
+    if (host_.size() < at + n) host_.resize(at + n);
+    std::memcpy(host_.data() + at, v.data(), n);
+  }
+  hipError_t copy(hipStream_t s) const {
+    return host_.empty() ? hipSuccess : hipMemcpyAsync(base_, host_.data(), host_.size(), hipMemcpyHostToDevice, s);
+  }
+
+ private:
+  std::vector<char>& host_;
+  char* base_;
+};
 
 inline const bip_alloc* plan_alloc(const bip_plan* p) { return p->has_alloc ? &p->alloc : nullptr; }
 
