@@ -66,7 +66,7 @@ __device__ inline void gather_row(const float2 (&v)[16], int t, int y, int col, 
 //   The sweeps' kernels took 53.9 ms with the stored start for 6 slices of 1024 x
 // 1024 and 42.7 so, 169 and 159 for 16 of 512 x 512, 16.9 and 16.3 for 20 of 256 x 256.
 template <int NX, int FLAGS>
-__global__ __launch_bounds__(256) void k_row_pass(float2* __restrict__ state, int ny,
+__global__ __launch_bounds__(256, 4) void k_row_pass(float2* __restrict__ state, int ny,
                                                   const float2* __restrict__ T,
                                                   const float2* __restrict__ twg, int L,
                                                   const int2* __restrict__ parents, int sign,
@@ -128,7 +128,12 @@ __global__ __launch_bounds__(256) void k_row_pass(float2* __restrict__ state, in
     if (ge > gb) gather_row<NX>(v, t, y, pcol, ny, ga, srec, gb, ge, parents[pcol], tw, L, sign);
   }
   if (FLAGS & ROW_FWD) {
-    fft::transform<NX, false, 1, true, true>(v, my_lds, t, tw, L);
+    // Above 256 the twiddles are read again: kept from the inverse transform they
+    // took 142 to 180 registers, two or three waves a SIMD (in 235 MB batches, 512:
+    // 83.3 us, 78.0 so; 1024: 103.3 and 86.7).
+    int tf = t;
+    if constexpr (NX > 256) asm volatile("" : "+v"(tf));
+    fft::transform<NX, false, 1, true, true>(v, my_lds, tf, tw, L);
 #pragma unroll
     for (int e = 0; e < 16; ++e) row[t + S::T * e] = v[e];
   }
