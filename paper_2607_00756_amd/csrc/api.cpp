@@ -628,9 +628,9 @@ int bip_plan_create(const bip_grid* grid, const bip_optics* optics, int32_t n_at
   p->one_sweep = small_grid(g.ny, g.nx) && !fixed_order(p) && !p->s2_stream;
   if (p->one_sweep) {
     if ((rc = upload(p, &p->d_planes, p->plane_start, st))) return fail(rc);
-  } else if ((rc = dalloc(p, &p->d_state1, (size_t)p->Bp1 * G, st)) ||
-             (rc = dalloc(p, &p->d_state2, (size_t)p->Bp2 * G, st))) {
-    return fail(rc);
+  } else {
+    if ((rc = dalloc(p, &p->d_state1, (size_t)(p->Bp1 + p->Bp2) * G, st))) return fail(rc);
+    p->d_state2 = p->d_state1 + (size_t)p->Bp1 * G;
   }
   std::vector<FocalAtom> fatoms;
   if (p->focal) {
@@ -662,37 +662,99 @@ int bip_plan_create(const bip_grid* grid, const bip_optics* optics, int32_t n_at
   return BIP_OK;
 }
 
-static int sweep_s1(bip_plan* p, hipStream_t st) {
+static RowStart s2_start(const bip_plan* p) { return RowStart{p->d_prop, (float)std::sqrt((double)p->g.ny * p->g.nx)}; }
+
+// Slices j0 .. i_max of nc S1 columns from c0 (j0 > 0: after the column pass of slice j0 - 1).
+static int s1_slices(bip_plan* p, int c0, int nc, int j0, hipStream_t st) {
   const bip_grid& g = p->g;
   const int64_t G = (int64_t)g.ny * g.nx;
-  const int batch = p->column_batch;
-  // ---- S1: entrance -> deepest ionization plane
-  const bool start = !fixed_order(p);  // the first row pass makes the plane waves (ROW_START)
-  if (!start)
+  const GatherArgs g1 = gather_args(p, 1);
+  float2* s1 = p->d_state1 + (int64_t)c0 * G;
+  for (int j = j0; j <= p->i_max; ++j) {
+    int flags = ROW_GATHER_BEFORE_T;
+    if (j > 0) flags |= ROW_INV;
+    else if (!fixed_order(p)) flags |= ROW_START;
+    if (j < p->i_max) flags |= ROW_T | ROW_FWD;
+    float2* save = nullptr;
+    if (p->d_ckpt1 && j < p->i_max && j % p->o.ckpt_stride == 0) {
+      flags |= ROW_SAVE;
+      save = p->d_ckpt1 + ((int64_t)(j / p->o.ckpt_stride) * p->Bp1 + c0) * G;
+    }
+    HIPCHK(timed(p, ST_S1_ROW, st, [&] { return launch_row_pass(flags, s1, nc, g.ny, g.nx, p->d_T + j * G, p->d_tw, p->L,
+                           p->d_par1, +1, g1, p->plane_start[j], p->plane_start[j + 1], c0, save, RowStart{}, st); }),
+           "S1 row pass");
+    if (j < p->i_max)
+      HIPCHK(timed(p, ST_S1_COL, st, [&] { return launch_col_pass(s1, nc, g.ny, g.nx, p->d_prop, p->d_tw, p->L, st); }),
+             "S1 column pass");
+  }
+  return BIP_OK;
+}
+
+// Slices j_hi .. j_lo of nc S2 columns from c0; the columns start here (ROW_START), or have had the
+// column pass of slice j_hi, or neither.
+enum S2From { S2_START, S2_PROPAGATED, S2_STATE };
+static int s2_slices(bip_plan* p, int c0, int nc, int j_hi, int j_lo, S2From from, hipStream_t st) {
+  const bip_grid& g = p->g;
+  const int64_t G = (int64_t)g.ny * g.nx;
+  const GatherArgs g2 = gather_args(p, 2);
+  float2* s2 = p->d_state2 + (int64_t)c0 * G;
+  for (int j = j_hi; j >= j_lo; --j) {
+    if (j < j_hi || from == S2_STATE)
+      HIPCHK(timed(p, ST_S2_COL, st, [&] { return launch_col_pass(s2, nc, g.ny, g.nx, p->d_prop, p->d_tw, p->L, st); }),
+             "S2 column pass");
+    int flags = (j == j_hi && from == S2_START ? ROW_START : ROW_INV) | ROW_T | ROW_GATHER_AFTER_T;
+    if (j > p->i_min) flags |= ROW_FWD;  // keep the state row-transformed until the last plane
+    float2* save = nullptr;
+    if (p->d_ckpt2 && (g.nz - 1 - j) % p->o.ckpt_stride == 0) {
+      flags |= ROW_SAVE;
+      save = p->d_ckpt2 + ((int64_t)((g.nz - 1 - j) / p->o.ckpt_stride) * p->Bp2 + c0) * G;
+    }
+    HIPCHK(timed(p, ST_S2_ROW, st, [&] { return launch_row_pass(flags, s2, nc, g.ny, g.nx, p->d_T + j * G, p->d_tw, p->L,
+                           p->d_par2, -1, g2, p->plane_start[j], p->plane_start[j + 1], c0, save, s2_start(p), st); }),
+           "S2 row pass");
+  }
+  return BIP_OK;
+}
+
+// S1: entrance -> deepest ionization plane
+static int sweep_s1(bip_plan* p, hipStream_t st) {
+  const bip_grid& g = p->g;
+  if (fixed_order(p))
     HIPCHK(timed(p, ST_INIT, st, [&] { return launch_init_planewaves(p->d_state1, p->d_par1, p->Bp1, g.ny, g.nx, p->d_tw, p->L, +1, 1.0f, st); }),
            "init S1");
-  GatherArgs g1 = gather_args(p, 1);
-  const int batch1 = balanced_batch(p->Bp1, batch);
+  const int batch1 = balanced_batch(p->Bp1, p->column_batch);
   for (int c0 = 0; c0 < p->Bp1; c0 += batch1) {
-    const int nc = std::min(batch1, p->Bp1 - c0);
-    float2* s1 = p->d_state1 + (int64_t)c0 * G;
-    for (int j = 0; j <= p->i_max; ++j) {
-      int flags = ROW_GATHER_BEFORE_T;
-      if (j > 0) flags |= ROW_INV;
-      else if (start) flags |= ROW_START;
-      if (j < p->i_max) flags |= ROW_T | ROW_FWD;
-      float2* save = nullptr;
-      if (p->d_ckpt1 && j < p->i_max && j % p->o.ckpt_stride == 0) {
-        flags |= ROW_SAVE;
-        save = p->d_ckpt1 + ((int64_t)(j / p->o.ckpt_stride) * p->Bp1 + c0) * G;
-      }
-      HIPCHK(timed(p, ST_S1_ROW, st, [&] { return launch_row_pass(flags, s1, nc, g.ny, g.nx, p->d_T + j * G, p->d_tw, p->L,
-                             p->d_par1, +1, g1, p->plane_start[j], p->plane_start[j + 1], c0, save, RowStart{}, st); }),
-             "S1 row pass");
-      if (j < p->i_max)
-        HIPCHK(timed(p, ST_S1_COL, st, [&] { return launch_col_pass(s1, nc, g.ny, g.nx, p->d_prop, p->d_tw, p->L, st); }),
-               "S1 column pass");
+    const int rc = s1_slices(p, c0, std::min(batch1, p->Bp1 - c0), 0, st);
+    if (rc) return rc;
+  }
+  return BIP_OK;
+}
+
+// Both sides of a plan whose sweeps start in their row passes, S1's columns and then S2's in even
+// batches.  In the batch that holds columns of both they advance side by side, S1's slice k with
+// S2's nz - 1 - k, until either reaches its last plane.
+static int sweep_both(bip_plan* p, hipStream_t st) {
+  const bip_grid& g = p->g;
+  const int64_t G = (int64_t)g.ny * g.nx;
+  const int total = p->Bp1 + p->Bp2, batch = balanced_batch(total, p->column_batch);
+  for (int c0 = 0; c0 < total; c0 += batch) {
+    const int nc = std::min(batch, total - c0), n1 = std::min(nc, std::max(0, p->Bp1 - c0)), n2 = nc - n1;
+    float2* s = p->d_state1 + (int64_t)c0 * G;
+    int k = 0;
+    for (; n1 > 0 && n2 > 0 && k < std::min(p->i_max, g.nz - 1 - p->i_min); ++k) {
+      const int j2 = g.nz - 1 - k;
+      const RowBoth both{n1, p->d_T + j2 * G, p->d_par2, gather_args(p, 2), p->plane_start[j2], p->plane_start[j2 + 1]};
+      HIPCHK(timed(p, ST_S2_ROW, st, [&] { return launch_row_pass(ROW_BOTH | (k ? ROW_INV : ROW_START) | ROW_T | ROW_FWD, s, nc,
+                             g.ny, g.nx, p->d_T + k * G, p->d_tw, p->L, p->d_par1, +1, gather_args(p, 1), p->plane_start[k],
+                             p->plane_start[k + 1], c0, nullptr, s2_start(p), st, both); }),
+             "row pass");
+      HIPCHK(timed(p, ST_S2_COL, st, [&] { return launch_col_pass(s, nc, g.ny, g.nx, p->d_prop, p->d_tw, p->L, st); }),
+             "column pass");
     }
+    int rc = n1 > 0 ? s1_slices(p, c0, n1, k, st) : BIP_OK;
+    if (!rc && n2 > 0)
+      rc = s2_slices(p, std::max(0, c0 - p->Bp1), n2, g.nz - 1 - k, p->i_min, k ? S2_PROPAGATED : S2_START, st);
+    if (rc) return rc;
   }
   return BIP_OK;
 }
@@ -721,7 +783,7 @@ int bip_build_smatrix(bip_plan* p, const float* V, void* stream) {
     sw.scale2 = (float)std::sqrt((double)G);
     HIPCHK(timed(p, ST_S2_ROW, st, [&] { return launch_sweep(sw, g.ny, g.nx, st); }), "sweeps");
   } else {
-    int rc = sweep_s1(p, st);
+    const int rc = !fixed_order(p) && !p->s2_stream ? sweep_both(p, st) : sweep_s1(p, st);
     if (rc) return rc;
   }
   // ---- focal back-propagation of the S1 windows to each atom's centroid plane
@@ -736,7 +798,7 @@ int bip_build_smatrix(bip_plan* p, const float* V, void* stream) {
   }
   // ---- S2: exit -> shallowest ionization plane (transpose multislice);
   // streamed plans sweep S2 inside bip_eels_signal, segment by segment
-  if (!p->s2_stream && !p->one_sweep) {
+  if (!p->s2_stream && fixed_order(p)) {
     int rc = sweep_s2(p, g.nz - 1, p->i_min, true, st);
     if (rc) return rc;
   }
@@ -754,32 +816,14 @@ int bip::sweep_s2(bip_plan* p, int j_hi, int j_lo, bool init, hipStream_t st) {
   const int batch2 = balanced_batch(p->Bp2, batch);
   // The parents start propagated by the first row pass (ROW_START), or row-transformed, the form the
   // state keeps between passes.
-  const bool start = init && !fixed_order(p);
-  const RowStart rs{p->d_prop, (float)(std::sqrt((double)G))};
-  if (init && !start)
+  if (init && fixed_order(p))
     HIPCHK(timed(p, ST_INIT, st, [&] { return launch_init_planewaves_rowft(p->d_state2, p->d_par2, p->Bp2, g.ny, g.nx, p->d_tw,
                                   p->L, (float)(1.0 / std::sqrt((double)G)), st); }),
            "init S2");
-  GatherArgs g2 = gather_args(p, 2);
   for (int c0 = 0; c0 < p->Bp2; c0 += batch2) {
-    const int nc = std::min(batch2, p->Bp2 - c0);
-    float2* s2 = p->d_state2 + (int64_t)c0 * G;
-    for (int j = j_hi; j >= j_lo; --j) {
-      const bool first = start && j == j_hi;
-      if (!first)
-        HIPCHK(timed(p, ST_S2_COL, st, [&] { return launch_col_pass(s2, nc, g.ny, g.nx, p->d_prop, p->d_tw, p->L, st); }),
-               "S2 column pass");
-      int flags = (first ? ROW_START : ROW_INV) | ROW_T | ROW_GATHER_AFTER_T;
-      if (j > p->i_min) flags |= ROW_FWD;  // keep the state row-transformed until the last plane
-      float2* save = nullptr;
-      if (p->d_ckpt2 && (g.nz - 1 - j) % p->o.ckpt_stride == 0) {
-        flags |= ROW_SAVE;
-        save = p->d_ckpt2 + ((int64_t)((g.nz - 1 - j) / p->o.ckpt_stride) * p->Bp2 + c0) * G;
-      }
-      HIPCHK(timed(p, ST_S2_ROW, st, [&] { return launch_row_pass(flags, s2, nc, g.ny, g.nx, p->d_T + j * G, p->d_tw, p->L,
-                             p->d_par2, -1, g2, p->plane_start[j], p->plane_start[j + 1], c0, save, rs, st); }),
-             "S2 row pass");
-    }
+    const int rc = s2_slices(p, c0, std::min(batch2, p->Bp2 - c0), j_hi, j_lo,
+                             init && !fixed_order(p) ? S2_START : S2_STATE, st);
+    if (rc) return rc;
   }
   return BIP_OK;
 }

@@ -215,7 +215,7 @@ struct bip_plan {
   bool one_sweep = false;       // both sweeps in one launch, no state in memory (launch_sweep)
   int32_t* d_planes = nullptr;  // plane_start, for that launch
   float2* d_state1 = nullptr;   // [Bp1][G]
-  float2* d_state2 = nullptr;   // [Bp2][G]
+  float2* d_state2 = nullptr;   // [Bp2][G], behind d_state1's
   float2* d_win1 = nullptr;     // window stacks
   float2* d_win2 = nullptr;
   // gradient state (ckpt_stride = 1)
@@ -309,6 +309,7 @@ hipError_t launch_sibson_general(const int2* query, int nq, const int2* parents,
 enum RowFlags {
   ROW_INV = 1, ROW_T = 2, ROW_FWD = 4, ROW_GATHER_BEFORE_T = 8, ROW_GATHER_AFTER_T = 16,
   ROW_SAVE = 32,  // write the state after T_j to `save` (slice checkpoint, [ncols][ny][nx])
+  ROW_BOTH = 128,  // columns of both sides (RowBoth): S1's gather before T, S2's after
   ROW_START = 64  // start from the parents' plane waves instead of reading the state (RowStart)
 };
 // The real-space wave a sweep starts its first row pass with: exp(2 pi i h.r/N) (S1, prop null), or
@@ -317,11 +318,19 @@ struct RowStart {
   const float2* prop = nullptr;
   float scale = 1.f;
 };
+// The S2 columns of a batch that ends S1's: column n1 of the batch is S2's first. All other arguments are S1's.
+struct RowBoth {
+  int n1 = 0;
+  const float2* T = nullptr;
+  const int2* parents = nullptr;
+  GatherArgs ga{};
+  int gb = 0, ge = 0;
+};
 // state (and save) point at the first column of the batch; col0 is that column's parent index
 hipError_t launch_row_pass(int flags, float2* state, int ncols, int ny, int nx, const float2* T,
                            const float2* tw, int L, const int2* parents, int detilt_sign,
                            const GatherArgs& ga, int gather_begin, int gather_end, int col0,
-                           float2* save, const RowStart& start, hipStream_t s);
+                           float2* save, const RowStart& start, hipStream_t s, const RowBoth& both = {});
 // Both sweeps of a small grid in one launch (small_grid); side 0: S1, 1: S2.
 struct SweepSide {
   const int2* parents;

@@ -57,6 +57,11 @@ __device__ inline void gather_row(const float2 (&v)[16], int t, int y, int col, 
   }
 }
 
+// A batch may hold the last columns of S1 and the first of S2, each workgroup on a
+// column of either (ROW_BOTH): the two sides advance side by side, so that a few
+// columns share their launches and the batches are even.  256 x 256, 30 slices, hex
+// parents: 57 + 58 passes of 15 us, 28 + 29 of 26 so; a map at f = 4, 50 slices: 4.95
+// ms of passes, 4.42 so; two configurations of 20 slices: 16.3 and 15.9.
 // A sweep of a plan without checkpoints starts with ROW_START, in registers: the
 // S1 wave is a plane wave, and so is the S2 wave after its first propagation, so
 // the state is neither written first nor read by this pass, and S2 needs no
@@ -71,13 +76,25 @@ __global__ __launch_bounds__(256, 4) void k_row_pass(float2* __restrict__ state,
                                                   const float2* __restrict__ twg, int L,
                                                   const int2* __restrict__ parents, int sign,
                                                   GatherArgs ga, int gb, int ge, int col0,
-                                                  float2* __restrict__ save, RowStart start) {
+                                                  float2* __restrict__ save, RowStart start, RowBoth both) {
   using S = RowShape<NX>;
   __shared__ float2 lds[S::ROWS * S::LDS_ROW];
   extern __shared__ float2 tw[];  // [L] twiddle table
-  __shared__ GatherRec srec[(FLAGS & (ROW_GATHER_BEFORE_T | ROW_GATHER_AFTER_T)) ? GREC_LDS : 1];
+  constexpr int GATHER = FLAGS & (ROW_GATHER_BEFORE_T | ROW_GATHER_AFTER_T | ROW_BOTH);
+  __shared__ GatherRec srec[GATHER ? GREC_LDS : 1];
+  if constexpr ((FLAGS & ROW_BOTH) != 0) {
+    if ((int)blockIdx.y >= both.n1) {
+      T = both.T;
+      parents = both.parents;
+      ga = both.ga;
+      gb = both.gb;
+      ge = both.ge;
+      col0 = -both.n1;
+      sign = -1;
+    }
+  }
   for (int i = threadIdx.x; i < L; i += 256) tw[i] = twg[i];
-  if constexpr ((FLAGS & (ROW_GATHER_BEFORE_T | ROW_GATHER_AFTER_T)) != 0) {
+  if constexpr (GATHER != 0) {
     if ((int)threadIdx.x < ge - gb && threadIdx.x < GREC_LDS) srec[threadIdx.x] = ga.rec[gb + threadIdx.x];
   }
   // the only workgroup barrier: a row and its LDS row belong to one wave, so
@@ -99,7 +116,7 @@ __global__ __launch_bounds__(256, 4) void k_row_pass(float2* __restrict__ state,
   if constexpr ((FLAGS & ROW_START) != 0) {
     const int2 hp = parents[pcol];
     float2 c = make_float2(1.f, 0.f);
-    if (start.prop) c = cscale(start.prop[(-hp.x & (ny - 1)) * NX + (-hp.y & (NX - 1))], start.scale);
+    if (start.prop && sign < 0) c = cscale(start.prop[(-hp.x & (ny - 1)) * NX + (-hp.y & (NX - 1))], start.scale);
     const int my = hp.x * y * (L / ny);
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
@@ -111,22 +128,28 @@ __global__ __launch_bounds__(256, 4) void k_row_pass(float2* __restrict__ state,
     for (int e = 0; e < 16; ++e) v[e] = row[t + S::T * e];
   }
   if (FLAGS & ROW_INV) fft::transform<NX, true, 1, true, true>(v, my_lds, t, tw, L);
-  if constexpr ((FLAGS & ROW_GATHER_BEFORE_T) != 0) {
+  auto gather = [&] {
     if (ge > gb) gather_row<NX>(v, t, y, pcol, ny, ga, srec, gb, ge, parents[pcol], tw, L, sign);
-  }
-  if (FLAGS & ROW_T) {
+  };
+  auto times_T = [&] {
     const float2* Trow = T + (int64_t)y * NX;
 #pragma unroll
     for (int e = 0; e < 16; ++e) v[e] = cmul(v[e], Trow[t + S::T * e]);
+  };
+  if constexpr ((FLAGS & ROW_BOTH) != 0) {
+    if (sign < 0) times_T();
+    gather();
+    if (sign > 0) times_T();
+  } else {
+    if constexpr ((FLAGS & ROW_GATHER_BEFORE_T) != 0) gather();
+    if constexpr ((FLAGS & ROW_T) != 0) times_T();
   }
   if constexpr ((FLAGS & ROW_SAVE) != 0) {  // slice checkpoint: the state after T_j
     float2* srow = save + ((int64_t)col * ny + y) * NX;
 #pragma unroll
     for (int e = 0; e < 16; ++e) srow[t + S::T * e] = v[e];
   }
-  if constexpr ((FLAGS & ROW_GATHER_AFTER_T) != 0) {
-    if (ge > gb) gather_row<NX>(v, t, y, pcol, ny, ga, srec, gb, ge, parents[pcol], tw, L, sign);
-  }
+  if constexpr ((FLAGS & ROW_GATHER_AFTER_T) != 0) gather();
   if (FLAGS & ROW_FWD) {
     // Above 256 the twiddles are read again: kept from the inverse transform they
     // took 142 to 180 registers, two or three waves a SIMD (in 235 MB batches, 512:
@@ -438,11 +461,11 @@ inline int columns_at_once(int ncols, int parts, int slots) {
 template <int NX, int FLAGS>
 hipError_t row_launch(float2* state, int ncols, int ny, const float2* T, const float2* tw, int L,
                       const int2* parents, int sign, const GatherArgs& ga, int gb, int ge,
-                      int col0, float2* save, const RowStart& start, hipStream_t s) {
+                      int col0, float2* save, const RowStart& start, const RowBoth& both, hipStream_t s) {
   using S = RowShape<NX>;
   dim3 grid(ny / S::ROWS, ncols);
   hipLaunchKernelGGL((k_row_pass<NX, FLAGS>), grid, dim3(256), L * sizeof(float2), s, state, ny, T, tw, L, parents,
-                     sign, ga, gb, ge, col0, save, start);
+                     sign, ga, gb, ge, col0, save, start, both);
   return hipGetLastError();
 }
 
@@ -450,11 +473,13 @@ template <int NX>
 hipError_t row_dispatch(int flags, float2* state, int ncols, int ny, const float2* T,
                         const float2* tw, int L, const int2* parents, int sign,
                         const GatherArgs& ga, int gb, int ge, int col0, float2* save,
-                        const RowStart& start, hipStream_t s) {
+                        const RowStart& start, const RowBoth& both, hipStream_t s) {
 #define ROW_CASE(F) \
   case F:           \
-    return row_launch<NX, F>(state, ncols, ny, T, tw, L, parents, sign, ga, gb, ge, col0, save, start, s);
+    return row_launch<NX, F>(state, ncols, ny, T, tw, L, parents, sign, ga, gb, ge, col0, save, start, both, s);
   switch (flags) {
+    ROW_CASE(ROW_BOTH | ROW_START | ROW_T | ROW_FWD)
+    ROW_CASE(ROW_BOTH | ROW_INV | ROW_T | ROW_FWD)
     ROW_CASE(ROW_START | ROW_GATHER_BEFORE_T | ROW_T | ROW_FWD)
     ROW_CASE(ROW_START | ROW_GATHER_BEFORE_T)
     ROW_CASE(ROW_START | ROW_T | ROW_GATHER_AFTER_T | ROW_FWD)
@@ -538,15 +563,15 @@ hipError_t launch_dv_reduce(const float* partial, int n_groups, int64_t n, float
 hipError_t launch_row_pass(int flags, float2* state, int ncols, int ny, int nx, const float2* T,
                            const float2* tw, int L, const int2* parents, int detilt_sign,
                            const GatherArgs& ga, int gather_begin, int gather_end, int col0,
-                           float2* save, const RowStart& start, hipStream_t s) {
+                           float2* save, const RowStart& start, hipStream_t s, const RowBoth& both) {
   if (ncols == 0) return hipSuccess;
   if ((flags & ROW_SAVE) && !save) return hipErrorInvalidValue;
   switch (nx) {
-    case 64: return row_dispatch<64>(flags, state, ncols, ny, T, tw, L, parents, detilt_sign, ga, gather_begin, gather_end, col0, save, start, s);
-    case 128: return row_dispatch<128>(flags, state, ncols, ny, T, tw, L, parents, detilt_sign, ga, gather_begin, gather_end, col0, save, start, s);
-    case 256: return row_dispatch<256>(flags, state, ncols, ny, T, tw, L, parents, detilt_sign, ga, gather_begin, gather_end, col0, save, start, s);
-    case 512: return row_dispatch<512>(flags, state, ncols, ny, T, tw, L, parents, detilt_sign, ga, gather_begin, gather_end, col0, save, start, s);
-    case 1024: return row_dispatch<1024>(flags, state, ncols, ny, T, tw, L, parents, detilt_sign, ga, gather_begin, gather_end, col0, save, start, s);
+    case 64: return row_dispatch<64>(flags, state, ncols, ny, T, tw, L, parents, detilt_sign, ga, gather_begin, gather_end, col0, save, start, both, s);
+    case 128: return row_dispatch<128>(flags, state, ncols, ny, T, tw, L, parents, detilt_sign, ga, gather_begin, gather_end, col0, save, start, both, s);
+    case 256: return row_dispatch<256>(flags, state, ncols, ny, T, tw, L, parents, detilt_sign, ga, gather_begin, gather_end, col0, save, start, both, s);
+    case 512: return row_dispatch<512>(flags, state, ncols, ny, T, tw, L, parents, detilt_sign, ga, gather_begin, gather_end, col0, save, start, both, s);
+    case 1024: return row_dispatch<1024>(flags, state, ncols, ny, T, tw, L, parents, detilt_sign, ga, gather_begin, gather_end, col0, save, start, both, s);
     default: return hipErrorInvalidValue;
   }
 }
