@@ -1128,7 +1128,7 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
     return abs2_groups((Dpad / det_m) * (Ppad / det_n), njobs, p->n_cu, std::max<int64_t>(0, split_cap) / slice_bytes);
   };
   std::vector<int64_t> gram_n(chunks.size(), 0);  // Gram tiles and K segments of each chunk
-  std::vector<int> gram_k(chunks.size(), 1);
+  std::vector<int> gram_k(chunks.size(), 1), gram_bm(chunks.size(), 0);
   int64_t split_bytes = 0;
   for (size_t c = 0; c < chunks.size(); ++c) {
     if (gram) {
@@ -1295,7 +1295,8 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
   GemmJob* d_jquad = d_jdet + jdet.size();
   if (gram)  // Gram launches: one per chunk over its atoms' jobs (their tile offsets set here)
     for (size_t c = 0; c < chunks.size(); ++c)
-      gemm_gram_plan(&jdet[det_first[chunks[c].first]], chunks[c].second - chunks[c].first, gram_prec, fixed_order(p));
+      gram_n[c] = gemm_gram_plan(&jdet[det_first[chunks[c].first]], chunks[c].second - chunks[c].first, gram_prec,
+                                 fixed_order(p), p->n_cu, gram_bm[c]);
   tables.add(d_probe, jprobe);
   if (p->focal) tables.add(d_fjobs, jfocal);
   tables.add(d_jdet, jdet);
@@ -1422,6 +1423,7 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
       q.out_plane = pl2;
       q.ksplit = gram_k[c];
       q.whole_diag = fixed_order(p);
+      q.gram_bm = gram_bm[c];
       q.gpart = (float4*)split_buf;
       q.gscale = (float)(p->f * p->f) / (gram_scale * gram_scale);
       q.qtri = 1;

@@ -188,11 +188,13 @@ int bip_eels_backward(bip_plan* p, int32_t n_ch, const float* H, const int64_t* 
       (int)std::max<int64_t>(1, std::min<int64_t>(p->n_atoms, (budget - (int64_t)fixed) / per_atom));
   // Gram tiles of each chunk of nat_max atoms (the Gram runs unsplit: fixed_order)
   std::vector<int64_t> gram_n;
+  std::vector<int> gram_bm;
   for (int c0 = 0; c0 < p->n_atoms; c0 += nat_max) {
     int64_t n = 0;
     for (int a = c0; a < std::min(p->n_atoms, c0 + nat_max); ++a) n += gemm_gram_tiles(p->W[a] * p->W[a], gprec, 1);
     if (n > INT32_MAX / 2) return err(BIP_EUNSUPPORTED, "Gram launch beyond the grid limit");
     gram_n.push_back(n);
+    gram_bm.push_back(0);
   }
   int gt, gtn;
   gemm_tile(prec, EPI_STORE, gt, gtn);
@@ -325,7 +327,9 @@ int bip_eels_backward(bip_plan* p, int32_t n_ch, const float* H, const int64_t* 
     sj.W2 = W2;
     sj.ldo = (int32_t)kd;
   }
-  for (int c0 = 0; c0 < na; c0 += nat_max) gemm_gram_plan(&hj[c0], std::min(nat_max, na - c0), gprec, 1);
+  for (int c0 = 0; c0 < na; c0 += nat_max)
+    gram_n[c0 / nat_max] =
+        gemm_gram_plan(&hj[c0], std::min(nat_max, na - c0), gprec, 1, p->n_cu, gram_bm[c0 / nat_max]);
   tables.add(d_jobs, hj);
   std::vector<AdjAtom>& hadj = p->h_adj;
   std::vector<ReconAtom>& hra = p->h_ratoms;  // the K-blocked operands of every atom, then the [d][r] ones
@@ -389,6 +393,7 @@ int bip_eels_backward(bip_plan* p, int32_t n_ch, const float* H, const int64_t* 
     ga.out2 = Gm;
     ga.ksplit = 1;
     ga.whole_diag = 1;
+    ga.gram_bm = gram_bm[c0 / nat_max];
     ga.gscale = 1.f / (gsc * gsc);
     HIPCHK(launch_zgemm_gram(gprec, prec, ga, (int)gram_n[c0 / nat_max], st), "Gram");
     // R = conj(psi) diag(Ibar) psi^T over the raster

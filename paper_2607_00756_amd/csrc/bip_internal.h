@@ -71,7 +71,7 @@ struct AdjAtom {
   int32_t sub, pad;    // and in the reconstruction-adjoint buffers
 };
 
-enum Epilogue { EPI_ABS2_MAP = 0, EPI_ABS2_BEAMS, EPI_GRAMQ, EPI_QUAD, EPI_STORE };
+enum Epilogue { EPI_ABS2_MAP = 0, EPI_ABS2_BEAMS, EPI_GRAMQ, EPI_QUAD, EPI_STORE, EPI_GRAMQ_SMALL };
 
 struct GemmArgs {
   const void* A;
@@ -91,6 +91,7 @@ struct GemmArgs {
                              // one partial row each
   int ksplit;                // EPI_GRAMQ, EPI_QUAD: K segments of every job (1: whole)
   int whole_diag;            // EPI_GRAMQ: every tile of a 128 x 128 block on the diagonal computed
+  int gram_bm;               // EPI_GRAMQ: rows of the tiles that the jobs' s0 counts (gemm_gram_plan)
   int nunits;                // EPI_GRAMQ: tiles x ksplit (set by launch_zgemm_gram)
   float4* gpart;             // EPI_GRAMQ: partial products of ksplit > 1 (gemm_gram_part_bytes a unit)
   float* slices;             // EPI_ABS2_BEAMS: [zsplit][P][ndet] of zsplit > 1
@@ -477,15 +478,16 @@ void gemm_tile(int prec, int epi, int& m, int& n);
 // (m_tiles, n_tiles, njobs) for EPI_STORE.  epi EPI_STORE + EPI_CONJ_A conjugates the A operand.
 constexpr int EPI_CONJ_A = 16;
 constexpr int ABS2_MAP_ROWS = 128;  // detector rows of an EPI_ABS2_MAP workgroup
-// EPI_GRAMQ: operands in in_prec, Q stored in out_prec (equal, or FP16 -> SPLIT_BF16); tiles: the
-// sum of gemm_gram_tiles over the launch's jobs
+// EPI_GRAMQ: operands in in_prec, Q stored in out_prec (equal, or FP16 -> SPLIT_BF16); tiles and
+// g.gram_bm: as gemm_gram_plan laid the launch's jobs
 hipError_t launch_zgemm_gram(int in_prec, int out_prec, const GemmArgs& g, int tiles, hipStream_t s);
 hipError_t launch_zgemm(int prec, int epi, const GemmArgs& g, int gx, int gy, int gz,
                         hipStream_t s);
 // Workgroup tiles of an EPI_GRAMQ job of n_lim rows.
 int64_t gemm_gram_tiles(int n_lim, int prec, int whole_diag);
-// Sets s0 of the jobs of one EPI_GRAMQ launch.  Call before they are uploaded.
-void gemm_gram_plan(GemmJob* jobs, int njobs, int prec, int whole_diag);
+// Sets s0 of the jobs of one EPI_GRAMQ launch; returns its tiles and, in bm, their rows.  Call before
+// the jobs are uploaded.
+int64_t gemm_gram_plan(GemmJob* jobs, int njobs, int prec, int whole_diag, int n_cu, int& bm);
 // K segments of an EPI_GRAMQ launch of `tiles` tiles of contraction length K: the count with the
 // least modelled time whose partial tiles (gemm_gram_part_bytes each) fit in part_bytes.
 int gemm_gram_ksplit(int prec, int64_t tiles, int K, int n_cu, int64_t part_bytes);

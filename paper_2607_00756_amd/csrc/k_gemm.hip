@@ -100,6 +100,14 @@ template <int EPI>
 struct Cfg<BIP_PREC_FP32, EPI> {
   static constexpr int WM = 2, WN = 2, NBM = 2, NBN = 2, NS = 3, WPE = 3;
 };
+// The Gram matrix of a plan that keeps its order of summation, where 64 x 64
+// tiles are fewer than the CUs: a tile's K loop cannot be split, so it is cut
+// smaller, one block a wave (4 atoms of 20 x 20 pixels, 2053 beams: 124 tiles
+// 196 us, 436 of 32 x 32 111 us).
+template <>
+struct Cfg<BIP_PREC_FP32, EPI_GRAMQ_SMALL> {
+  static constexpr int WM = 2, WN = 2, NBM = 1, NBN = 1, NS = 4, WPE = 4;
+};
 template <>
 struct Cfg<BIP_PREC_FP32, EPI_QUAD> {
   static constexpr int WM = 2, WN = 2, NBM = 2, NBN = 4, NS = 3, WPE = 2;
@@ -121,11 +129,13 @@ struct Tile : Cfg<PREC, EPI> {
   static constexpr int OPA = PT<PREC>::PLANES * PLA;        // A's chunk
   static constexpr int SB = OPA + PT<PREC>::PLANES * PLB;   // one stage
   static constexpr int RA = BM / 16 / NW, RB = BN / 16 / NW;  // 16-row blocks loaded per wave and plane
-  static constexpr int LPC = PT<PREC>::PLANES * (RA + RB);  // loads per wave and chunk
+  static constexpr int UNITS = PT<PREC>::PLANES * (BM + BN) / 16;  // 1 KB pieces of a chunk
+  static constexpr int LPC = UNITS / NW;                           // loads per wave and chunk
   static constexpr int LDS = C::NS * SB;
   // accumulator quads per thread (re and im): the layout of a partial tile
   static constexpr int QUADS = 2 * C::NBM * C::NBN;
-  static_assert(RA >= 1 && RB >= 1 && RA * 16 * NW == BM && RB * 16 * NW == BN, "whole row blocks per wave");
+  static constexpr bool ROWS = RA * 16 * NW == BM && RB * 16 * NW == BN;  // every wave loads rows of each plane
+  static_assert(UNITS % NW == 0, "whole pieces per wave");
 };
 
 // The FP32 Gram matrix sums its K products (all detector beams) in segments
@@ -136,7 +146,7 @@ struct Tile : Cfg<PREC, EPI> {
 // 32 products per rounding and are not segmented.)
 template <int PREC, int EPI>
 constexpr bool k_segmented() {
-  return EPI == EPI_GRAMQ && PREC == BIP_PREC_FP32;
+  return (EPI == EPI_GRAMQ || EPI == EPI_GRAMQ_SMALL) && PREC == BIP_PREC_FP32;
 }
 constexpr int KSEG = 2048;
 
@@ -213,8 +223,20 @@ template <int PREC, int EPI>
 __device__ inline void issue_chunk(const char* A, int64_t a_plane_b, int64_t lda_b, const char* B, int64_t b_plane_b,
                                    int64_t ldb_b, int64_t k0_bytes, char* buf, int wave, int lane) {
   using T = Tile<PREC, EPI>;
-  issue_rows<PREC, T::RA, T::PLA>(A, a_plane_b, lda_b, k0_bytes, buf, wave, lane);
-  issue_rows<PREC, T::RB, T::PLB>(B, b_plane_b, ldb_b, k0_bytes, buf + T::OPA, wave, lane);
+  if constexpr (T::ROWS) {
+    issue_rows<PREC, T::RA, T::PLA>(A, a_plane_b, lda_b, k0_bytes, buf, wave, lane);
+    issue_rows<PREC, T::RB, T::PLB>(B, b_plane_b, ldb_b, k0_bytes, buf + T::OPA, wave, lane);
+  } else {
+    // the chunk's 1 KB pieces in LDS order (A's planes, B's planes, row blocks in each), dealt to the waves
+    constexpr int UA = PT<PREC>::PLANES * T::BM / 16;
+#pragma unroll
+    for (int i = 0; i < T::LPC; ++i) {
+      const int u = T::LPC * wave + i, v = u < UA ? u : u - UA, nb = (u < UA ? T::BM : T::BN) / 16;
+      const int p = v / nb, row = 16 * (v - p * nb) + (lane >> 2), seg = (lane & 3) ^ swz(row);
+      const char* src = (u < UA ? A + p * a_plane_b + row * lda_b : B + p * b_plane_b + row * ldb_b) + k0_bytes + seg * 16;
+      __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(buf + u * 1024), 16, 0, 0);
+    }
+  }
 }
 
 template <typename T, int PLANE>
@@ -451,15 +473,16 @@ __host__ __device__ inline void blocked_tile(int e, int nt, int& ti, int& tj) {
 // others).
 constexpr int GRAM_TILE = 128;
 __host__ __device__ inline int gram_tiles(int n_lim, int bm, int whole_diag) {
-  const int nt = (n_lim + bm - 1) / bm;
-  return nt * (nt + 1) / 2 + (whole_diag && bm < GRAM_TILE ? nt / 2 : 0);
+  const int nt = (n_lim + bm - 1) / bm, R = GRAM_TILE / bm, rest = nt % R;
+  return nt * (nt + 1) / 2 + (whole_diag ? nt / R * (R * (R - 1) / 2) + rest * (rest - 1) / 2 : 0);
 }
 struct GramUnit {
   int jb, seg, m0, n0;
 };
 template <int BM>
 __device__ inline GramUnit gram_unit(const GemmArgs& g, int u, int ksplit) {
-  static_assert(BM == GRAM_TILE || 2 * BM == GRAM_TILE, "one or two tiles a block");
+  constexpr int R = GRAM_TILE / BM;  // tiles of a block's side
+  static_assert(R * BM == GRAM_TILE, "whole tiles a block");
   int lo = 0, hi = g.njobs - 1;  // the job: the last with s0 ksplit <= u
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
@@ -477,8 +500,15 @@ __device__ inline GramUnit gram_unit(const GemmArgs& g, int u, int ksplit) {
   if (e < nt * (nt + 1) / 2) {
     blocked_tile(e, nt, ti, tj);
   } else {
-    tj = 2 * (e - nt * (nt + 1) / 2);
-    ti = tj + 1;
+    // below the diagonal of block b, row by row
+    constexpr int C = R > 1 ? R * (R - 1) / 2 : 1;
+    e -= nt * (nt + 1) / 2;
+    const int b = e / C;
+    e -= b * C;
+    int i = 1;
+    while (e >= i) e -= i++;
+    ti = R * b + i;
+    tj = R * b + e;
   }
   r.m0 = ti * BM;
   r.n0 = tj * BM;
@@ -565,13 +595,14 @@ __global__ __launch_bounds__((Tile<PREC, EPI>::NT), (Cfg<PREC, EPI>::WPE)) void 
   constexpr int ESZ = PT<PREC>::ESZ;
   constexpr bool ACCUM = (EPI == EPI_ABS2_MAP || EPI == EPI_ABS2_BEAMS || EPI == EPI_QUAD);
   constexpr bool ABS2 = EPI == EPI_ABS2_MAP || EPI == EPI_ABS2_BEAMS;
+  constexpr bool GRAM = EPI == EPI_GRAMQ || EPI == EPI_GRAMQ_SMALL;
   // wave index in a scalar register: the LDS destinations of the direct loads
   // and the wave's tile offsets are then scalar values
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / T::WN, wn = wave % T::WN;
   const int lr = lane & 15, kg = lane >> 4;
   int m0, n0, jb0, jb1, kseg = 0, unit = 0;
-  if constexpr (EPI == EPI_GRAMQ) {
+  if constexpr (GRAM) {
     // 1-D grid.  Workgroup i runs on XCD i mod 8, and each XCD takes one
     // contiguous eighth of the launch's units: its tiles of one job and K
     // segment share their operand row blocks in its L2, and every XCD has the
@@ -707,7 +738,7 @@ __global__ __launch_bounds__((Tile<PREC, EPI>::NT), (Cfg<PREC, EPI>::WPE)) void 
         k0 = max(g.qtri ? n0 : 0, (int)((int64_t)nk * kseg / g.ksplit) * PT<PREC>::BK);
         k1 = (int)((int64_t)nk * (kseg + 1) / g.ksplit) * PT<PREC>::BK;
         if (k0 >= k1) continue;
-      } else if constexpr (EPI == EPI_GRAMQ) {
+      } else if constexpr (GRAM) {
         const int nk = job.K / PT<PREC>::BK;
         k0 = (int)((int64_t)nk * kseg / g.ksplit) * PT<PREC>::BK;
         k1 = (int)((int64_t)nk * (kseg + 1) / g.ksplit) * PT<PREC>::BK;
@@ -1012,7 +1043,15 @@ hipError_t zgemm_prec(int epi, const GemmArgs& g, dim3 grid, hipStream_t s) {
 template <int PREC, int OPREC>
 hipError_t gram_launch(const GemmArgs& g, int tiles, hipStream_t s) {
   using T = Tile<PREC, EPI_GRAMQ>;
-  hipError_t e = zgemm_launch<PREC, EPI_GRAMQ, true, OPREC>(g, dim3((unsigned)((g.nunits + 7) / 8 * 8)), s);
+  const dim3 grid((unsigned)((g.nunits + 7) / 8 * 8));
+  if (g.gram_bm != T::BM) {
+    if constexpr (PREC == BIP_PREC_FP32) {
+      if (g.gram_bm == Tile<PREC, EPI_GRAMQ_SMALL>::BM && g.ksplit == 1)
+        return zgemm_launch<PREC, EPI_GRAMQ_SMALL, true, OPREC>(g, grid, s);
+    }
+    return hipErrorInvalidValue;
+  }
+  hipError_t e = zgemm_launch<PREC, EPI_GRAMQ, true, OPREC>(g, grid, s);
   if (e != hipSuccess || g.ksplit == 1) return e;
   const int lds = g.n_ch * 2 * T::BM * (int)sizeof(float2);
   const int hlds = lds <= 65536;
@@ -1021,6 +1060,8 @@ hipError_t gram_launch(const GemmArgs& g, int tiles, hipStream_t s) {
   return hipGetLastError();
 }
 
+constexpr int GRAM_SMALL = 32;
+static_assert(Tile<BIP_PREC_FP32, EPI_GRAMQ_SMALL>::BM == GRAM_SMALL && Tile<BIP_PREC_FP32, EPI_GRAMQ_SMALL>::BN == GRAM_SMALL, "");
 constexpr int gram_bm(int prec) { return prec == BIP_PREC_FP32 ? 64 : 128; }
 static_assert(Tile<BIP_PREC_FP32, EPI_GRAMQ>::BM == 64 && Tile<BIP_PREC_SPLIT_BF16, EPI_GRAMQ>::BM == 128 &&
                   Tile<BIP_PREC_BF16, EPI_GRAMQ>::BM == 128 && Tile<BIP_PREC_FP16, EPI_GRAMQ>::BM == 128,
@@ -1092,12 +1133,21 @@ hipError_t launch_zgemm(int prec, int epi, const GemmArgs& g, int gx, int gy, in
 
 int64_t gemm_gram_tiles(int n_lim, int prec, int whole_diag) { return gram_tiles(n_lim, gram_bm(prec), whole_diag); }
 
-void gemm_gram_plan(GemmJob* jobs, int njobs, int prec, int whole_diag) {
-  int64_t n = 0;
-  for (int j = 0; j < njobs; ++j) {
-    jobs[j].s0 = (int32_t)n;
-    n += gram_tiles(jobs[j].n_lim, gram_bm(prec), whole_diag);
-  }
+int64_t gemm_gram_plan(GemmJob* jobs, int njobs, int prec, int whole_diag, int n_cu, int& bm) {
+  auto lay = [&] {
+    int64_t n = 0;
+    for (int j = 0; j < njobs; ++j) {
+      jobs[j].s0 = (int32_t)n;
+      n += gram_tiles(jobs[j].n_lim, bm, whole_diag);
+    }
+    return n;
+  };
+  bm = gram_bm(prec);
+  const int64_t n = lay();
+  // whole_diag: no K segments either, so few tiles are cut smaller (Cfg)
+  if (!whole_diag || prec != BIP_PREC_FP32 || n >= n_cu) return n;
+  bm = GRAM_SMALL;
+  return lay();
 }
 
 int64_t gemm_gram_part_bytes(int prec) {
