@@ -163,7 +163,9 @@ __global__ __launch_bounds__(256) void k_grad_tau(const AdjAtom* __restrict__ at
 }
 
 // Phase A of the reconstruction adjoint, per target beam b (one wave) and
-// window pixel r (one lane): g_z and gamma from the beam's cotangent.
+// window pixel r (one lane): g_z and gamma from the beam's cotangent.  The beam is
+// the same for a wave, so its table rows come through scalar loads (16 windows of
+// 24 x 24, 12,785 beams: 1.13 ms with vector loads, 0.90 so; phase B 0.85 and 0.76).
 // SIDE 1: the cotangent of S1~^b is c Z[cell(b)][r] (the adjoint of the
 // probe sum, see k_probe.hip); SIDE 2: g_S2~ [d][r] from the contraction.
 template <int SIDE>
@@ -180,7 +182,7 @@ __global__ __launch_bounds__(256) void k_recon_adj_a(ReconArgs a, const AdjAtom*
   const int64_t ld_src = SIDE == 1 ? (a.W * a.W + 63) & ~63 : (a.W * a.W + 31) & ~31;
   float2* gz = gz_all + (int64_t)at.sub * gz_stride;
   float* gam = gam_all + (int64_t)at.sub * gz_stride;
-  const int b = blockIdx.y * 4 + (threadIdx.x >> 6);
+  const int b = blockIdx.y * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // scalar: its tables too
   if (b >= a.nb) return;
   const int W2 = a.W * a.W;
   const int r = blockIdx.x * 64 + (threadIdx.x & 63);
@@ -243,7 +245,7 @@ __global__ __launch_bounds__(256) void k_recon_adj_b(ReconArgs a, const AdjAtom*
   float2* gwin = gwin_all + wo;
   const float2* gz = gz_all + (int64_t)at.sub * gz_stride;
   const float* gam = gam_all + (int64_t)at.sub * gz_stride;
-  const int p = blockIdx.y * 4 + (threadIdx.x >> 6);
+  const int p = blockIdx.y * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // scalar, as in phase A
   if (p >= Bp) return;
   const int W2 = a.W * a.W;
   const int r = blockIdx.x * 64 + (threadIdx.x & 63);
