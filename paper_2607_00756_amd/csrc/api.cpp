@@ -1324,6 +1324,7 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
   pa.Sx = scan_sx;
   pa.P = P;
   pa.Ppad = (int)Ppad;
+  pa.half = p->f == 1 && !fixed_order(p);
   pa.gy = std::gcd(p->f, scan_sy);
   pa.gx = std::gcd(p->f, scan_sx);
   // probe coefficients of the whole aperture; retained beams scaled by f^2

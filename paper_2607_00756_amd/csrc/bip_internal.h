@@ -139,6 +139,7 @@ struct ProbeArgs {
   const float2* tw;         // [L] exp(-2 pi i m / L)
   int L, ny, nx, mode;
   int Sy, Sx, P, Ppad;
+  int half;                 // f = 1 and sums free to reorder: outputs o and S - o of a DFT from one set of products
   int gy, gx;               // beams fall on residues that are multiples of these (dividing S_y, S_x)
   float cb;                 // probe coefficient c_b
   int unit0, n_units;       // the launch's pixel tiles (job t0 numbering) and their count

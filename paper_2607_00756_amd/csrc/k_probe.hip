@@ -79,6 +79,64 @@ __device__ inline void dft_mfma_part(const float2* sF, const float2* sT, int S, 
   }
 }
 
+// The same DFT with g = 1 and every output, in half the products: with F = a + i b,
+// X[o] and X[S - o] are sums and differences of C = sum cos(o j) F[j] and D = sum
+// sin(o j) F[j], so only the rows o < ceil(S / 2) are multiplied, cos and sin each
+// against re and im.  Row 0 of sin, zero otherwise, takes the alternating signs of
+// X[S / 2] when S is even.  Blocks 2 k and 2 k + 1 of a group hold C and D of rows 32
+// vi + 16 k + ..; dft_half_out hands out the outputs.  (Every map but those of plans
+// with checkpoints, which keep the order of their sums, and f > 1, whose masks need
+// few outputs.  Fold and DFT over y, 64 x 64 raster, 112 windows of 24 x 24: 2.57 and
+// 1.68 ms with all rows, 2.21 and 1.43 so; 128 x 128, 12 windows of 24 to 64: 7.1 and
+// 6.6, 5.2 and 4.2.)
+__device__ inline void dft_half_part(const float2* sF, const float2* sT, int S, int vi, int jb, int je, int wave,
+                                     int lane, v4f (&xr)[4], v4f (&xi)[4]) {
+  const int li = lane & 15, lk = lane >> 4, R = (S + 1) / 2;
+  int idx[2], step[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int i = 32 * vi + 16 * k + li, o = i < R ? i : 0;
+    idx[k] = (o * (jb + lk)) % S;
+    step[k] = (4 * o) % S;
+  }
+  const bool alt = vi == 0 && li == 0 && S % 2 == 0;
+  const float sign = lk & 1 ? -1.f : 1.f;  // (-1)^j: jb and the steps of j are even
+  for (int j0 = jb; j0 < je; j0 += 4) {
+    const float2 f = sF[(j0 - jb + lk) * RT + 16 * wave + li];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      if (32 * vi + 16 * k < R) {  // wave-uniform
+        const float2 e = sT[idx[k]];
+        const float sn = k == 0 && alt ? sign : -e.y;
+        xr[2 * k] = __builtin_amdgcn_mfma_f32_16x16x4f32(e.x, f.x, xr[2 * k], 0, 0, 0);
+        xi[2 * k] = __builtin_amdgcn_mfma_f32_16x16x4f32(e.x, f.y, xi[2 * k], 0, 0, 0);
+        xr[2 * k + 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(sn, f.x, xr[2 * k + 1], 0, 0, 0);
+        xi[2 * k + 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(sn, f.y, xi[2 * k + 1], 0, 0, 0);
+      }
+      idx[k] += step[k];
+      if (idx[k] >= S) idx[k] -= S;
+    }
+  }
+}
+template <typename Out>
+__device__ inline void dft_half_out(int S, int vi, int lane, const v4f (&xr)[4], const v4f (&xi)[4], Out out) {
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int i = 32 * vi + 16 * k + 4 * (lane >> 4) + q;
+      const float cr = xr[2 * k][q], ci = xi[2 * k][q], dr = xr[2 * k + 1][q], di = xi[2 * k + 1][q];
+      if (i >= (S + 1) / 2) continue;
+      if (i == 0) {
+        out(0, cr, ci);
+        if (S % 2 == 0) out(S / 2, dr, di);
+      } else {
+        out(i, cr + di, ci - dr);
+        out(S - i, cr - di, ci + dr);
+      }
+    }
+}
+
 __device__ inline void dft_mfma(const float2* sF, const float2* sT, int S, int obase, int wave,
                                 int lane, v4f (&xr)[4], v4f (&xi)[4]) {
 #pragma unroll
@@ -117,13 +175,14 @@ __device__ inline void fold_beam(FoldBeam& q, const ProbeArgs& pa, int b) {
 // the sum: with each loaded when needed, three trips to L2 a beam, a map of 112
 // windows of 24 x 24 with 8.1k beams and a 64 x 64 raster took 3.3 ms, 12 windows
 // of 24 to 64 with a 128 x 128 raster 8.0, 24 of 64 x 64 with hex parents 4.9;
-// with both loaded ahead 2.6, 7.2 and 4.1 (the DFT's matrix products alone are
-// 0.9, and the 50 vector instructions a beam and 64 pixels 0.7, of the first).
+// with both loaded ahead 2.6, 7.2 and 4.1, and 2.2, 5.2 and 3.3 with the DFT by
+// halves (whose matrix products alone are 0.45, and the 50 vector instructions a
+// beam and 64 pixels 0.7, of the first).
 // Residue row i of the workspace is row i g_y of the grid.  (256 x 256, 112
 // atoms, 64 x 64 scans, f = 4: the fold takes 0.21 ms and the DFT over y 0.09,
 // against 2.48 and 1.67 with every residue and every scan, of which 15 of 16 are
 // zero or outside the masks.)
-template <int NV>
+template <int NV, bool HALF>
 __global__ __launch_bounds__(NT, NV <= 2 ? 4 : NV == 3 ? 3 : 2) void k_probe_fold_x(const ProbeArgs pa) {
   extern __shared__ float2 sm[];
   const int Sx = pa.Sx, nc = Sx / pa.gx, nr = pa.Sy / pa.gy;  // residue columns and rows in use
@@ -240,12 +299,21 @@ __global__ __launch_bounds__(NT, NV <= 2 ? 4 : NV == 3 ? 3 : 2) void k_probe_fol
     for (int c = ce + wave; c < cp; c += 4) sF[(c - cc) * RT + lane] = make_float2(0.f, 0.f);
     __syncthreads();
 #pragma unroll
-    for (int vi = 0; vi < NV; ++vi)
-      dft_mfma_part(sF, sT, Sx, pa.gx, job.cv0, job.cnv, 64 * vi, cc, cp, wave, lane, xr[vi], xi[vi]);
+    for (int vi = 0; vi < NV; ++vi) {
+      if constexpr (HALF) dft_half_part(sF, sT, Sx, vi, cc, cp, wave, lane, xr[vi], xi[vi]);
+      else dft_mfma_part(sF, sT, Sx, pa.gx, job.cv0, job.cnv, 64 * vi, cc, cp, wave, lane, xr[vi], xi[vi]);
+    }
     __syncthreads();  // the chunk is consumed before the next one is folded
   }
   const int li = lane & 15, lk = lane >> 4;
   float2* X = pa.fx + job.fx_off + (int64_t)ai * Sx * job.ldf + r0 + 16 * wave + li;
+  if constexpr (HALF) {
+#pragma unroll
+    for (int vi = 0; vi < NV; ++vi)
+      dft_half_out(Sx, vi, lane, xr[vi], xi[vi],
+                   [&](int v, float re, float im) { X[(int64_t)v * job.ldf] = make_float2(re, im); });
+    return;
+  }
 #pragma unroll
   for (int vi = 0; vi < NV; ++vi)
 #pragma unroll
@@ -262,7 +330,7 @@ __global__ __launch_bounds__(NT, NV <= 2 ? 4 : NV == 3 ? 3 : 2) void k_probe_fol
 // operand's rows are the scans of the atom's mask, (i_u, i_v) row by row (all
 // scans at f = 1); U_n's are all scans, those off the mask not written (the
 // products mask them).
-template <int PREC, bool U, int NV>
+template <int PREC, bool U, int NV, bool HALF>
 __global__ __launch_bounds__(NT) void k_probe_y(const ProbeArgs pa) {
   extern __shared__ float2 sm[];
   const int Sy = pa.Sy, Sx = pa.Sx, nr = Sy / pa.gy;
@@ -306,8 +374,10 @@ __global__ __launch_bounds__(NT) void k_probe_y(const ProbeArgs pa) {
     }
     __syncthreads();
 #pragma unroll
-    for (int vi = 0; vi < NV; ++vi)
-      dft_mfma_part(sG, sT, Sy, pa.gy, job.cu0, job.cnu, 64 * vi, ac, ap, wave, lane, xr[vi], xi[vi]);
+    for (int vi = 0; vi < NV; ++vi) {
+      if constexpr (HALF) dft_half_part(sG, sT, Sy, vi, ac, ap, wave, lane, xr[vi], xi[vi]);
+      else dft_mfma_part(sG, sT, Sy, pa.gy, job.cu0, job.cnu, 64 * vi, ac, ap, wave, lane, xr[vi], xi[vi]);
+    }
     __syncthreads();  // the chunk is consumed before the next one is staged
   }
   // this lane's output pixel
@@ -325,7 +395,14 @@ __global__ __launch_bounds__(NT) void k_probe_y(const ProbeArgs pa) {
       store_planes<PREC>(pa.out, job.out_off + (int64_t)rho * kd + ro, pa.out_plane, re, im);
     }
   };
-  if (in) {
+  if constexpr (HALF) {
+    if (in) {
+#pragma unroll
+      for (int vi = 0; vi < NV; ++vi)
+        dft_half_out(Sy, vi, lane, xr[vi], xi[vi],
+                     [&](int u, float re, float im) { put(u * Sx + v, pa.cb * re, pa.cb * im); });
+    }
+  } else if (in) {
 #pragma unroll
     for (int vi = 0; vi < NV; ++vi)
 #pragma unroll
@@ -436,13 +513,15 @@ hipError_t launch_probe_fold_x(const ProbeArgs& pa, int unit0, int n_units, int 
   q.n_units = n_units;
   q.n_jobs = n_jobs;
   const size_t lds = ((size_t)std::min((pa.Sx / pa.gx + 3) & ~3, FOLD_CH) * RT + pa.Sx + pa.L) * sizeof(float2);
-  switch ((max_cnv + 63) / 64) {
-    case 1: return launch_lds(k_probe_fold_x<1>, dim3((unsigned)blocks), lds, q, s);
-    case 2: return launch_lds(k_probe_fold_x<2>, dim3((unsigned)blocks), lds, q, s);
-    case 3: return launch_lds(k_probe_fold_x<3>, dim3((unsigned)blocks), lds, q, s);
-    case 4: return launch_lds(k_probe_fold_x<4>, dim3((unsigned)blocks), lds, q, s);
-    default: return hipErrorInvalidValue;
-  }
+  if (pa.half && (pa.gx != 1 || pa.gy != 1 || max_cnv != pa.Sx)) return hipErrorInvalidValue;
+  const int nv = (max_cnv + 63) / 64;
+#define PF(NV)                                                                                     \
+  if (nv == NV)                                                                                    \
+    return pa.half ? launch_lds(k_probe_fold_x<NV, true>, dim3((unsigned)blocks), lds, q, s)       \
+                   : launch_lds(k_probe_fold_x<NV, false>, dim3((unsigned)blocks), lds, q, s);
+  PF(1) PF(2) PF(3) PF(4)
+#undef PF
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_probe_y(const ProbeArgs& pa, int prec, bool u, int max_kd, int max_cnu, int max_cnv, int n_jobs,
@@ -451,8 +530,11 @@ hipError_t launch_probe_y(const ProbeArgs& pa, int prec, bool u, int max_kd, int
   const dim3 grid((unsigned)((max_kd + RT - 1) / RT), (unsigned)max_cnv, (unsigned)n_jobs);
   const size_t lds = ((size_t)std::min((pa.Sy / pa.gy + 3) & ~3, FOLD_CH) * RT + pa.Sy) * sizeof(float2);
   const int nv = (max_cnu + 63) / 64;
-#define PYV(P, UU, NV) \
-  if (nv == NV) return launch_lds(k_probe_y<P, UU, NV>, grid, lds, pa, s);
+  if (pa.half && (pa.gx != 1 || pa.gy != 1 || max_cnu != pa.Sy || max_cnv != pa.Sx)) return hipErrorInvalidValue;
+#define PYV(P, UU, NV)                                                          \
+  if (nv == NV)                                                                 \
+    return pa.half ? launch_lds(k_probe_y<P, UU, NV, true>, grid, lds, pa, s)   \
+                   : launch_lds(k_probe_y<P, UU, NV, false>, grid, lds, pa, s);
 #define PY(P)                                                                                  \
   if (prec == P) {                                                                             \
     if (u) {                                                                                   \
