@@ -1467,7 +1467,7 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
       int zj = 1;
       u.ksplit = 1;
       if (fixed_order(p)) zj = quad_groups(Ppad / 128 * nt, nat, p->n_cu);
-      else quad_split((int64_t)mt * nt, nat, max_kd / gemm_bk(precision), p->n_cu, zj, u.ksplit);
+      else quad_split(mt, nt, quad_n / gemm_bk(precision), nat, max_kd / gemm_bk(precision), p->n_cu, zj, u.ksplit);
       u.zsplit = zj * u.ksplit;
       HIPCHK(timed(p, ST_DET, st, [&] { return launch_zgemm(precision, EPI_QUAD, u, mt, nt, u.zsplit, st); }),
              "quadratic form");

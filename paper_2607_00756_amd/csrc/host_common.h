@@ -212,21 +212,33 @@ inline int quad_groups(int64_t qt, int nat, int n_cu) {
   return best;
 }
 
-// Job groups (z) and K segments (k) of the quadratic form: qt tiles x z x k
-// workgroups give a CU ceil(qt z k / n_cu) of them, of ceil(nat / z) jobs of
-// ceil(chunks / k) K chunks, each job with about kQuadFill chunk times of
-// filling and epilogue (psi staging).  Take the pair with the least modelled
-// time, at most GEMM_MAX_ZSPLIT partial rows; the smaller on ties (fewer rows
-// to reduce).
+// Job groups (z) and K segments (k) of the quadratic form, at most GEMM_MAX_ZSPLIT
+// partial rows.  The workgroups (mt row tiles x nt column tiles x z k) go to the
+// CUs as these come free, the column tiles in order: tile y runs the K chunks from
+// its own column on (per_tile of them a tile), so the first tiles are the longest.
+// A job costs a workgroup its chunks and about kQuadFill chunk times of filling and
+// epilogue (psi staging).  Modelled time: the longest workgroup where every CU gets
+// one at most; else the work of a CU and, for the uneven end, half the longest.
+// The smallest split within a hundredth of the best (fewer rows to reduce).
+//   Counted as if every tile ran all chunks, 24 windows of 32 x 32 against 4096 scans
+// took one group, each CU one workgroup of its own length: 2.08 ms, 1.44 so; 112 windows
+// of 24 x 24 8 groups: 2.37 and 2.27.
 constexpr double kQuadFill = 6.0;
-inline void quad_split(int64_t qt, int nat, int chunks, int64_t n_cu, int& z_out, int& k_out) {
+inline void quad_split(int64_t mt, int64_t nt, int per_tile, int nat, int chunks, int64_t n_cu, int& z_out, int& k_out) {
   z_out = k_out = 1;
   double cost = 1e300;
   for (int z = 1; z <= std::min(GEMM_MAX_ZSPLIT, nat); ++z)
     for (int k = 1; z * k <= GEMM_MAX_ZSPLIT && k <= std::max(1, chunks / 2); ++k) {
-      const double c = (double)((qt * z * k + n_cu - 1) / n_cu) * (double)((nat + z - 1) / z) *
-                       ((double)((chunks + k - 1) / k) + kQuadFill);
-      if (c < 0.999 * cost) {
+      const int seg = (chunks + k - 1) / k;
+      const double longest = (double)((nat + z - 1) / z) * (seg + kQuadFill);
+      double work = 0;
+      for (int64_t y = 0; y < nt; ++y) {
+        const int64_t mine = std::max<int64_t>(0, chunks - y * per_tile);
+        work += (double)mine + kQuadFill * (double)((mine + seg - 1) / seg);
+      }
+      work *= (double)mt * nat / n_cu;
+      const double c = mt * nt * z * k <= n_cu ? longest : std::max(longest, work + 0.5 * longest);
+      if (c < 0.99 * cost) {
         z_out = z;
         k_out = k;
         cost = c;
