@@ -512,11 +512,13 @@ def main():
     # algorithmic bytes of a slice step are 16 G per column (the state read once
     # and written once); a step runs as two passes (rows, then columns), so each
     # pass is credited with half of it, 8 G per column of its batch
-    # (the batches run over both sides' columns, S1's first; over each side's own when S2 is streamed)
+    # (the batches run over both sides' columns where that saves one, over each side's own otherwise
+    # and when S2 is streamed)
     batch, segments = (int(v) for v in plan.query(bip.Q_SCALARS)[2:4])
     for st, ncol in (("s1_row", plan.Bp1), ("s1_col", plan.Bp1), ("s2_row", plan.Bp2), ("s2_col", plan.Bp2)):
-        if not segments:
-            ncol = plan.Bp1 + plan.Bp2
+        total = plan.Bp1 + plan.Bp2
+        if not segments and -(-total // batch) < -(-plan.Bp1 // batch) - (-plan.Bp2 // batch):
+            ncol = total
         n_batches = -(-ncol // batch)
         work[st] = (8.0 * G * ncol * stages[st][1] / args.steps / n_batches / 1e9, "GB/s", "hbm",
                     HBM_PEAK_GBS)

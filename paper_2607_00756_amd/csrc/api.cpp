@@ -730,13 +730,19 @@ static int sweep_s1(bip_plan* p, hipStream_t st) {
   return BIP_OK;
 }
 
-// Both sides of a plan whose sweeps start in their row passes, S1's columns and then S2's in even
-// batches.  In the batch that holds columns of both they advance side by side, S1's slice k with
-// S2's nz - 1 - k, until either reaches its last plane.
+// Both sides of a plan whose sweeps start in their row passes.  Where it saves a batch (a batch of
+// fewer columns takes almost the time of a full one) the batches run over S1's columns and then S2's;
+// in the batch that holds columns of both they advance side by side, S1's slice k with S2's
+// nz - 1 - k, until either reaches its last plane.
 static int sweep_both(bip_plan* p, hipStream_t st) {
   const bip_grid& g = p->g;
   const int64_t G = (int64_t)g.ny * g.nx;
+  auto batches = [&](int64_t n) { return (n + p->column_batch - 1) / p->column_batch; };
   const int total = p->Bp1 + p->Bp2, batch = balanced_batch(total, p->column_batch);
+  if (batches(total) == batches(p->Bp1) + batches(p->Bp2)) {
+    const int rc = sweep_s1(p, st);
+    return rc ? rc : sweep_s2(p, g.nz - 1, p->i_min, true, st);
+  }
   for (int c0 = 0; c0 < total; c0 += batch) {
     const int nc = std::min(batch, total - c0), n1 = std::min(nc, std::max(0, p->Bp1 - c0)), n2 = nc - n1;
     float2* s = p->d_state1 + (int64_t)c0 * G;

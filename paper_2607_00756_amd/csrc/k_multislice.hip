@@ -59,7 +59,7 @@ __device__ inline void gather_row(const float2 (&v)[16], int t, int y, int col, 
 
 // A batch may hold the last columns of S1 and the first of S2, each workgroup on a
 // column of either (ROW_BOTH): the two sides advance side by side, so that a few
-// columns share their launches and the batches are even.  256 x 256, 30 slices, hex
+// columns share their launches, where that saves a batch.  256 x 256, 30 slices, hex
 // parents: 57 + 58 passes of 15 us, 28 + 29 of 26 so; a map at f = 4, 50 slices: 4.95
 // ms of passes, 4.42 so; two configurations of 20 slices: 16.3 and 15.9.
 // A sweep of a plan without checkpoints starts with ROW_START, in registers: the
