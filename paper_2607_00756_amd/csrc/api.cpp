@@ -1451,7 +1451,6 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
         // each atom over the scans of its own mask, one partial row block per atom, as many atoms
         // at a time as the partial rows hold (at least GEMM_MAX_ZSPLIT)
         const int nt = max_n1 / quad_n, mt = (int)(max_prow / quad_m);
-        u.crop = 0;
         u.Mpad = (int)max_prow;
         u.ksplit = 1;
         const int64_t most = max_prow > 0 ? n_partial_tiles * Ppad / (nt * max_prow) : 0;

@@ -101,7 +101,7 @@ struct GemmArgs {
   float gscale;              // EPI_GRAMQ: factor on G (undoes a scaling of the operand), > 0
   int qtri;                  // EPI_GRAMQ: Q block-triangular (upper tiles doubled, lower not
                              // stored); EPI_QUAD: K from the tile's first column (reads that form)
-  int crop;                  // EPI_ABS2_*, EPI_QUAD: keep scan rho = u S_x + v only inside the
+  int crop;                  // EPI_ABS2_*: keep scan rho = u S_x + v only inside the
   int Sy, Sx;                // job's crop mask (PRISM interpolation factor > 1)
   float oscale;              // EPI_ABS2_*: factor on the intensities (f^2 of the detector sum)
   int mtiles, ntiles;        // EPI_ABS2_*: output tiles along M and N (set by launch_zgemm)

@@ -732,8 +732,6 @@ __global__ __launch_bounds__((Tile<PREC, EPI>::NT), (Cfg<PREC, EPI>::WPE)) void 
       // the block-triangular quadratic form runs K over r' >= the tile's first r
       int k0 = 0, k1 = job.K;
       if constexpr (EPI == EPI_QUAD) {
-        // scans along M; a tile holding no row of the job's crop mask skips the job
-        if (g.crop && !crop_rows_any(job, m0, min(m0 + BM - 1, g.P - 1), g.Sy, g.Sx)) continue;
         const int nk = job.K / PT<PREC>::BK;
         k0 = max(g.qtri ? n0 : 0, (int)((int64_t)nk * kseg / g.ksplit) * PT<PREC>::BK);
         k1 = (int)((int64_t)nk * (kseg + 1) / g.ksplit) * PT<PREC>::BK;
@@ -809,7 +807,6 @@ __global__ __launch_bounds__((Tile<PREC, EPI>::NT), (Cfg<PREC, EPI>::WPE)) void 
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
               const int rhol = wm * 16 * NBM + bm * 16 + kg * 4 + v;  // rho - m0
-              if (g.crop && !crop_in(job, m0 + rhol, g.Sy, g.Sx)) continue;
               const float2 ps = load_planes<PREC>(smem, (int64_t)rhol * QR + rl, QPL);
               sq[bm][bn][v] += ps.x * acc.re[bm][bn][v] + ps.y * acc.im[bm][bn][v];
             }
