@@ -28,7 +28,9 @@
  *     valid and the outputs are undefined.
  *   - A plan is not thread safe; different plans are independent.
  *   - Results are bitwise reproducible for identical inputs (no atomics in
- *     any reduction).
+ *     any reduction) and the same room for the workspace: where the device, the
+ *     allocator or the environment's BIP_WORKSPACE_GB (GiB) has none left for the
+ *     partial sums of a split contraction, it runs whole and rounds differently.
  */
 #ifndef BIP_H
 #define BIP_H
@@ -120,7 +122,8 @@ typedef struct bip_plan bip_plan;
  * caching allocator serves it.
  *   alloc    returns `bytes` of device memory usable in stream order on
  *            `stream` (the hipStream_t of the call that allocates), or NULL
- *            on failure (the call then returns BIP_ENOMEM).
+ *            on failure (the call then does with a smaller block where it
+ *            can, else returns BIP_ENOMEM).
  *   release  gives back a block from alloc (same size and stream); the
  *            library calls it in stream order: work queued on `stream`
  *            before the call may still use the block, none after it.

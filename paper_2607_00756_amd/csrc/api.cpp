@@ -1119,12 +1119,15 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
       b = e;
     }
   }
-  size_t need = (size_t)(fixed + max_chunk + 16 * 256);
+  // what the call cannot do without
+  const size_t need = (size_t)(fixed + max_chunk + 16 * 256);
   // Partial products of contractions split over K segments (Gram) or job
-  // groups (per-beam): as much as the launches want, within kSplitBytes, and
-  // with a caller-given workspace within what the rest of the call leaves.
+  // groups (per-beam): as much as the launches want, within kSplitBytes and
+  // what `need` leaves of the caller's workspace or budget (the operands of the
+  // default budget leave kSplitBytes beside them).
   int64_t split_cap = kSplitBytes;
-  if (ext_work) split_cap = std::min<int64_t>(split_cap, (int64_t)ext_bytes - (int64_t)need);
+  if (ext_work || env)
+    split_cap = std::min(split_cap, (ext_work ? (int64_t)ext_bytes : budget) - (int64_t)need);
   const int det_epi = map_direct ? EPI_ABS2_MAP : EPI_ABS2_BEAMS;
   int det_m, det_n, quad_m, quad_n;
   gemm_tile(precision, det_epi, det_m, det_n);
@@ -1136,30 +1139,42 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
   std::vector<int64_t> gram_n(chunks.size(), 0);  // Gram tiles and K segments of each chunk
   std::vector<int> gram_k(chunks.size(), 1), gram_bm(chunks.size(), 0);
   int64_t split_bytes = 0;
-  for (size_t c = 0; c < chunks.size(); ++c) {
-    if (gram) {
-      for (int i = chunks[c].first; i < chunks[c].second; ++i)
-        gram_n[c] += gemm_gram_tiles(p->W[atoms[i]] * p->W[atoms[i]], gram_prec, fixed_order(p));
-      if (!fixed_order(p)) gram_k[c] = gemm_gram_ksplit(gram_prec, gram_n[c], (int)Dk, p->n_cu, split_cap);
-      if (gram_n[c] * gram_k[c] > INT32_MAX / 2) return err(BIP_EUNSUPPORTED, "Gram launch beyond the grid limit");
-      if (gram_k[c] > 1) split_bytes = std::max(split_bytes, gram_n[c] * gram_k[c] * gemm_gram_part_bytes(gram_prec));
-    } else {
-      const int z = det_groups((chunks[c].second - chunks[c].first) * n_ch);
-      if (z > 1) split_bytes = std::max(split_bytes, z * slice_bytes);
+  auto choose_splits = [&] {
+    split_bytes = 0;
+    for (size_t c = 0; c < chunks.size(); ++c) {
+      if (gram) {
+        if (!fixed_order(p)) gram_k[c] = gemm_gram_ksplit(gram_prec, gram_n[c], (int)Dk, p->n_cu, split_cap);
+        if (gram_k[c] > 1) split_bytes = std::max(split_bytes, gram_n[c] * gram_k[c] * gemm_gram_part_bytes(gram_prec));
+      } else {
+        const int z = det_groups((chunks[c].second - chunks[c].first) * n_ch);
+        if (z > 1) split_bytes = std::max(split_bytes, z * slice_bytes);
+      }
     }
-  }
-  if (!ext_work || split_bytes > 0) need += (size_t)roundup(split_bytes, 256);
+    split_bytes = roundup(split_bytes, 256);
+  };
+  for (size_t c = 0; c < chunks.size() && gram; ++c)
+    for (int i = chunks[c].first; i < chunks[c].second; ++i)
+      gram_n[c] += gemm_gram_tiles(p->W[atoms[i]] * p->W[atoms[i]], gram_prec, fixed_order(p));
+  choose_splits();
+  for (size_t c = 0; c < chunks.size(); ++c)
+    if (gram_n[c] * gram_k[c] > INT32_MAX / 2) return err(BIP_EUNSUPPORTED, "Gram launch beyond the grid limit");
   char* work_base = nullptr;
   size_t work_cap = 0;
   if (ext_work) {
-    if (need > ext_bytes)
-      return err(BIP_EUNSUPPORTED, "this signal needs " + std::to_string(need) +
+    if (need + split_bytes > ext_bytes)
+      return err(BIP_EUNSUPPORTED, "this signal needs " + std::to_string(need + split_bytes) +
                                        " bytes of workspace; the allocation-free entry point has " +
                                        std::to_string(ext_bytes));
     work_base = (char*)ext_work;
     work_cap = ext_bytes;
   } else {
-    int rc = ensure_work(p, need, st);
+    const size_t with = need + split_bytes;
+    if (split_bytes > 0 && (with >= p->work_refused || !grow_work(p, with, st))) {  // no room: whole contractions
+      p->work_refused = std::min(p->work_refused, with);
+      split_cap = 0;
+      choose_splits();
+    }
+    int rc = ensure_work(p, need + split_bytes, st);
     if (rc) return rc;
     work_base = (char*)p->d_work;
     work_cap = p->work_bytes;

@@ -232,6 +232,7 @@ struct bip_plan {
   // signal workspace (grown on demand)
   void* d_work = nullptr;
   size_t work_bytes = 0;
+  size_t work_refused = SIZE_MAX;  // smallest size with partial products that the device had no room for: not asked for again
   float* d_tmp = nullptr;  // output of weighted / accumulated signals before the sum
   size_t tmp_bytes = 0;
   // host tables read by asynchronous copies; kept alive until the next call

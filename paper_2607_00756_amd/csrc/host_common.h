@@ -92,14 +92,21 @@ class TableCopy {
 
 inline const bip_alloc* plan_alloc(const bip_plan* p) { return p->has_alloc ? &p->alloc : nullptr; }
 
-// A block owned by the plan until bip_plan_destroy.
-inline int plan_block(bip_plan* p, void** out, size_t bytes, hipStream_t s) {
-  *out = raw_alloc(plan_alloc(p), bytes, s);
-  if (!*out) return err(BIP_ENOMEM, "device allocation of " + std::to_string(bytes) + " bytes failed");
-  p->allocations.push_back({*out, bytes});
+// A block owned by the plan until bip_plan_destroy; null when the device has no room for it.
+inline void* take_block(bip_plan* p, size_t bytes, hipStream_t s) {
+  void* ptr = raw_alloc(plan_alloc(p), bytes, s);
+  if (!ptr) return nullptr;
+  p->allocations.push_back({ptr, bytes});
   p->bytes_now += (int64_t)bytes;
   p->bytes_peak = std::max(p->bytes_peak, p->bytes_now);
-  return BIP_OK;
+  return ptr;
+}
+inline int no_room(size_t bytes) {
+  return err(BIP_ENOMEM, "device allocation of " + std::to_string(bytes) + " bytes failed");
+}
+inline int plan_block(bip_plan* p, void** out, size_t bytes, hipStream_t s) {
+  *out = take_block(p, bytes, s);
+  return *out ? BIP_OK : no_room(bytes);
 }
 inline void plan_release(bip_plan* p, void* ptr, hipStream_t s) {
   for (size_t i = 0; i < p->allocations.size(); ++i)
@@ -141,21 +148,22 @@ struct Workspace {
   }
 };
 
-// Grow the plan's workspace to `bytes`.  The old block is released in stream
-// order, so no synchronization is needed.
-inline int ensure_work(bip_plan* p, size_t bytes, hipStream_t s) {
-  if (p->work_bytes >= bytes) return BIP_OK;
+// Grow the plan's workspace to `bytes`; false when the device has no room.  The
+// old block is released in stream order, so no synchronization is needed.
+inline bool grow_work(bip_plan* p, size_t bytes, hipStream_t s) {
+  if (p->work_bytes >= bytes) return true;
   if (p->d_work) {
     plan_release(p, p->d_work, s);
     p->d_work = nullptr;
     p->work_bytes = 0;
   }
-  void* ptr = nullptr;
-  int rc = plan_block(p, &ptr, bytes, s);
-  if (rc) return rc;
-  p->d_work = ptr;
+  p->d_work = take_block(p, bytes, s);
+  if (!p->d_work) return false;
   p->work_bytes = bytes;
-  return BIP_OK;
+  return true;
+}
+inline int ensure_work(bip_plan* p, size_t bytes, hipStream_t s) {
+  return grow_work(p, bytes, s) ? BIP_OK : no_room(bytes);
 }
 
 // Largest parent-column batch of a sweep: BIP_COLUMN_BATCH if set (0 = all
@@ -187,7 +195,8 @@ inline int balanced_batch(int n, int cap) {
 }
 
 // Most a launch may add to the workspace for partial products of split
-// contractions.
+// contractions, within what a budget that the caller set leaves of it and while
+// the device has room; without it they run whole.
 constexpr int64_t kSplitBytes = (int64_t)512 << 20;
 
 // Plans that keep checkpoints differentiate the map: their contractions run

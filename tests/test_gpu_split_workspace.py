@@ -1,0 +1,81 @@
+"""Room for the partial products of split contractions: an allocator that has room for
+the operands only, and a BIP_WORKSPACE_GB that ends between the two sizes, both run the
+contractions whole; the budget then holds all that the call takes.  One window of 32 x 32
+pixels, whose Gram matrix runs in K segments and whose per-beam products run in job
+groups when there is room.
+
+Tolerance: 4e-5 against the oracle, as for the split contractions themselves."""
+import numpy as np
+import pytest
+
+from tests._tiny import as_oracle_problem, tiny_cfg, tiny_problem
+
+pytestmark = pytest.mark.gpu
+
+GIB = 1 << 30
+SCAN, N_CH = (4, 4), 6
+
+
+def arena(limit=None):
+    """A TorchAllocator that notes the sizes it is asked for and has no block above `limit`."""
+    from paper_2607_00756_amd import bip
+    al = bip.TorchAllocator()
+    inner, al.asked, al.limit = al._fns[0], [], limit
+
+    def alloc(n, stream, ctx):
+        al.asked.append(int(n))
+        if al.limit is not None and n > al.limit:
+            al.failed += 1
+            return None
+        return inner(n, stream, ctx)
+
+    al._fns = (bip._ALLOC_FN(alloc), al._fns[1], inner)
+    al.struct = bip.BipAlloc(al._fns[0], al._fns[1], None)
+    return al
+
+
+def signal(tp, mode_name, limit=None, calls=1):
+    """Output of the last call, the sizes each call asked for, and the refusals."""
+    import torch
+    from paper_2607_00756_amd import bip
+    al = arena()
+    plan = bip.Plan.from_config(tp.cfg, tp.tau, tp.win_size, tp.win_origin, allocator=al)
+    plan.build_smatrix(torch.from_numpy(tp.V).cuda())
+    H = torch.from_numpy(tp.H).cuda()
+    mode = getattr(bip, mode_name)
+    cols = {"OUT_BEAMS": (plan.ndet,), "OUT_QEELS": (plan.nq,)}.get(mode_name, ())
+    out = torch.full((SCAN[0] * SCAN[1],) + cols, float("nan"), dtype=torch.float32, device="cuda")
+    al.limit = limit
+    asked = []
+    for _ in range(calls):
+        al.asked.clear()
+        plan.eels_signal(N_CH, H, tp.H_off, SCAN, mode, bip.PREC_SPLIT_BF16, out)
+        asked.append(list(al.asked))
+    got = out.cpu().numpy().astype(np.float64)
+    plan.close()
+    return got, asked, al.failed
+
+
+@pytest.mark.parametrize("mode_name", ["OUT_MAP", "OUT_MAP_DIRECT", "OUT_BEAMS", "OUT_QEELS"])
+def test_contractions_run_whole_where_there_is_no_room(mode_name, monkeypatch):
+    from oracle import eels as E
+    monkeypatch.delenv("BIP_WORKSPACE_GB", raising=False)
+    cfg = tiny_cfg(ny=64, nx=64, nz=3, ly=8.0, lx=8.0, s=2, scan=SCAN)
+    tp = tiny_problem(cfg, n_atoms=1, n_ch=N_CH, seed=5, planes=[1], win_sizes=[32])
+    oracle_mode = {"OUT_BEAMS": E.OUT_BEAMS, "OUT_QEELS": E.OUT_QEELS}.get(mode_name, E.OUT_MAP)
+    want = E.BiP(as_oracle_problem(tp)).run(mode=oracle_mode)
+
+    def holds(got):
+        return np.linalg.norm(got - want) <= 4e-5 * np.linalg.norm(want)
+
+    free, asked, _ = signal(tp, mode_name)
+    split = max(asked[0])
+    got, asked, failed = signal(tp, mode_name, limit=split - 1, calls=2)
+    print(f"[{mode_name}] workspace {split} B with partial products, asked of the short arena {asked}", flush=True)
+    assert failed == 1 and asked[0][0] == split and len(asked[0]) == 2 and asked[1] == []
+    whole = asked[0][1]
+    assert whole < split and holds(free) and holds(got)
+    budget = (whole + split) // 2
+    monkeypatch.setenv("BIP_WORKSPACE_GB", repr(budget / GIB))
+    got, asked, failed = signal(tp, mode_name)
+    assert failed == 0 and max(asked[0]) <= budget and holds(got)
