@@ -1126,15 +1126,17 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
   // what `need` leaves of the caller's workspace or budget (the operands of the
   // default budget leave kSplitBytes beside them).
   int64_t split_cap = kSplitBytes;
-  if (ext_work || env)
-    split_cap = std::min(split_cap, (ext_work ? (int64_t)ext_bytes : budget) - (int64_t)need);
+  if (ext_work || env) {
+    const int64_t left = (ext_work ? (int64_t)ext_bytes : budget) - (int64_t)need;
+    split_cap = std::min(split_cap, std::max<int64_t>(0, left) / 256 * 256);  // the block is taken in steps of 256
+  }
   const int det_epi = map_direct ? EPI_ABS2_MAP : EPI_ABS2_BEAMS;
   int det_m, det_n, quad_m, quad_n;
   gemm_tile(precision, det_epi, det_m, det_n);
   gemm_tile(precision, EPI_QUAD, quad_m, quad_n);
   const int64_t slice_bytes = map_direct ? Dpad / det_m * Ppad * 4 : (int64_t)P * p->ndet * 4;
   auto det_groups = [&](int njobs) {  // job groups of a per-beam launch of njobs jobs
-    return abs2_groups((Dpad / det_m) * (Ppad / det_n), njobs, p->n_cu, std::max<int64_t>(0, split_cap) / slice_bytes);
+    return abs2_groups((Dpad / det_m) * (Ppad / det_n), njobs, p->n_cu, split_cap / slice_bytes);
   };
   std::vector<int64_t> gram_n(chunks.size(), 0);  // Gram tiles and K segments of each chunk
   std::vector<int> gram_k(chunks.size(), 1), gram_bm(chunks.size(), 0);

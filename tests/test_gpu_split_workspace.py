@@ -79,3 +79,23 @@ def test_contractions_run_whole_where_there_is_no_room(mode_name, monkeypatch):
     monkeypatch.setenv("BIP_WORKSPACE_GB", repr(budget / GIB))
     got, asked, failed = signal(tp, mode_name)
     assert failed == 0 and max(asked[0]) <= budget and holds(got)
+
+
+def test_noalloc_holds_slices_that_leave_less_than_a_step_of_the_array():
+    """Three job groups' slices would leave 96 bytes of the fixed array, less than the steps it
+    is handed out in: the call is not refused.  Either order of the 12 positive terms of a beam
+    rounds within 12 x 2^-24 = 7e-7."""
+    import torch
+    from paper_2607_00756_amd import bip
+    cfg = tiny_cfg(ny=64, nx=64, nz=3, ly=8.0, lx=8.0, theta=36e-3, s=2, scan=(29, 58))
+    tp = tiny_problem(cfg, n_atoms=3, n_ch=4, W=16, seed=2, planes=[0, 1, 2])
+    plan = bip.Plan.from_config(cfg, tp.tau, tp.win_size, tp.win_origin)
+    plan.build_smatrix(torch.from_numpy(tp.V).cuda())
+    H = torch.from_numpy(tp.H).cuda()
+    got = []
+    for noalloc in (False, True):
+        out = torch.full((29 * 58, plan.ndet), float("nan"), dtype=torch.float32, device="cuda")
+        plan.eels_signal(4, H, tp.H_off, cfg.scan, bip.OUT_BEAMS, bip.PREC_SPLIT_BF16, out, noalloc=noalloc)
+        got.append(out.cpu().numpy().astype(np.float64))
+    plan.close()
+    assert np.linalg.norm(got[1] - got[0]) <= 1e-6 * np.linalg.norm(got[0])
