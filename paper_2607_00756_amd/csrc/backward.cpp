@@ -83,7 +83,7 @@ int bip_eels_backward(bip_plan* p, int32_t n_ch, const float* H, const int64_t* 
   const int prec = precision;
   const int gprec = gram_precision(prec, p->ndet);
   const float gsc = gprec == BIP_PREC_FP16 ? 256.f : 1.f;
-  const int64_t esz = prec == BIP_PREC_FP32 ? 4 : 2, gesz = gprec == BIP_PREC_FP32 ? 4 : 2;
+  const int64_t gesz = gprec == BIP_PREC_FP32 ? 4 : 2;
   const int BKF = gemm_bk(gprec);
   int Wmax = 0;
   for (int a = 0; a < p->n_atoms; ++a) Wmax = std::max(Wmax, p->W[a]);

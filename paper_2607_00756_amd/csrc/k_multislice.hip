@@ -488,8 +488,6 @@ hipError_t row_dispatch(int flags, float2* state, int ncols, int ny, const float
     ROW_CASE(ROW_INV | ROW_GATHER_BEFORE_T | ROW_T | ROW_FWD | ROW_SAVE)
     ROW_CASE(ROW_INV | ROW_T | ROW_GATHER_AFTER_T | ROW_FWD | ROW_SAVE)
     ROW_CASE(ROW_INV | ROW_T | ROW_GATHER_AFTER_T | ROW_SAVE)
-    ROW_CASE(ROW_T | ROW_GATHER_AFTER_T | ROW_SAVE)
-    ROW_CASE(ROW_GATHER_BEFORE_T | ROW_T | ROW_FWD)
     ROW_CASE(ROW_INV | ROW_GATHER_BEFORE_T | ROW_T | ROW_FWD)
     ROW_CASE(ROW_INV | ROW_GATHER_BEFORE_T)
     ROW_CASE(ROW_GATHER_BEFORE_T)
@@ -497,7 +495,6 @@ hipError_t row_dispatch(int flags, float2* state, int ncols, int ny, const float
     ROW_CASE(ROW_INV | ROW_T | ROW_FWD | ROW_SAVE)  // recomputing a checkpoint segment
     ROW_CASE(ROW_INV | ROW_T | ROW_GATHER_AFTER_T | ROW_FWD)
     ROW_CASE(ROW_INV | ROW_T | ROW_GATHER_AFTER_T)
-    ROW_CASE(ROW_T | ROW_GATHER_AFTER_T)
     default:
       return hipErrorInvalidValue;
   }

@@ -413,22 +413,6 @@ __device__ inline void recon_kblk_tile(const ReconArgs& a, void* out, int n_r, i
   }
 }
 
-// One atom: a workgroup per beam tile and run of rpw pixel tiles.  Workgroup i
-// runs on XCD i mod 8; each XCD takes a contiguous range of (run, beam tile)
-// pairs, neighbouring beam tiles on the same pixels, so that the parents they
-// share stay in its L2.
-template <int PREC>
-__global__ __launch_bounds__(256) void k_recon_kblk(ReconArgs a, void* out, int nrows, int ncols,
-                                                    int64_t plane, int rpw) {
-  const int nbt = (ncols + TB - 1) / TB, nrt = (nrows + TR - 1) / TR;
-  const int nch = (nrt + rpw - 1) / rpw;
-  const int per = (int)(gridDim.x / 8);
-  const int lin = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
-  if (lin >= nbt * nch) return;
-  const int bt = lin % nbt, ch = lin / nbt;
-  recon_kblk_tile<PREC>(a, out, nrows, ncols, plane, bt, ch * rpw, min(nrt, ch * rpw + rpw));
-}
-
 // Every atom of a chunk in one launch: a workgroup per (atom, run of rpw pixel
 // tiles, beam tile); an XCD takes a contiguous range of them, so the beam
 // tiles of one atom, which share parents, meet in its L2.
@@ -530,20 +514,6 @@ hipError_t launch_recon_operand(const ReconArgs& a, void* out, int kind, int pre
   const int64_t nblk = (nt + 7) / 8 * 8;
   if (nblk > INT32_MAX) return hipErrorInvalidValue;
   dim3 grid((unsigned)nblk), block(256);
-  if (kind == 0 && a.tile_np <= TILE_NP) {
-#define RK(P)                                                                                    \
-  if (prec == P) {                                                                               \
-    hipLaunchKernelGGL((k_recon_kblk<P>), grid, block, a.L * sizeof(float2), s, a, out,          \
-                       (int)nrows_pad, (int)ncols_pad, plane_stride, (int)rpw);                  \
-    return hipGetLastError();                                                                    \
-  }
-    RK(BIP_PREC_FP32)
-    RK(BIP_PREC_SPLIT_BF16)
-    RK(BIP_PREC_BF16)
-    RK(BIP_PREC_FP16)
-#undef RK
-    return hipErrorInvalidValue;
-  }
 #define RC(P, K)                                                                            \
   if (prec == P && kind == K) {                                                             \
     hipLaunchKernelGGL((k_recon_operand<P, K>), grid, block, a.L * sizeof(float2), s, a, out, ld, (int)nrows_pad, \
