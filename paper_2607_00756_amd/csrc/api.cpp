@@ -684,7 +684,7 @@ static int s1_slices(bip_plan* p, int c0, int nc, int j0, hipStream_t st) {
                            p->d_par1, +1, g1, p->plane_start[j], p->plane_start[j + 1], c0, save, RowStart{}, st); }),
            "S1 row pass");
     if (j < p->i_max)
-      HIPCHK(timed(p, ST_S1_COL, st, [&] { return launch_col_pass(s1, nc, g.ny, g.nx, p->d_prop, p->d_tw, p->L, st); }),
+      HIPCHK(timed(p, ST_S1_COL, st, [&] { return launch_col_pass(s1, nc, g.ny, g.nx, p->d_prop, p->d_tw, p->L, p->n_cu, st); }),
              "S1 column pass");
   }
   return BIP_OK;
@@ -700,7 +700,7 @@ static int s2_slices(bip_plan* p, int c0, int nc, int j_hi, int j_lo, S2From fro
   float2* s2 = p->d_state2 + (int64_t)c0 * G;
   for (int j = j_hi; j >= j_lo; --j) {
     if (j < j_hi || from == S2_STATE)
-      HIPCHK(timed(p, ST_S2_COL, st, [&] { return launch_col_pass(s2, nc, g.ny, g.nx, p->d_prop, p->d_tw, p->L, st); }),
+      HIPCHK(timed(p, ST_S2_COL, st, [&] { return launch_col_pass(s2, nc, g.ny, g.nx, p->d_prop, p->d_tw, p->L, p->n_cu, st); }),
              "S2 column pass");
     int flags = (j == j_hi && from == S2_START ? ROW_START : ROW_INV) | ROW_T | ROW_GATHER_AFTER_T;
     if (j > p->i_min) flags |= ROW_FWD;  // keep the state row-transformed until the last plane
@@ -754,7 +754,7 @@ static int sweep_both(bip_plan* p, hipStream_t st) {
                              g.ny, g.nx, p->d_T + k * G, p->d_tw, p->L, p->d_par1, +1, gather_args(p, 1), p->plane_start[k],
                              p->plane_start[k + 1], c0, nullptr, s2_start(p), st, both); }),
              "row pass");
-      HIPCHK(timed(p, ST_S2_COL, st, [&] { return launch_col_pass(s, nc, g.ny, g.nx, p->d_prop, p->d_tw, p->L, st); }),
+      HIPCHK(timed(p, ST_S2_COL, st, [&] { return launch_col_pass(s, nc, g.ny, g.nx, p->d_prop, p->d_tw, p->L, p->n_cu, st); }),
              "column pass");
     }
     int rc = n1 > 0 ? s1_slices(p, c0, n1, k, st) : BIP_OK;

@@ -472,7 +472,7 @@ int bip_eels_backward(bip_plan* p, int32_t n_ch, const float* H, const int64_t* 
            "segment row transform");
     for (int r = 0; r < n_more; ++r) {
       const int j = slice_of(r);
-      HIPCHK(launch_col_pass(rec, nc, g.ny, g.nx, p->d_prop, p->d_tw, p->L, st), "segment column pass");
+      HIPCHK(launch_col_pass(rec, nc, g.ny, g.nx, p->d_prop, p->d_tw, p->L, p->n_cu, st), "segment column pass");
       HIPCHK(launch_row_pass(ROW_INV | ROW_T | ROW_FWD | ROW_SAVE, rec, nc, g.ny, g.nx, p->d_T + j * G,
                              p->d_tw, p->L, par, 0, none, 0, 0, 0, seg_slot(r), RowStart{}, st),
              "segment row pass");
@@ -497,7 +497,7 @@ int bip_eels_backward(bip_plan* p, int32_t n_ch, const float* H, const int64_t* 
         if (rc) return rc;
         for (int j = je; j >= js; --j) {
           const float2* u = j == js ? ck : seg_slot(j - js - 1);
-          HIPCHK(launch_col_pass(s1, nc, g.ny, g.nx, p->d_prop_conj, p->d_tw, p->L, st), "S1 adjoint column pass");
+          HIPCHK(launch_col_pass(s1, nc, g.ny, g.nx, p->d_prop_conj, p->d_tw, p->L, p->n_cu, st), "S1 adjoint column pass");
           int flags = ADJ_INV | ADJ_DV;
           if (j > 0) flags |= ADJ_CONJT | ADJ_INJ_AFTER | ADJ_FWD;
           HIPCHK(launch_row_adjoint(flags, s1, nc, g.ny, g.nx, p->d_T + j * G, p->d_tw, p->L, inj1,
@@ -527,7 +527,7 @@ int bip_eels_backward(bip_plan* p, int32_t n_ch, const float* H, const int64_t* 
         flags |= j == p->i_min ? ADJ_ZERO : ADJ_INV;
         if (j < g.nz - 1) flags |= ADJ_CONJT | ADJ_FWD;
         if (j > p->i_min)
-          HIPCHK(launch_col_pass(s2, nc, g.ny, g.nx, p->d_prop_conj, p->d_tw, p->L, st), "S2 adjoint column pass");
+          HIPCHK(launch_col_pass(s2, nc, g.ny, g.nx, p->d_prop_conj, p->d_tw, p->L, p->n_cu, st), "S2 adjoint column pass");
         HIPCHK(launch_row_adjoint(flags, s2, nc, g.ny, g.nx, p->d_T + j * G, p->d_tw, p->L, inj2, ps(j),
                                   ps(j + 1), c0, v, two_sigma, dvp, grp, st),
                "S2 adjoint row pass");

@@ -362,7 +362,7 @@ hipError_t launch_row_adjoint(int flags, float2* state, int ncols, int ny, int n
                               int groups, hipStream_t s);
 hipError_t launch_dv_reduce(const float* partial, int n_groups, int64_t n, float* dv, hipStream_t s);
 hipError_t launch_col_pass(float2* state, int ncols, int ny, int nx, const float2* prop,
-                           const float2* tw, int L, hipStream_t s);
+                           const float2* tw, int L, int n_cu, hipStream_t s);
 
 // reconstruction (k_recon.hip)
 struct ReconArgs {
@@ -385,6 +385,7 @@ struct ReconArgs {
   int L;
   int retilt_sign;       // +1: exp(+2 pi i h.r/N) (S1), -1 (S2)
   int mode;              // BIP_RECON_*
+  int n_cu;              // compute units of the device
 };
 // plain complex64 output [nb][W*W]
 hipError_t launch_recon_plain(const ReconArgs& a, float2* out, hipStream_t s);

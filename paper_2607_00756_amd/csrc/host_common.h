@@ -303,6 +303,7 @@ inline ReconArgs recon_args(const bip_plan* p, int a, int side) {
   r.L = p->L;
   r.retilt_sign = side == 1 ? +1 : -1;
   r.mode = p->o.recon_mode;
+  r.n_cu = p->n_cu;
   return r;
 }
 

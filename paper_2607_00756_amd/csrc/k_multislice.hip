@@ -303,7 +303,7 @@ struct ColShape {
 // 128-byte lines when CB < 16, meet in its L2.  For the same bytes, blocks
 // dealt over the XCDs took 117 us at 512 rows (CB = 8) and 177 us at 1024 (CB =
 // 16, one workgroup a CU); so 83 us and 109 us.
-constexpr int kCus = 256, kColWaves = 60;
+constexpr int kColWaves = 60;
 template <int NY>
 __global__ __launch_bounds__(ColShape<NY>::THREADS, ColShape<NY>::THREADS > 256 ? 2 : 3) void k_col_pass(
     float2* __restrict__ state, int nx, int ncols, const float2* __restrict__ prop,
@@ -574,14 +574,14 @@ hipError_t launch_row_pass(int flags, float2* state, int ncols, int ny, int nx, 
 }
 
 hipError_t launch_col_pass(float2* state, int ncols, int ny, int nx, const float2* prop,
-                           const float2* tw, int L, hipStream_t s) {
+                           const float2* tw, int L, int n_cu, hipStream_t s) {
   if (ncols == 0) return hipSuccess;
 #define COL_CASE(N)                                                                  \
   case N: {                                                                          \
     using S = ColShape<N>;                                                           \
     if (nx % S::CB) return hipErrorInvalidValue;                                     \
     const int nbx = nx / S::CB;                                                      \
-    const int at_once = columns_at_once(ncols, nbx, kCus * kColWaves * 64 / S::THREADS); \
+    const int at_once = columns_at_once(ncols, nbx, n_cu * kColWaves * 64 / S::THREADS); \
     hipLaunchKernelGGL(k_col_pass<N>, dim3(nbx * at_once), dim3(S::THREADS), L * sizeof(float2), s, \
                        state, nx, ncols, prop, tw, L);                               \
     return hipGetLastError();                                                        \

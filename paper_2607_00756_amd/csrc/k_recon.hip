@@ -61,6 +61,7 @@ __global__ void k_recon_plain(ReconArgs a, float2* out) {
 // per CU resident to hide the read latency.  Rows and columns beyond the beams
 // or the window are written as zeros.
 constexpr int TB = TILE_B, TR = 32;
+constexpr int64_t kWgs = 8;  // workgroups a CU that a launch wants
 
 // scale s conj(w) (sign > 0) or scale s w.  The rounding is spelled out: the
 // compiler may contract these products either way, and the operand is to have
@@ -443,12 +444,12 @@ hipError_t launch_recon_kblk_atoms(const ReconArgs& a, const ReconAtom* atoms, i
                                    hipStream_t s) {
   if (n_atoms <= 0 || ncols_pad <= 0) return hipSuccess;
   if (a.tile_np > TILE_NP || ncols_pad > INT32_MAX) return hipErrorInvalidValue;
-  // A run stages its tile's weights once and prefetches slab by slab, so runs
-  // are as long as they can be while the launch has about 2048 workgroups (8 a
-  // CU): one 32 x 32 window against 2053 beams took 115 us in 33 workgroups
-  // of 32 slabs, and 20 us in 33 x 32.
+  // A run stages its tile's weights once and prefetches slab by slab, so runs are
+  // as long as they can be while the launch has about kWgs workgroups a CU: one
+  // 32 x 32 window against 2053 beams took 115 us in 33 workgroups of 32 slabs, and
+  // 20 us in 33 x 32.
   const int64_t nbt = (ncols_pad + TB - 1) / TB, nrt = (max_nr + TR - 1) / TR;
-  const int64_t want = std::max<int64_t>(1, std::min<int64_t>(nrt, (2048 + nbt * n_atoms - 1) / (nbt * n_atoms)));
+  const int64_t want = std::max<int64_t>(1, std::min<int64_t>(nrt, (kWgs * a.n_cu + nbt * n_atoms - 1) / (nbt * n_atoms)));
   const int64_t rpw = (nrt + want - 1) / want, nch = (nrt + rpw - 1) / rpw;
   const int64_t nt = nbt * nch * n_atoms;
   const int64_t nblk = (nt + 7) / 8 * 8;
@@ -474,7 +475,7 @@ hipError_t launch_recon_rows_atoms(const ReconArgs& a, const ReconAtom* atoms, i
   if (nrows_pad > INT32_MAX) return hipErrorInvalidValue;
   // runs of pixel tiles as in launch_recon_kblk_atoms
   const int64_t nbt = (nrows_pad + TB - 1) / TB, nrt = (max_nr + TR - 1) / TR;
-  const int64_t want = std::max<int64_t>(1, std::min<int64_t>(nrt, (2048 + nbt * n_atoms - 1) / (nbt * n_atoms)));
+  const int64_t want = std::max<int64_t>(1, std::min<int64_t>(nrt, (kWgs * a.n_cu + nbt * n_atoms - 1) / (nbt * n_atoms)));
   const int64_t rpw = (nrt + want - 1) / want, nch = (nrt + rpw - 1) / rpw;
   const int64_t nblk = (nbt * nch * n_atoms + 7) / 8 * 8;
   if (nblk > INT32_MAX) return hipErrorInvalidValue;
@@ -507,8 +508,8 @@ hipError_t launch_recon_operand(const ReconArgs& a, void* out, int kind, int pre
   const int64_t n_b = kind == 0 ? ncols_pad : nrows_pad, n_r = kind == 0 ? nrows_pad : ncols_pad;
   const int64_t nbt = (n_b + TB - 1) / TB, nrt = (n_r + TR - 1) / TR;
   // runs of pixel tiles long enough to reuse the staged weights, short
-  // enough that the launch still has about 2048 workgroups
-  const int64_t nch = std::max<int64_t>(1, std::min<int64_t>(nrt, (2048 + nbt - 1) / nbt));
+  // enough that the launch still has about kWgs workgroups a CU
+  const int64_t nch = std::max<int64_t>(1, std::min<int64_t>(nrt, (kWgs * a.n_cu + nbt - 1) / nbt));
   const int64_t rpw = (nrt + nch - 1) / nch;
   const int64_t nt = nbt * ((nrt + rpw - 1) / rpw);
   const int64_t nblk = (nt + 7) / 8 * 8;
