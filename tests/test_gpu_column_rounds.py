@@ -36,3 +36,30 @@ def test_many_columns_match_the_oracle(ny, nx, ly, lx, theta, monkeypatch):
     want = ms.s2_windows(cfg, par[pick], prob.T, prob.P, [(0, y, x)])[0] * E.carrier(cfg, par[pick], y, x, +1)
     plan.close()
     assert np.linalg.norm(got[pick] - want) <= 1e-5 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("ny,nx,ly,lx,theta", [(128, 128, 16.0, 16.0, 40e-3), (128, 64, 16.0, 8.0, 60e-3)])
+def test_many_columns_of_checkpointed_sweeps_match_the_oracle(ny, nx, ly, lx, theta, monkeypatch):
+    """Grids of sides up to 128 run the column pass in plans with checkpoints only (without, as in
+    the first case above, a sweep is one launch).  Four and two blocks of x; every column is checked."""
+    import torch
+    from oracle import eels as E
+    from oracle import multislice as ms
+    from paper_2607_00756_amd import bip
+    monkeypatch.setenv("BIP_COLUMN_BATCH", "0")
+    cfg = dataclasses.replace(tiny_cfg(ny=ny, nx=nx, nz=2, ly=ly, lx=lx, alpha=15e-3, theta=theta, s=3, scan=(2, 2)),
+                              s2_exact=True)
+    tp = tiny_problem(cfg, n_atoms=1, n_ch=1, W=8, seed=12, planes=[0])
+    plan = bip.Plan.from_config(cfg, tp.tau, tp.win_size, tp.win_origin, ckpt_stride=1)
+    at_once = 15 * torch.cuda.get_device_properties(0).multi_processor_count // (nx // 32)  # of a launch, 60 waves a CU
+    assert plan.Bp2 > at_once and plan.Bp2 % at_once
+    plan.build_smatrix(torch.from_numpy(tp.V).cuda())
+    out = torch.full((plan.Bp2, 8, 8), float("nan"), dtype=torch.complex64, device="cuda")
+    plan.parent_windows(0, 2, out)
+    got, par = out.cpu().numpy(), plan.query(bip.Q_PARENTS2)
+    plan.close()
+    prob = as_oracle_problem(tp)
+    y, x = prob.window(0)
+    want = ms.s2_windows(cfg, par, prob.T, prob.P, [(0, y, x)])[0] * E.carrier(cfg, par, y, x, +1)
+    print(f"[{ny} x {nx}] {len(par)} columns, {at_once} at once", flush=True)
+    assert np.linalg.norm(got - want) <= 1e-5 * np.linalg.norm(want)
