@@ -1,6 +1,6 @@
 """Reverse sweeps on wide grids (each row length has its own kernel), with column
-batches that give a workgroup no, one and several columns in turn, against the
-FP64 oracle gradient.  Bar: rel-L2 1e-3, as for the other gradients."""
+batches that give a workgroup one and several columns in turn (a launch has no more
+workgroups a row than columns) and that leave a short one, against the FP64 oracle gradient.  Bar: rel-L2 1e-3, as for the other gradients."""
 import numpy as np
 import pytest
 
@@ -27,3 +27,10 @@ def test_wide_rows_match_the_oracle_gradient(nx, batch):
     gH_ref = np.concatenate([ref["gH"][a].ravel() for a in range(2)])
     assert rel_l2(dV, ref["dV"]) < 1e-3
     assert np.linalg.norm(gH - gH_ref) < 1e-3 * np.linalg.norm(gH_ref)
+
+
+@pytest.mark.parametrize("nx,batch", [(128, 7), (1024, 45)])
+def test_batches_of_a_few_columns_match_the_oracle_gradient(nx, batch):
+    """15 and 31 columns in batches of 5 and of 7 with a short last one; more than the 32 groups
+    of a launch in a batch of several, so that some workgroups have two columns and some one."""
+    test_wide_rows_match_the_oracle_gradient(nx, batch)
