@@ -12,8 +12,8 @@ HBM before the timed region.  The metric is scan positions x transitions per
 second, one unit being one (scan position, atom, channel) triple.
 
 Prints one JSON line.  It carries the roofline of the dominant kernel (device
-time from HIP events recorded on the launch stream inside the timed region)
-and the FP64 CPU oracle timed on a bounded sample of the same workload.
+time from HIP events recorded on the launch stream in a second pass of the same
+steps) and the FP64 CPU oracle timed on a bounded sample of the same workload.
 """
 from __future__ import annotations
 
@@ -338,6 +338,41 @@ def measured_traffic(stage, column_batch):
     return float(t["bytes_per_launch"])
 
 
+def sweep_passes(bp1, bp2, ny, nx, nz, i_max, i_min, batch, segments):
+    """{stage: [launches, columns over all launches]} of the parent sweeps of a build and a signal
+    on a plan without checkpoints.  Batches that hold columns of both sides run their shared passes
+    under S2; a grid of sides up to 128 with resident S2 windows is one launch (no pass over memory)."""
+    n = {st: [0, 0] for st in ("s1_row", "s1_col", "s2_row", "s2_col")}
+
+    def add(stage, launches, columns):
+        n[stage][0] += launches
+        n[stage][1] += launches * columns
+
+    def batches(first, end):
+        rounds = -(-(end - first) // batch)
+        size = -(-(end - first) // rounds) if rounds else 1
+        return [(c, min(c + size, end)) for c in range(first, end, size)]
+
+    if max(ny, nx) <= 128 and not segments:
+        n["s2_row"] = [1, 0]
+        return n
+    total = bp1 + bp2
+    share = not segments and -(-total // batch) < -(-bp1 // batch) - (-bp2 // batch)
+    for a, b in batches(0, total) if share else batches(0, bp1) + batches(bp1, total):
+        n1 = max(0, min(b, bp1) - a)
+        n2 = b - a - n1
+        both = min(i_max, nz - 1 - i_min) if n1 and n2 else 0
+        add("s2_row", both, b - a)
+        add("s2_col", both, b - a)
+        if n1:
+            add("s1_row", i_max + 1 - both, n1)
+            add("s1_col", i_max - both, n1)
+        if n2:
+            add("s2_row", nz - i_min - both, n2)
+            add("s2_col", nz - 1 - i_min - both, n2)
+    return n
+
+
 def atom_groups_run(args):
     """The whole ionized-atom set in K groups: per group a plan (created
     untimed), warmup steps, then timed steps of build + signal.  The job time
@@ -507,28 +542,28 @@ def main():
     else:
         work["gram_gemm"] = (float(np.sum(8.0 * W2 * W2 * nd)) / 1e12, "TFLOP/s", "mfma", mfma_peak)
         work["det_gemm"] = (float(np.sum(8.0 * W2 * W2 * P)) / 1e12, "TFLOP/s", "mfma", mfma_peak)
-    # parent sweeps: every pass reads and writes the whole state of the columns
-    # of its batch; launches_per_step / n_batches passes over all columns
-    # algorithmic bytes of a slice step are 16 G per column (the state read once
-    # and written once); a step runs as two passes (rows, then columns), so each
-    # pass is credited with half of it, 8 G per column of its batch
-    # (the batches run over both sides' columns where that saves one, over each side's own otherwise
-    # and when S2 is streamed)
+    # parent sweeps: algorithmic bytes of a slice step are 16 G per column (the state read once
+    # and written once); a step runs as two passes (rows, then columns), so each pass is credited
+    # with half of it, 8 G per column of its launch
     batch, segments = (int(v) for v in plan.query(bip.Q_SCALARS)[2:4])
-    for st, ncol in (("s1_row", plan.Bp1), ("s1_col", plan.Bp1), ("s2_row", plan.Bp2), ("s2_col", plan.Bp2)):
-        total = plan.Bp1 + plan.Bp2
-        if not segments and -(-total // batch) < -(-plan.Bp1 // batch) - (-plan.Bp2 // batch):
-            ncol = total
-        n_batches = -(-ncol // batch)
-        work[st] = (8.0 * G * ncol * stages[st][1] / args.steps / n_batches / 1e9, "GB/s", "hbm",
-                    HBM_PEAK_GBS)
+    planes = plan.query(bip.Q_PLANES)
+    i_max, i_min = int(planes.max()), int(planes.min())
+    col_slices = plan.Bp1 * i_max + plan.Bp2 * (cfg.nz - i_min)
+    passes = sweep_passes(plan.Bp1, plan.Bp2, cfg.ny, cfg.nx, cfg.nz, i_max, i_min, batch, segments)
+    whole = passes["s2_row"] == [1, 0]
+    if whole:  # one launch, the state in registers: the two 2-D transforms of a slice step (S2 starts after one)
+        work["s2_row"] = ((col_slices - plan.Bp2) * 10.0 * G * math.log2(G) / 1e12, "TFLOP/s", "alu", ALU_PEAK_TFLOPS)
+    else:
+        for st, (_, columns) in passes.items():
+            work[st] = (8.0 * G * columns / 1e9, "GB/s", "hbm", HBM_PEAK_GBS)
     names = {"probe_fold": "k_probe_fold_x (S1~ reconstruction + residue fold + DFT over x)",
              "probe_dft": "k_probe_y (DFT over y, operand store)",
              "recon": "k_recon_operand (S2~ reconstruction)",
              "gram_gemm": "k_zgemm Gram matrix + H correlation",
              "det_gemm": "k_zgemm detector contraction" if direct else "k_zgemm quadratic form",
              "s1_row": "k_row_pass (S1)", "s1_col": "k_col_pass (S1)",
-             "s2_row": "k_row_pass (S2)", "s2_col": "k_col_pass (S2)"}
+             "s2_row": "k_sweep (both sides)" if whole else "k_row_pass (S2 and shared batches)",
+             "s2_col": "k_col_pass (S2 and shared batches)"}
     dom = max(work, key=lambda k: stages[k][0])
     dom_ms, dom_n = stages[dom]
     launches_per_step = dom_n / args.steps
@@ -539,9 +574,8 @@ def main():
                      "unit": w[1], "bound": w[2], "frac": (w[0] / (stages[k][0] / args.steps / 1e3) / w[3]
                                                             if stages[k][0] > 0 else None)}
                  for k, w in work.items()}
-    # multislice as a whole: algorithmic 16 G bytes per parent column per slice
-    planes = plan.query(bip.Q_PLANES)
-    col_slices = plan.Bp1 * int(planes.max()) + plan.Bp2 * (cfg.nz - int(planes.min()))
+    # multislice as a whole: algorithmic 16 G bytes per parent column per slice (none of it moves in
+    # one launch of whole sweeps)
     ms_bytes = 16.0 * G * col_slices
     ms_time = sum(stages[k][0] for k in ("s1_row", "s1_col", "s2_row", "s2_col")) / args.steps
     res = {
@@ -578,8 +612,8 @@ def main():
         "stages_ms_per_step": {k: v[0] / args.steps for k, v in stages.items()},
         "ms_per_step_with_stage_events": ms_step_profiled,
         "multislice": {"algorithmic_GB": ms_bytes / 1e9, "ms_per_step": ms_time,
-                       "achieved_GBs": ms_bytes / (ms_time / 1e3) / 1e9,
-                       "frac_of_hbm": ms_bytes / (ms_time / 1e3) / 1e9 / HBM_PEAK_GBS},
+                       "achieved_GBs": None if whole else ms_bytes / (ms_time / 1e3) / 1e9,
+                       "frac_of_hbm": None if whole else ms_bytes / (ms_time / 1e3) / 1e9 / HBM_PEAK_GBS},
         "wall_s": wall,
     }
     if args.compare:

@@ -390,8 +390,9 @@ int bip_set_profiling(bip_plan* plan, int32_t enable);
  * BIP_N_STAGES entries, indexed by BIP_ST_*.  reset != 0 clears the totals.
  * Stages: TRANSMIT exp(i sigma V); S1_ROW / S1_COL and S2_ROW / S2_COL the
  * row and column FFT passes of the two parent sweeps (window gathers fused
- * into the row passes; the sweeps of a grid of sides up to 128 are one launch,
- * counted as S2_ROW); INIT plane-wave parents; RECON S2~ reconstruction;
+ * into the row passes; passes over a batch that holds columns of both sides are
+ * counted as S2_ROW / S2_COL while it does, and the sweeps of a grid of sides up
+ * to 128 are one launch, counted as S2_ROW); INIT plane-wave parents; RECON S2~ reconstruction;
  * FOLD S1~ reconstruction fused with the residue fold and the first DFT of
  * the probe synthesis; PROBE its second DFT and operand store; DET the
  * detector contraction (beams, qEELS, direct map) or the quadratic form of
