@@ -71,7 +71,10 @@ typedef struct bip_optics {
                            transmitted state of every parent column at every k-th
                            slice (slice checkpoints) so that bip_eels_backward can
                            run; it recomputes the other slices of a segment from
-                           its checkpoint (k = 1: nothing recomputed) */
+                           its checkpoint (k = 1: nothing recomputed).  The sums of
+                           such a plan keep one order, so its outputs and those of a
+                           plan without checkpoints agree to FP32 rounding, not to
+                           the bit */
   double s2_window_gb;  /* budget of the S2 window stacks (GiB; 0 = 48).  When the
                            windows of all atoms exceed it, the S2 sweep runs inside
                            bip_eels_signal in plane segments whose windows fit the

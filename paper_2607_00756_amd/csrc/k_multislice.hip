@@ -152,8 +152,10 @@ __global__ __launch_bounds__(256, 4) void k_row_pass(float2* __restrict__ state,
   if constexpr ((FLAGS & ROW_GATHER_AFTER_T) != 0) gather();
   if (FLAGS & ROW_FWD) {
     // Above 256 the twiddles are read again: kept from the inverse transform they
-    // took 142 to 180 registers, two or three waves a SIMD (in 235 MB batches, 512:
-    // 83.3 us, 78.0 so; 1024: 103.3 and 86.7).
+    // took 142 to 180 registers, two or three waves a SIMD (in 235 MB batches, 16
+    // slices of 512: 83.3 us, 78.0 so; 6 of 1024: 103.3 and 86.7.  With 100 slices of
+    // 512 and 20 windows a plane the tables and the windows share the cache with the
+    // state: 114 us).
     int tf = t;
     if constexpr (NX > 256) asm volatile("" : "+v"(tf));
     fft::transform<NX, false, 1, true, true>(v, my_lds, tf, tw, L);
@@ -302,7 +304,8 @@ struct ColShape {
 // reads only its part of the propagator, and neighbouring blocks, which share
 // 128-byte lines when CB < 16, meet in its L2.  For the same bytes, blocks
 // dealt over the XCDs took 117 us at 512 rows (CB = 8) and 177 us at 1024 (CB =
-// 16, one workgroup a CU); so 83 us and 109 us.
+// 16, one workgroup a CU); so 83 us and 109 us (16 and 6 slices; in the midst of 100
+// slices with 20 windows a plane, 512 rows: 122 and 95 us).
 constexpr int kColWaves = 60;
 template <int NY>
 __global__ __launch_bounds__(ColShape<NY>::THREADS, ColShape<NY>::THREADS > 256 ? 2 : 3) void k_col_pass(
