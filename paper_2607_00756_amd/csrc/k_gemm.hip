@@ -563,8 +563,10 @@ __device__ inline void gram_store(const GemmArgs& g, const GemmJob& job, int m0,
             hi += a.x * b.y - a.y * b.x;
           }
         }
-        qr = cr * hr - ci * hi;
-        qi = cr * hi + ci * hr;
+        // spelled out: the compiler may contract these either way, and Q is to have the same bits
+        // in each kernel that writes it, and those it had before
+        qr = fmaf(cr, hr, -(ci * hi));
+        qi = fmaf(ci, hr, cr * hi);
       }
       if (g.qtri && !block_diag) {
         // block-triangular Q for the quadratic form: psi^H Q psi sums each

@@ -32,3 +32,17 @@ def test_gram_tiles_give_the_same_bits(W):
     I0 = E.BiP(prob).run(mode=E.OUT_MAP)
     ref = A.MapGradient(prob).run(I0 - ibar / 2.0)["gH"][0].ravel()
     assert np.linalg.norm(few - ref) < 1e-3 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("W", [4, 8, 12, 20, 28])
+def test_gram_tiles_give_q_the_same_bits(W):
+    """dL/dV, whose S1 part comes through Q = G o conj(H) H^T of a complex H: the other atoms that
+    make the launch one of 64 x 64 tiles have no transition potential and add zeros."""
+    cfg = tiny_cfg(ny=64, nx=64, nz=3, ly=16.0, lx=16.0, alpha=0.012, theta=0.02, s=2, scan=(4, 5))
+    tp = tiny_problem(cfg, n_atoms=13, n_ch=2, seed=W, vscale=25.0, planes=[1] + [2] * 12, win_sizes=[W] + [32] * 12)
+    tp.H[tp.H_off[1]:] = 0
+    one = tiny_problem(cfg, n_atoms=1, n_ch=2, seed=W, vscale=25.0, planes=[1], win_sizes=[W])
+    one.V, one.tau, one.win_origin, one.H = tp.V, tp.tau[:1], tp.win_origin[:1], tp.H[:tp.H_off[1]]
+    ibar = np.random.default_rng(W).normal(size=20) * 1e-3
+    many, few = (_gpu_grad(cfg, p, ibar, E.RECON_MAGNITUDE)[0] for p in (tp, one))
+    assert np.linalg.norm(few[0]) > 0 and np.array_equal(few, many)
