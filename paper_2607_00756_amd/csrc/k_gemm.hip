@@ -87,14 +87,18 @@ constexpr double GRAM_FILL = 6.0, GRAM_PART = 0.03;
 //   168 -> 115 ms (1.28 PFLOP/s of hardware products); at W = 24, 16,207 beams
 //   x 960 scans x 72 channels, 26.8 -> 12.5 ms (with the tile order below).
 //   The Gram and store products of two-plane operands run two workgroups of 4
-//   waves per CU for the same reason; their other roles keep one, with four
-//   stages and the larger register sets of their running sums.
+//   waves per CU for the same reason, and their per-beam products 8 waves: with
+//   4, one a SIMD, the job stream's addresses had the accumulators copied through
+//   AGPRs in every chunk (BF16, 9 tiles of 648 chunks, no job groups: 0.57 ms
+//   before the stream, 0.89 with it, 0.57 so; 32,417 beams x 2304 scans, 6 windows
+//   of 32 x 32 x 3 channels: 14.4, 14.9 and 10.8 ms).  Their quadratic form keeps
+//   one of 4, with four stages and the larger register set of its running sums.
 // The quadratic form's waves are always 64 columns (r) wide and its tiles
 // 128: the order of its sum over r is the same in every configuration.
 template <int PREC, int EPI>
 struct Cfg {
-  static constexpr bool TWO = EPI == EPI_GRAMQ || EPI == EPI_STORE;
-  static constexpr int WM = 2, WN = 2, NBM = 4, NBN = 4, NS = TWO ? 2 : 4, WPE = TWO ? 2 : 1;
+  static constexpr bool TWO = EPI == EPI_GRAMQ || EPI == EPI_STORE, BEAM = EPI == EPI_ABS2_MAP || EPI == EPI_ABS2_BEAMS;
+  static constexpr int WM = 2, WN = BEAM ? 4 : 2, NBM = 4, NBN = BEAM ? 2 : 4, NS = TWO ? 2 : 4, WPE = TWO || BEAM ? 2 : 1;
 };
 template <int EPI>
 struct Cfg<BIP_PREC_FP32, EPI> {

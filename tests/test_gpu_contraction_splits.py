@@ -56,3 +56,12 @@ def test_splits_match_the_oracle(case, out_name, prec):
 @pytest.mark.parametrize("prec", [0, 1])
 def test_whole_contractions_match_the_oracle(prec):
     assert run(CASES[2], "map", prec, ckpt=1) <= TOL[prec]
+
+
+@pytest.mark.parametrize("prec", [2, 3])
+@pytest.mark.parametrize("out_name", ["direct", "beams"])
+@pytest.mark.parametrize("case", CASES, ids=["w8", "w12", "w16-20", "w4-24-8", "w32"])
+def test_single_16_bit_products_match_the_oracle(case, out_name, prec):
+    """BF16 and FP16 operands carry 2^-9 and 2^-12, four factors into an intensity; held to the
+    bounds of the tiny specimen's outputs in these precisions."""
+    assert run(case, out_name, prec) <= {2: 3e-2, 3: 1e-3}[prec]
