@@ -121,25 +121,30 @@ __global__ __launch_bounds__(NT) void k_focal_parents(float2* win, const FocalAt
 
 // Periodic kernel of the forward step along one axis, per atom (grid: atoms x
 // axes, M threads): c[d] = 1/M sum_k exp(2 pi i k d / M) exp(-i pi lambda dist
-// q_k^2), in FP64, rounded once; ker[atom][axis][FOCAL_M].
+// q_k^2), in FP64, rounded once; ker[atom][axis][FOCAL_M].  The M values of either
+// factor are evaluated once, one a thread (a sine and cosine per term, a thread's
+// M terms one after the other, made a focal map of one atom 20 us longer).
 constexpr int FOCAL_M = 128;
-__global__ void k_focal_kernel(const FocalAtom* __restrict__ atoms, const double* __restrict__ dist, double dy,
-                               double dx, double lambda, float2* __restrict__ ker) {
+__global__ __launch_bounds__(FOCAL_M) void k_focal_kernel(const FocalAtom* __restrict__ atoms,
+                                                          const double* __restrict__ dist, double dy, double dx,
+                                                          double lambda, float2* __restrict__ ker) {
+  __shared__ double2 step[FOCAL_M], root[FOCAL_M];
   const FocalAtom fa = atoms[blockIdx.x];
   const int M = fa.M, d = threadIdx.x;
-  if (d >= M) return;
   const double delta = blockIdx.y == 0 ? dy : dx;
   const double pi = 3.14159265358979323846;
+  if (d < M) {
+    const double q = (d < M / 2 ? d : d - M) / (M * delta);
+    sincos(-pi * lambda * dist[fa.atom] * q * q, &step[d].y, &step[d].x);
+    sincos(2.0 * pi * d / M, &root[d].y, &root[d].x);
+  }
+  __syncthreads();
+  if (d >= M) return;
   double re = 0.0, im = 0.0;
   for (int k = 0; k < M; ++k) {
-    const int ks = k < M / 2 ? k : k - M;
-    const double q = ks / (M * delta);
-    double ph = -pi * lambda * dist[fa.atom] * q * q;
-    ph += 2.0 * pi * ((k * d) & (M - 1)) / M;
-    double s, c;
-    sincos(ph, &s, &c);
-    re += c;
-    im += s;
+    const double2 a = step[k], w = root[(k * d) & (M - 1)];
+    re += a.x * w.x - a.y * w.y;
+    im += a.x * w.y + a.y * w.x;
   }
   ker[((int64_t)fa.atom * 2 + blockIdx.y) * FOCAL_M + d] = make_float2((float)(re / M), (float)(im / M));
 }
