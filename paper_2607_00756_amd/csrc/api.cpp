@@ -1352,6 +1352,7 @@ static int signal_atoms(bip_plan* p, const std::vector<int32_t>& atoms, int32_t 
   pa.gx = std::gcd(p->f, scan_sx);
   // probe coefficients of the whole aperture; retained beams scaled by f^2
   pa.cb = (float)((double)p->f * p->f / std::sqrt((double)p->g.ny * p->g.nx * p->B_full));
+  pa.n_cu = p->n_cu;
   pa.H = (const float2*)H;
   pa.n_ch = n_ch;
   for (size_t c = 0; c < chunks.size(); ++c) {

@@ -149,6 +149,8 @@ struct ProbeArgs {
   int64_t out_plane;
   const float2* H;          // U_n = H_n psi when the detector contraction follows
   int n_ch;
+  int n_cu;                 // compute units of the device
+  int zc;                   // channel groups of U_n (set by launch_probe_y)
 };
 
 // Focal back-propagation of S1: one atom's enlarged window and its plane.

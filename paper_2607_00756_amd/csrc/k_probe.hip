@@ -330,6 +330,12 @@ __global__ __launch_bounds__(NT, NV <= 2 ? 4 : NV == 3 ? 3 : 2) void k_probe_fol
 // operand's rows are the scans of the atom's mask, (i_u, i_v) row by row (all
 // scans at f = 1); U_n's are all scans, those off the mask not written (the
 // products mask them).
+// The channels of U_n are dealt over zc workgroups, each with a DFT of its own, while
+// that leaves two workgroups a CU: 17 of them that wrote 34 channels of 65 x 17 scans of
+// an 8 x 8 window one after the other took 194 us (FP16; 43 at the probe's own kernel of
+// focal maps, one workgroup a scan, which this one replaced), 39 us in 30 groups.  With
+// four a CU the DFT repeated for 768 workgroups of 3 channels cost more than it gave (170
+// and 240 us).
 template <int PREC, bool U, int NV, bool HALF>
 __global__ __launch_bounds__(NT) void k_probe_y(const ProbeArgs pa) {
   extern __shared__ float2 sm[];
@@ -337,7 +343,8 @@ __global__ __launch_bounds__(NT) void k_probe_y(const ProbeArgs pa) {
   const int CH = min((nr + 3) & ~3, FOLD_CH);
   float2* sG = sm;            // [CH][RT]
   float2* sT = sm + CH * RT;  // [Sy]
-  const ProbeJob job = pa.jobs[blockIdx.z];
+  const int zc = U ? pa.zc : 1, cg = U ? (int)blockIdx.z % zc : 0;  // channel group
+  const ProbeJob job = pa.jobs[blockIdx.z / zc];
   const int W2 = job.W * job.W;
   const int kd = job.kd;
   const int r0 = blockIdx.x * RT;
@@ -386,7 +393,7 @@ __global__ __launch_bounds__(NT) void k_probe_y(const ProbeArgs pa) {
   const bool in = ro < kd, live_o = ro < W2;
   auto put = [&](int rho, float re, float im) {
     if constexpr (U) {
-      for (int n = 0; n < pa.n_ch; ++n) {
+      for (int n = pa.n_ch * cg / zc; n < pa.n_ch * (cg + 1) / zc; ++n) {
         const float2 hn = live_o ? pa.H[job.h_off + (int64_t)n * W2 + ro] : make_float2(0.f, 0.f);
         store_planes<PREC>(pa.out, job.out_off + ((int64_t)n * pa.Ppad + rho) * kd + ro,
                            pa.out_plane, hn.x * re - hn.y * im, hn.x * im + hn.y * re);
@@ -527,14 +534,20 @@ hipError_t launch_probe_fold_x(const ProbeArgs& pa, int unit0, int n_units, int 
 hipError_t launch_probe_y(const ProbeArgs& pa, int prec, bool u, int max_kd, int max_cnu, int max_cnv, int n_jobs,
                           hipStream_t s) {
   if (n_jobs <= 0 || max_cnu <= 0 || max_cnv <= 0) return hipSuccess;
-  const dim3 grid((unsigned)((max_kd + RT - 1) / RT), (unsigned)max_cnv, (unsigned)n_jobs);
+  ProbeArgs q = pa;
+  q.zc = 1;
+  if (u) {  // up to two workgroups a CU
+    const int64_t wgs = (int64_t)((max_kd + RT - 1) / RT) * max_cnv * n_jobs;
+    q.zc = (int)std::max<int64_t>(1, std::min<int64_t>(pa.n_ch, 2 * pa.n_cu / wgs));
+  }
+  const dim3 grid((unsigned)((max_kd + RT - 1) / RT), (unsigned)max_cnv, (unsigned)(n_jobs * q.zc));
   const size_t lds = ((size_t)std::min((pa.Sy / pa.gy + 3) & ~3, FOLD_CH) * RT + pa.Sy) * sizeof(float2);
   const int nv = (max_cnu + 63) / 64;
   if (pa.half && (pa.gx != 1 || pa.gy != 1 || max_cnu != pa.Sy || max_cnv != pa.Sx)) return hipErrorInvalidValue;
 #define PYV(P, UU, NV)                                                          \
   if (nv == NV)                                                                 \
-    return pa.half ? launch_lds(k_probe_y<P, UU, NV, true>, grid, lds, pa, s)   \
-                   : launch_lds(k_probe_y<P, UU, NV, false>, grid, lds, pa, s);
+    return pa.half ? launch_lds(k_probe_y<P, UU, NV, true>, grid, lds, q, s)    \
+                   : launch_lds(k_probe_y<P, UU, NV, false>, grid, lds, q, s);
 #define PY(P)                                                                                  \
   if (prec == P) {                                                                             \
     if (u) {                                                                                   \

@@ -65,3 +65,26 @@ def test_single_16_bit_products_match_the_oracle(case, out_name, prec):
     """BF16 and FP16 operands carry 2^-9 and 2^-12, four factors into an intensity; held to the
     bounds of the tiny specimen's outputs in these precisions."""
     assert run(case, out_name, prec) <= {2: 3e-2, 3: 1e-3}[prec]
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("focal", [False, True])
+@pytest.mark.parametrize("wins,n_ch,scan", [([8], 34, (5, 3)), ([4, 12], 7, (1, 2)), ([8], 2, (3, 64))])
+def test_channel_groups_match_the_oracle(wins, n_ch, scan, focal, prec):
+    """U_n written by several workgroups of channels: more groups than channels wanted, groups of
+    unequal size, few groups; tolerances as above."""
+    import dataclasses
+
+    import torch
+    from oracle import eels as E
+    from paper_2607_00756_amd import bip
+    cfg = dataclasses.replace(tiny_cfg(ny=64, nx=64, nz=3, ly=8.0, lx=8.0, s=2, scan=scan), focal=focal)
+    tp = tiny_problem(cfg, n_atoms=len(wins), n_ch=n_ch, seed=n_ch, vscale=25.0, planes=[2, 1][:len(wins)], win_sizes=wins)
+    plan = bip.Plan.from_config(cfg, tp.tau, tp.win_size, tp.win_origin)
+    plan.build_smatrix(torch.from_numpy(tp.V).cuda())
+    out = torch.full((scan[0] * scan[1], plan.ndet), float("nan"), dtype=torch.float32, device="cuda")
+    plan.eels_signal(n_ch, torch.from_numpy(tp.H).cuda(), tp.H_off, scan, bip.OUT_BEAMS, prec, out)
+    got = out.cpu().numpy().astype(np.float64)
+    plan.close()
+    want = E.BiP(as_oracle_problem(tp)).run(mode=E.OUT_BEAMS)
+    assert np.linalg.norm(got - want) <= TOL[prec] * np.linalg.norm(want)
